@@ -101,11 +101,18 @@ __device__ __forceinline__ long long uniform_ll(long long v)
                        (unsigned int)__builtin_amdgcn_readfirstlane((int)(unsigned int)u));
 }
 
+// Vectors per lane per tile of packed rows, whatever the rule's: more would
+// spill beside the unpacked scans of the same kernel.
+constexpr int BATCH_PACK_U = 2;
+
 template <bool STATS, int HIST, int U>
 __device__ void batch_scan(const BatchItem &it, long long u0, long long u1, Lane &L, Wave &W,
                            const Hist &H)
 {
-    scan_units<STATS, HIST, CUBE_ACCUM_FP64MERGE, U>(it.g, u0, u1, L, W, H);
+    if (it.g.pack.cb > 0)
+        scan<STATS, HIST, CUBE_ACCUM_FP64MERGE, BATCH_PACK_U, true>(it.g, u0, u1, L, W, H);
+    else
+        scan<STATS, HIST, CUBE_ACCUM_FP64MERGE, U, false>(it.g, u0, u1, L, W, H);
 }
 
 // The LDS histogram flush of the batched launch, which keeps its LDS
@@ -734,6 +741,7 @@ int cube_batch_enqueue(cube_batch_t *b, const cube_query_t *q, int32_t n, void *
         g.seg_len = seg;
         g.segs = box.n == 0 ? 1 : (g.row_len + seg - 1) / seg;
         g.n_units = box.n == 0 ? 0 : g.ny * g.nz * g.segs;
+        if (g.n_units) pack_rows(g, b->threads, BATCH_PACK_U);
         long long upt = tv / seg;
         if (upt < 1) upt = 1;
         upts[(size_t)i] = upt;

@@ -380,6 +380,7 @@ void collapse(const Box &b, Geom *g)
     g->sy = sy;
     g->sz = sz;
     g->n_total = b.n;
+    g->pack.cb = 0;
 }
 
 // The partition of a fully automatic launch (no explicit shape, no tuned
@@ -444,6 +445,12 @@ int make_plan(const Box &b, bool stats, int hist_kind_req, int nbins, Plan *p)
         }
     }
     p->lds = pass_lds_bytes(stats, p->hist, nbins, p->copies_log2, threads);
+    // Which kernel runs if the rows need no cutting (the usual case), for the
+    // occupancy below.
+    Geom whole = p->g;
+    cut_rows(whole, 1);
+    pack_rows(whole, threads, p->unroll);
+    const bool packed = whole.pack.cb > 0;
     p->chunks = 0;
     if (chunk_log2 > 0 && p->hist != HIST_HOT && accum_mode() == CUBE_ACCUM_FP64MERGE) {
         // Dynamic partition: one persistent wave of blocks (the tuned blocks
@@ -457,7 +464,8 @@ int make_plan(const Box &b, bool stats, int hist_kind_req, int nbins, Plan *p)
             if (p->lds + 4096 <= 160 * 1024 || p->hist != HIST_LDS || p->copies_log2 == 0) break;
             --p->copies_log2;
         }
-        const int fit = pass_blocks_per_cu(stats, p->hist, threads, p->lds, p->unroll, true);
+        const int fit =
+            pass_blocks_per_cu(stats, p->hist, threads, p->lds, p->unroll, true, packed);
         const long long chunks = chunks_of(b.n, chunk_log2);
         if (g_blocks == 0) {
             const int per_cu = resident > 0 && resident < fit ? resident : fit;
@@ -469,9 +477,11 @@ int make_plan(const Box &b, bool stats, int hist_kind_req, int nbins, Plan *p)
         p->chunks = (int)chunks;
         p->blocks = (int)blocks;
         cut_rows(p->g, chunks);
+        pack_rows(p->g, threads, p->unroll);
         return CUBE_OK;
     }
-    const int bpc = pass_blocks_per_cu(stats, p->hist, threads, p->lds, p->unroll);
+    const int bpc =
+        pass_blocks_per_cu(stats, p->hist, threads, p->lds, p->unroll, false, packed);
     // At least four blocks per CU over the launch: with one resident
     // histogram block per CU, four waves of blocks measured faster than one
     // persistent wave on large boxes (shorter per-block ranges, overlapped
@@ -506,6 +516,7 @@ int make_plan(const Box &b, bool stats, int hist_kind_req, int nbins, Plan *p)
     if ((size_t)blocks * (threads / 64) > REC_CAP) blocks = (long long)(REC_CAP / (threads / 64));
     p->blocks = (int)blocks;
     cut_rows(p->g, blocks);
+    pack_rows(p->g, threads, p->unroll);
     return CUBE_OK;
 }
 
@@ -528,6 +539,13 @@ void cut_rows(Geom &g, long long blocks)
     g.seg_len = seg_len;
     g.segs = segs;
     g.n_units = rows * segs;
+    g.pack.cb = 0;
+}
+
+void pack_rows(Geom &g, int threads, int unroll)
+{
+    const int mis = (int)((16 - ((uintptr_t)g.ptr & 15)) & 15) >> 2;
+    g.pack = row_pack(g.row_len, g.ny, g.nz, g.sy, g.sz, g.segs, mis, threads, unroll);
 }
 
 __global__ void k_write_empty(cube_stats_t *out, unsigned long long *counts, int nbins)

@@ -26,6 +26,7 @@
 namespace cube {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));  // any voxel's address
 
 constexpr int MAX_WAVES = 16;   // 1024 threads per block at most
 
@@ -649,6 +650,109 @@ __device__ __forceinline__ void scan_units(const Geom &g, long long u0, long lon
                 ++z;
             }
         }
+    }
+}
+
+// Visit the rows [u0, u1) of a packed geometry (cube_rows.h): `f` is called
+// with 4 * U voxels per lane, lanes without a voxel padded with NaN, and
+// f.pair() after every second call and at the end.  Bound by HBM on long
+// rows, by the latency of a few tiles on small boxes.  Measured against the
+// scan of one row at a time (scan_units), whole calls: a 1187 x 911 x 263
+// box in rows of 2048, statistics + 1024 bins 1.71 -> 0.275 ms (4.1 TB/s);
+// a 61 x 47 x 200 box, statistics 0.180 -> 0.026 ms; the median of a
+// 941 x 937 x 240 box 3.76 -> 0.55 ms.
+//
+// PIPE: the next tile's loads are issued before a tile is processed (twice the
+// load registers); the selection passes, which only count, run faster without.
+template <int U, bool PIPE, class F>
+__device__ __forceinline__ void scan_rows(const Geom &g, long long u0, long long u1, F &f)
+{
+    if (u0 >= u1) return;
+    const RowPack &pk = g.pack;
+    const unsigned int lr = threadIdx.x / (unsigned int)pk.cb;
+    const unsigned int lc = threadIdx.x - lr * (unsigned int)pk.cb;
+    const unsigned int ny = (unsigned int)g.ny, r0 = (unsigned int)u0, r1 = (unsigned int)u1;
+    RowLane ln = row_lane(pk, g.ptr, g.sy, g.sz, ny, r0, r1, lr);
+    int s[U], d[U];
+    unsigned int edge = 0u;  // bit k: this wavefront masks voxels of its k-th vector
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+        row_vector(pk, (int)g.row_len, lc, k & (pk.cg - 1), &s[k], &d[k]);
+        if (__builtin_amdgcn_ballot_w64(d[k] != 0)) edge |= 1u << k;
+    }
+    auto load = [&](f4 (&v)[U]) {
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            v[k] = f4{qnan(), qnan(), qnan(), qnan()};
+            if (ln.row < ln.row_end) v[k] = __builtin_nontemporal_load((const f4u *)(ln.p + s[k]));
+            if (((k + 1) & (pk.cg - 1)) == 0) row_advance(pk, ny, ln);
+        }
+    };
+    auto take = [&](const f4 (&v)[U]) {
+        float x[4 * U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            x[4 * k + 0] = v[k].x;
+            x[4 * k + 1] = v[k].y;
+            x[4 * k + 2] = v[k].z;
+            x[4 * k + 3] = v[k].w;
+            if ((edge >> k) & 1u) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    x[4 * k + i] = row_own(i, d[k]) ? x[4 * k + i] : qnan();
+            }
+        }
+        f(x);
+    };
+    const unsigned int tiles = row_tiles(pk, r0, r1, U);
+    f4 va[U];
+    if constexpr (!PIPE) {
+        for (unsigned int k = 0; k < tiles; ++k) {
+            load(va);
+            take(va);
+            f.pair();
+        }
+        return;
+    }
+    f4 vb[U];
+    load(va);
+    unsigned int k = 0;
+    while (true) {
+        if (k + 1 < tiles) load(vb);
+        take(va);
+        if (++k == tiles) break;
+        if (k + 1 < tiles) load(va);
+        take(vb);
+        f.pair();
+        if (++k == tiles) break;
+    }
+    f.pair();
+}
+
+// The pass's step for scan_rows.
+template <bool STATS, int HIST, int ACC>
+struct PassStep {
+    Lane &L;
+    Wave &W;
+    const Hist &H;
+    template <int NV>
+    __device__ __forceinline__ void operator()(const float (&x)[NV])
+    {
+        process<STATS, HIST, ACC, NV>(x, L, W, H);
+    }
+    __device__ __forceinline__ void pair() { fold<STATS, ACC>(L); }
+};
+
+// Scan the work units [u0, u1) of a box in the form its geometry asks for.
+template <bool STATS, int HIST, int ACC, int U, bool PACKED>
+__device__ __forceinline__ void scan(const Geom &g, long long u0, long long u1, Lane &L, Wave &W,
+                                     const Hist &H)
+{
+    if constexpr (PACKED) {
+        PassStep<STATS, HIST, ACC> f = {L, W, H};
+        scan_rows<U, true>(g, u0, u1, f);
+    } else {
+        scan_units<STATS, HIST, ACC, U>(g, u0, u1, L, W, H);
     }
 }
 

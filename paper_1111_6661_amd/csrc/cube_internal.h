@@ -9,6 +9,7 @@
 #include <string>
 #include <vector>
 
+#include "cube_rows.h"
 #include "cubestats.h"
 
 namespace cube {
@@ -48,11 +49,14 @@ struct HistRange {
 // row (y, z) starting at ptr + y*sy + z*sz.  Rows are cut into `segs`
 // segments of `seg_len` floats (seg_len a multiple of 4); a unit of work is
 // one segment of one row, numbered u = (z*ny + y)*segs + s.
+// Rows shorter than one block tile are packed onto the block (cube_rows.h,
+// pack.cb > 0).
 struct Geom {
     const float *ptr;
     int64_t row_len, ny, nz, sy, sz;
     int64_t seg_len, segs, n_units;
     uint64_t n_total;
+    RowPack pack;
 };
 
 // Histogram modes of a pass: none; LDS sub-histograms (every in-range voxel
@@ -102,9 +106,10 @@ __host__ __device__ inline int dyn_ring_offset_words(bool lds_hist, int nbins, i
 }
 
 // Occupancy of one pass configuration: resident blocks per CU.
-// `dynamic`: of the dynamic-partition kernel.
+// `dynamic`: of the dynamic-partition kernel; `packed`: of the kernel for
+// packed rows.
 int pass_blocks_per_cu(bool stats, int hist, int threads, size_t lds_bytes, int unroll,
-                       bool dynamic = false);
+                       bool dynamic = false, bool packed = false);
 
 // ------------------------------------------------ host helpers (cube_capi.hip)
 // A validated box: extents, pitches (defaults resolved) and voxel count.
@@ -171,6 +176,9 @@ int make_plan(const Box &b, bool stats, int hist_kind_req, int nbins, Plan *p);
 // Cut the rows of a collapsed box into segments so that there are at least
 // `blocks` work units (a row is never cut below 4 floats).
 void cut_rows(Geom &g, long long blocks);
+// Pack the rows of a cut geometry onto blocks of `threads` threads that take
+// `unroll` vectors per lane per tile, where that is the faster form.
+void pack_rows(Geom &g, int threads, int unroll);
 
 // One pass over a validated device box on stream `s`, with the calling
 // stream's workspace: statistics (to dev_out) and/or a histogram (HIST_NONE

@@ -12,7 +12,7 @@
 
 namespace cube {
 
-template <bool STATS, int HIST, int ACC, int U>
+template <bool STATS, int HIST, int ACC, int U, bool PACKED>
 __global__ void __launch_bounds__(1024) k_pass(PassArgs a)
 {
     extern __shared__ unsigned int lds[];
@@ -50,9 +50,9 @@ __global__ void __launch_bounds__(1024) k_pass(PassArgs a)
     Wave W = {0.f, ACC == CUBE_ACCUM_NAIVE32 ? 1 : 0, 0ull, 0ull, 0ull};
 
     if (HIST == HIST_NONE || hist_on)
-        scan_units<STATS, HIST, ACC, U>(g, u0, u1, L, W, H);
+        scan<STATS, HIST, ACC, U, PACKED>(g, u0, u1, L, W, H);
     else  // an invalid range bins nothing: count valid voxels only
-        scan_units<STATS, HIST_NONE, ACC, U>(g, u0, u1, L, W, H);
+        scan<STATS, HIST_NONE, ACC, U, PACKED>(g, u0, u1, L, W, H);
 
     write_wave_record<STATS, ACC>(L, W, &a.recs[(long long)blockIdx.x * nw + wid]);
     if (HIST == HIST_LDS) hist_flush(lds, a.nbins, a.copies_log2, a.hist_acc);
@@ -95,7 +95,7 @@ __global__ void __launch_bounds__(1024) k_pass(PassArgs a)
 // histogram is kept over all of a block's chunks and flushed once.  The
 // moments are accumulated as in CUBE_ACCUM_FP64MERGE (the planner uses this
 // pass for that mode only), without the hot-bin histogram form.
-template <bool STATS, int HIST, int U>
+template <bool STATS, int HIST, int U, bool PACKED>
 __global__ void __launch_bounds__(1024) k_pass_dyn(PassArgs a)
 {
     extern __shared__ unsigned int lds[];
@@ -151,9 +151,9 @@ __global__ void __launch_bounds__(1024) k_pass_dyn(PassArgs a)
         Lane L = {INFINITY, -INFINITY, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         Wave W = {0.f, 0, 0ull, 0ull, 0ull};
         if (HIST == HIST_NONE || hist_on)
-            scan_units<STATS, HIST, ACC, U>(g, u0, u1, L, W, H);
+            scan<STATS, HIST, ACC, U, PACKED>(g, u0, u1, L, W, H);
         else
-            scan_units<STATS, HIST_NONE, ACC, U>(g, u0, u1, L, W, H);
+            scan<STATS, HIST_NONE, ACC, U, PACKED>(g, u0, u1, L, W, H);
         write_wave_record<STATS, ACC>(L, W, &ring[filled * nw + wid]);
         if (tid == 0) s_ids[filled] = c;
         __syncthreads();  // every part written; every thread has read s_chunk
@@ -212,59 +212,74 @@ size_t pass_lds_bytes(bool stats, int hist, int nbins, int copies_log2, int thre
     return 0;
 }
 
-template <bool STATS, int HIST, int ACC>
-static const void *kernel_of(int unroll)
+template <bool STATS, int HIST, int ACC, int U>
+static const void *kernel_of(bool packed)
 {
-    if (unroll == 2) return reinterpret_cast<const void *>(&k_pass<STATS, HIST, ACC, 2>);
-    return reinterpret_cast<const void *>(&k_pass<STATS, HIST, ACC, 4>);
+    return packed ? reinterpret_cast<const void *>(&k_pass<STATS, HIST, ACC, U, true>)
+                  : reinterpret_cast<const void *>(&k_pass<STATS, HIST, ACC, U, false>);
+}
+
+template <bool STATS, int HIST, int ACC>
+static const void *kernel_of(int unroll, bool packed)
+{
+    return unroll == 2 ? kernel_of<STATS, HIST, ACC, 2>(packed)
+                       : kernel_of<STATS, HIST, ACC, 4>(packed);
+}
+
+template <bool STATS, int HIST, int U>
+static const void *dyn_kernel_of(bool packed)
+{
+    return packed ? reinterpret_cast<const void *>(&k_pass_dyn<STATS, HIST, U, true>)
+                  : reinterpret_cast<const void *>(&k_pass_dyn<STATS, HIST, U, false>);
 }
 
 template <bool STATS, int HIST>
-static const void *dyn_kernel_of(int unroll)
+static const void *dyn_kernel_of(int unroll, bool packed)
 {
-    if (unroll == 2) return reinterpret_cast<const void *>(&k_pass_dyn<STATS, HIST, 2>);
-    return reinterpret_cast<const void *>(&k_pass_dyn<STATS, HIST, 4>);
+    return unroll == 2 ? dyn_kernel_of<STATS, HIST, 2>(packed)
+                       : dyn_kernel_of<STATS, HIST, 4>(packed);
 }
 
 // The dynamic-partition kernels: FP64MERGE moments, no hot-bin form.
-static const void *pick_dyn(bool stats, int hist, int u)
+static const void *pick_dyn(bool stats, int hist, int u, bool pk)
 {
     if (stats) {
-        if (hist == HIST_NONE) return dyn_kernel_of<true, HIST_NONE>(u);
-        if (hist == HIST_LDS) return dyn_kernel_of<true, HIST_LDS>(u);
-        return dyn_kernel_of<true, HIST_GLOBAL>(u);
+        if (hist == HIST_NONE) return dyn_kernel_of<true, HIST_NONE>(u, pk);
+        if (hist == HIST_LDS) return dyn_kernel_of<true, HIST_LDS>(u, pk);
+        return dyn_kernel_of<true, HIST_GLOBAL>(u, pk);
     }
-    if (hist == HIST_LDS) return dyn_kernel_of<false, HIST_LDS>(u);
-    return dyn_kernel_of<false, HIST_GLOBAL>(u);
+    if (hist == HIST_LDS) return dyn_kernel_of<false, HIST_LDS>(u, pk);
+    return dyn_kernel_of<false, HIST_GLOBAL>(u, pk);
 }
 
-static const void *pick(bool stats, int hist, int acc, int u)
+static const void *pick(bool stats, int hist, int acc, int u, bool pk)
 {
     const bool naive = acc == CUBE_ACCUM_NAIVE32;
     if (stats) {
         if (hist == HIST_NONE)
-            return naive ? kernel_of<true, HIST_NONE, CUBE_ACCUM_NAIVE32>(u)
-                         : kernel_of<true, HIST_NONE, CUBE_ACCUM_FP64MERGE>(u);
+            return naive ? kernel_of<true, HIST_NONE, CUBE_ACCUM_NAIVE32>(u, pk)
+                         : kernel_of<true, HIST_NONE, CUBE_ACCUM_FP64MERGE>(u, pk);
         if (hist == HIST_LDS)
-            return naive ? kernel_of<true, HIST_LDS, CUBE_ACCUM_NAIVE32>(u)
-                         : kernel_of<true, HIST_LDS, CUBE_ACCUM_FP64MERGE>(u);
+            return naive ? kernel_of<true, HIST_LDS, CUBE_ACCUM_NAIVE32>(u, pk)
+                         : kernel_of<true, HIST_LDS, CUBE_ACCUM_FP64MERGE>(u, pk);
         if (hist == HIST_HOT)
-            return naive ? kernel_of<true, HIST_HOT, CUBE_ACCUM_NAIVE32>(u)
-                         : kernel_of<true, HIST_HOT, CUBE_ACCUM_FP64MERGE>(u);
-        return naive ? kernel_of<true, HIST_GLOBAL, CUBE_ACCUM_NAIVE32>(u)
-                     : kernel_of<true, HIST_GLOBAL, CUBE_ACCUM_FP64MERGE>(u);
+            return naive ? kernel_of<true, HIST_HOT, CUBE_ACCUM_NAIVE32>(u, pk)
+                         : kernel_of<true, HIST_HOT, CUBE_ACCUM_FP64MERGE>(u, pk);
+        return naive ? kernel_of<true, HIST_GLOBAL, CUBE_ACCUM_NAIVE32>(u, pk)
+                     : kernel_of<true, HIST_GLOBAL, CUBE_ACCUM_FP64MERGE>(u, pk);
     }
-    if (hist == HIST_LDS) return kernel_of<false, HIST_LDS, CUBE_ACCUM_FP64MERGE>(u);
-    if (hist == HIST_HOT) return kernel_of<false, HIST_HOT, CUBE_ACCUM_FP64MERGE>(u);
-    return kernel_of<false, HIST_GLOBAL, CUBE_ACCUM_FP64MERGE>(u);
+    if (hist == HIST_LDS) return kernel_of<false, HIST_LDS, CUBE_ACCUM_FP64MERGE>(u, pk);
+    if (hist == HIST_HOT) return kernel_of<false, HIST_HOT, CUBE_ACCUM_FP64MERGE>(u, pk);
+    return kernel_of<false, HIST_GLOBAL, CUBE_ACCUM_FP64MERGE>(u, pk);
 }
 
 int pass_blocks_per_cu(bool stats, int hist, int threads, size_t lds_bytes, int unroll,
-                       bool dynamic)
+                       bool dynamic, bool packed)
 {
     int n = 0;
-    const void *k = dynamic && hist != HIST_HOT ? pick_dyn(stats, hist, unroll)
-                                                : pick(stats, hist, CUBE_ACCUM_FP64MERGE, unroll);
+    const void *k = dynamic && hist != HIST_HOT
+                        ? pick_dyn(stats, hist, unroll, packed)
+                        : pick(stats, hist, CUBE_ACCUM_FP64MERGE, unroll, packed);
     if (lds_bytes > 64 * 1024 &&
         hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes) !=
             hipSuccess)
@@ -279,8 +294,9 @@ hipError_t launch_pass(const PassArgs &a, bool stats, int hist, int threads, int
 {
     if (a.n_chunks > 0 && (hist == HIST_HOT || a.accum_mode != CUBE_ACCUM_FP64MERGE))
         return hipErrorInvalidValue;  // the planner never asks for these
-    const void *k = a.n_chunks > 0 ? pick_dyn(stats, hist, unroll)
-                                   : pick(stats, hist, a.accum_mode, unroll);
+    const bool packed = a.g.pack.cb > 0;
+    const void *k = a.n_chunks > 0 ? pick_dyn(stats, hist, unroll, packed)
+                                   : pick(stats, hist, a.accum_mode, unroll, packed);
     if (lds_bytes > 64 * 1024) {
         // More than the default dynamic LDS limit of a launch.
         hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize,

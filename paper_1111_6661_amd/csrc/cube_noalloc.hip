@@ -101,6 +101,7 @@ extern "C" int cube_stats_hist_noalloc(const float *ptr, const int64_t *dims, fl
             p.chunks = (int)NA_RECS;
             if (p.blocks > p.chunks) p.blocks = p.chunks;
             cut_rows(p.g, p.chunks);
+            pack_rows(p.g, p.threads, p.unroll);
         }
     } else if ((long long)p.blocks * waves > (long long)NA_RECS) {
         int t = 0, bl = 0, c = 0, u = 0;
@@ -117,6 +118,7 @@ extern "C" int cube_stats_hist_noalloc(const float *ptr, const int64_t *dims, fl
             return fail(CUBE_EINVAL, "box of %llu voxels too large for the allocation-free scratch",
                         (unsigned long long)b.n);
         cut_rows(p.g, p.blocks);
+        pack_rows(p.g, p.threads, p.unroll);
     }
 
     WaveRec *recs = (WaveRec *)base;

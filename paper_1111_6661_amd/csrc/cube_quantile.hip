@@ -119,7 +119,7 @@ struct QuantStep {
     }
 };
 
-template <int NL>
+template <int NL, bool PACKED>
 __global__ void __launch_bounds__(Q_THREADS) k_quant(QuantArgs a)
 {
     extern __shared__ unsigned int lds[];
@@ -151,7 +151,7 @@ __global__ void __launch_bounds__(Q_THREADS) k_quant(QuantArgs a)
     st.clog = a.copies_log2;
     st.cbase = tid & 63 & ((1 << a.copies_log2) - 1);
     st.valid = 0u;
-    scan_box(a.g, st, a.claim);
+    scan_box<PACKED>(a.g, st, a.claim);
     // Every lane of a wavefront holds the same count (sums of ballots).
     if (NL == 0 && (tid & 63) == 0 && st.valid) atomicAdd(&s_valid, st.valid);
     __syncthreads();
@@ -165,6 +165,13 @@ __global__ void __launch_bounds__(Q_THREADS) k_quant(QuantArgs a)
         if (sum) atomicAdd(&a.acc[b], (unsigned long long)sum);
     }
     if (NL == 0 && tid == 0 && s_valid) atomicAdd(a.n_valid, (unsigned long long)s_valid);
+}
+
+template <int NL>
+const void *quant_kernel(bool packed)
+{
+    return packed ? reinterpret_cast<const void *>(&k_quant<NL, true>)
+                  : reinterpret_cast<const void *>(&k_quant<NL, false>);
 }
 
 struct QuantWorkspace {
@@ -233,10 +240,11 @@ int quant_pass(QuantWorkspace *w, const Box &box, const Geom &g, int nl, int shi
     a.tab = w->tab;
     a.acc = w->acc;
     a.n_valid = w->acc + Q_ACC;
-    const void *k = nl == 0   ? reinterpret_cast<const void *>(&k_quant<0>)
-                    : nl == 1 ? reinterpret_cast<const void *>(&k_quant<1>)
-                    : nl == 2 ? reinterpret_cast<const void *>(&k_quant<2>)
-                              : reinterpret_cast<const void *>(&k_quant<3>);
+    const bool packed = g.pack.cb > 0;
+    const void *k = nl == 0   ? quant_kernel<0>(packed)
+                    : nl == 1 ? quant_kernel<1>(packed)
+                    : nl == 2 ? quant_kernel<2>(packed)
+                              : quant_kernel<3>(packed);
     if (lds > 64 * 1024 &&
         (e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) !=
             hipSuccess)
@@ -299,7 +307,7 @@ int run_quantiles(const Box &box, const double *q, int m, double *out, uint64_t 
     const int cl = scan_chunk_log2(box);
     const long long units = cl ? chunks_of(box.n, cl) : 0;
     const long long grid = (long long)cu_count() * 2;
-    scan_geom(box, units > grid ? units : grid, &P.g);
+    scan_geom(box, units > grid ? units : grid, Q_THREADS, &P.g);
     rc = quantiles_run(P, q, m, out, n_valid_out, w->h_tab, 1);
     if (rc == 1) return fail(CUBE_EINVAL, "no valid voxel");
     if (rc == CUBE_OK) g_quant_reads = P.reads;

@@ -96,15 +96,38 @@ struct Claim {
     int nc;
 };
 
-// Visit every voxel of the box once (called by every thread of the block).
+// The scan of units [u0, u1) in the form the geometry asks for.
 template <class Step>
+struct PlainStep {  // scan_rows' step without a fold
+    Step &step;
+    template <int NV>
+    __device__ __forceinline__ void operator()(const float (&x)[NV])
+    {
+        step(x);
+    }
+    __device__ __forceinline__ void pair() {}
+};
+template <bool PACKED, class Step>
+__device__ __forceinline__ void scan_some(const Geom &g, long long u0, long long u1, Step &step)
+{
+    if constexpr (PACKED) {
+        PlainStep<Step> f = {step};
+        scan_rows<SEL_U, false>(g, u0, u1, f);
+    } else {
+        scan_units_of(g, u0, u1, step);
+    }
+}
+
+// Visit every voxel of the box once (called by every thread of the block).
+// PACKED: the geometry's rows are packed (pack_rows).
+template <bool PACKED, class Step>
 __device__ __forceinline__ void scan_box(const Geom &g, Step &step, const Claim &cl)
 {
     if (cl.nc <= 0) {
         const unsigned long long G = gridDim.x;
         const long long u0 = (long long)(((unsigned long long)g.n_units * blockIdx.x) / G);
         const long long u1 = (long long)(((unsigned long long)g.n_units * (blockIdx.x + 1)) / G);
-        scan_units_of(g, u0, u1, step);
+        scan_some<PACKED>(g, u0, u1, step);
         return;
     }
     __shared__ int s_chunk;
@@ -119,7 +142,7 @@ __device__ __forceinline__ void scan_box(const Geom &g, Step &step, const Claim 
         if (tid == 0 && early) next = atomicAdd(cl.ctr, 1u);
         const long long u0 = (long long)(((unsigned long long)g.n_units * c) / cl.nc);
         const long long u1 = (long long)(((unsigned long long)g.n_units * (c + 1)) / cl.nc);
-        scan_units_of(g, u0, u1, step);
+        scan_some<PACKED>(g, u0, u1, step);
         __syncthreads();  // every thread has read s_chunk
         if (tid == 0) s_chunk = (int)(early ? next : atomicAdd(cl.ctr, 1u));
         __syncthreads();
@@ -129,7 +152,7 @@ __device__ __forceinline__ void scan_box(const Geom &g, Step &step, const Claim 
 // The geometry of a selection pass over a validated box: rows cut into
 // segments so that there are at least `blocks` work units (one per block,
 // or one per chunk of a dynamic partition).
-inline void scan_geom(const Box &b, long long blocks, Geom *g)
+inline void scan_geom(const Box &b, long long blocks, int threads, Geom *g)
 {
     collapse(b, g);
     const long long rows = g->ny * g->nz;
@@ -139,6 +162,15 @@ inline void scan_geom(const Box &b, long long blocks, Geom *g)
     g->seg_len = seg_len;
     g->segs = (g->row_len + seg_len - 1) / seg_len;
     g->n_units = rows * g->segs;
+    pack_rows(*g, threads, SEL_U);
+}
+
+// Whether the rows of box b, not cut, are packed.
+inline bool scan_packs(const Box &b, int threads)
+{
+    Geom g;
+    scan_geom(b, 1, threads, &g);
+    return g.pack.cb > 0;
 }
 
 // The chunk size (log2 voxels; 0: static) of a selection pass over box b:

@@ -132,6 +132,7 @@ struct NextStep {
     }
 };
 
+template <bool PACKED>
 __global__ void __launch_bounds__(1024) k_select(SelectArgs a)
 {
     extern __shared__ unsigned int lds[];
@@ -166,7 +167,7 @@ __global__ void __launch_bounds__(1024) k_select(SelectArgs a)
         CountStep<true> cc;
         cc.c = c;
         cc.valid = 0;
-        scan_box(a.g, cc, a.claim);
+        scan_box<PACKED>(a.g, cc, a.claim);
         __syncthreads();
         if (tid == 0) {
             a.cand_n[blockIdx.x] = min(s_cnt, a.cand_cap);
@@ -182,7 +183,7 @@ __global__ void __launch_bounds__(1024) k_select(SelectArgs a)
             select_step<1>(xv, cs.valid, c);
         }
     } else {
-        scan_box(a.g, cs, a.claim);
+        scan_box<PACKED>(a.g, cs, a.claim);
     }
     const unsigned long long valid = cs.valid;
     const int lane = tid & 63;
@@ -279,6 +280,7 @@ __global__ void __launch_bounds__(1024) k_select(SelectArgs a)
 // The voxel of the next rank when the last histogram did not hold it: the
 // smallest valid key above the selected one.  Every block exits at once
 // unless it is needed.
+template <bool PACKED>
 __global__ void __launch_bounds__(1024) k_select_next(SelectArgs a)
 {
     __shared__ unsigned int s_last;
@@ -287,7 +289,7 @@ __global__ void __launch_bounds__(1024) k_select_next(SelectArgs a)
     NextStep ns;
     ns.K = a.st->prefix;
     ns.m = 0xffffffffu;
-    scan_box(a.g, ns, a.claim);
+    scan_box<PACKED>(a.g, ns, a.claim);
     unsigned int m = ns.m;
     for (int off = 32; off > 0; off >>= 1) {
         const unsigned int o = __shfl_xor(m, off);
@@ -369,13 +371,17 @@ int select_rank(const Box &b, uint64_t rank, int rank_mode, float *value, uint64
     SelectArgs a;
     memset(&a, 0, sizeof a);
     const int threads = 1024;
-    const void *ksel = reinterpret_cast<const void *>(&k_select);
+    // Which kernels: packed rows when the box's rows need no cutting and are
+    // short (scan_geom below decides for good).
+    const void *ksel = scan_packs(b, threads) ? reinterpret_cast<const void *>(&k_select<true>)
+                                              : reinterpret_cast<const void *>(&k_select<false>);
     // One grid for every pass (pass 2 reads the candidates of its own block
     // index), sized by the largest pass's LDS: 4096 bins in 8 copies.
     int blocks = 0, chunks = 0;
     if ((rc = scan_plan(b, ksel, threads, (size_t)(4096 + 2) * 8 * 4, &blocks, &chunks)))
         return rc;
-    scan_geom(b, chunks > blocks ? chunks : blocks, &a.g);
+    scan_geom(b, chunks > blocks ? chunks : blocks, threads, &a.g);
+    const bool packed = a.g.pack.cb > 0;
     a.st = w->st;
     a.acc = w->acc;
     a.ticket = w->ticket;
@@ -399,7 +405,8 @@ int select_rank(const Box &b, uint64_t rank, int rank_mode, float *value, uint64
         const int nb = 1 << sel_width(p);
         a.copies_log2 = nb >= 4096 ? 3 : 5;
         const size_t lds = ((size_t)(nb + 2) << a.copies_log2) * 4;
-        const void *k = reinterpret_cast<const void *>(&k_select);
+        const void *k = packed ? reinterpret_cast<const void *>(&k_select<true>)
+                               : reinterpret_cast<const void *>(&k_select<false>);
         if (lds > 64 * 1024 &&
             (e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) !=
                 hipSuccess)
@@ -413,8 +420,9 @@ int select_rank(const Box &b, uint64_t rank, int rank_mode, float *value, uint64
     if (rank_mode == 1) {
         SelectArgs ac = a;
         void *args[] = {&ac};
-        if ((e = hipLaunchKernel(reinterpret_cast<const void *>(&k_select_next),
-                                 dim3((unsigned)blocks), dim3(threads), args, 0, nullptr)) !=
+        const void *k = packed ? reinterpret_cast<const void *>(&k_select_next<true>)
+                               : reinterpret_cast<const void *>(&k_select_next<false>);
+        if ((e = hipLaunchKernel(k, dim3((unsigned)blocks), dim3(threads), args, 0, nullptr)) !=
             hipSuccess)
             return hip_fail(e, "select launch");
     }
