@@ -263,7 +263,7 @@ CUBE_API int cube_set_partition(int32_t chunk_log2);
  * CUBE_Q_STATS, CUBE_Q_HIST or CUBE_Q_FUSED (nbins bins) over the given
  * DEVICE box would use, as one JSON object written to `out` (at most `cap`
  * bytes, NUL-terminated): threads per block, blocks, float4 loads per tile,
- * LDS histogram copies, histogram form ("none", "lds", "hot", "global"),
+ * LDS histogram copies, histogram form ("none", "lds", "hot", "global", "fine"),
  * partition ("static" or "dynamic"), chunk count (0 when static) and work
  * units.  Launches nothing.  Errors: CUBE_EINVAL for the box errors of the
  * other calls, an unknown kind, nbins outside [1, CUBE_MAX_BINS], a NULL

@@ -103,6 +103,7 @@ struct Workspace {
     HistRange *d_range = nullptr;
     cube_stats_t *h_out = nullptr;        // pinned
     unsigned long long *h_counts = nullptr;
+    unsigned int *dump = nullptr;         // blocks' rows of counts (many bins), DUMP_BYTES
     hipEvent_t used = nullptr;            // recorded after the last work queued with it
     std::mutex mu;                        // held by synchronous calls
 };
@@ -128,6 +129,7 @@ void free_ws(Workspace *w)
     hipFree(w->d_out);
     hipFree(w->d_counts);
     hipFree(w->d_range);
+    hipFree(w->dump);
     hipHostFree(w->h_out);
     hipHostFree(w->h_counts);
     hipSetDevice(prev);
@@ -173,6 +175,28 @@ int get_ws(hipStream_t s, Workspace **out)
     g_ws[key] = w;
     *out = w;
     return CUBE_OK;
+}
+
+// The blocks' rows of counts: one buffer of a fixed size per workspace, made
+// at the first pass that wants it and kept with the workspace.  False when
+// there is none and none can be made (a capturing stream, no memory): the
+// pass then adds its counts with atomics.
+constexpr int DEFER_MIN_BINS = 8192;
+constexpr size_t DUMP_BYTES = (size_t)256 * FINE_WORDS * 4;
+
+bool have_dump(Workspace *w, hipStream_t s)
+{
+    std::lock_guard<std::mutex> lk(g_mu);
+    if (w->dump) return true;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (s && (hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone)) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (hipMalloc(&w->dump, DUMP_BYTES) == hipSuccess) return true;
+    (void)hipGetLastError();
+    w->dump = nullptr;
+    return false;
 }
 
 // Record that work using `w` was queued on `s` (after a successful enqueue).
@@ -383,6 +407,11 @@ void collapse(const Box &b, Geom *g)
     g->pack.cb = 0;
 }
 
+// From how many voxels on a histogram of more than 32768 bins takes 16-bit
+// counters in LDS (HIST_FINE): below, clearing and writing out 128 KiB per
+// block costs more than an atomic per voxel.
+constexpr uint64_t FINE_MIN_VOXELS = (uint64_t)1 << 20;
+
 // The partition of a fully automatic launch (no explicit shape, no tuned
 // entry): dynamic for large boxes, where blocks on the slower XCDs would
 // otherwise set the end of the pass.  Measured with the default shapes on
@@ -395,7 +424,7 @@ static int default_chunk_log2(bool hist, uint64_t n)
     return n >= ((uint64_t)1 << 30) ? 19 : 0;
 }
 
-int make_plan(const Box &b, bool stats, int hist_kind_req, int nbins, Plan *p)
+int make_plan(const Box &b, bool stats, int hist_kind_req, int nbins, Plan *p, bool dump)
 {
     collapse(b, &p->g);
     int threads = g_threads, unroll = g_unroll, copies_req = g_copies;
@@ -428,7 +457,13 @@ int make_plan(const Box &b, bool stats, int hist_kind_req, int nbins, Plan *p)
     p->copies_log2 = 0;
     if (hist_kind_req) {
         if (nbins > 32768) {
-            p->hist = HIST_GLOBAL;
+            p->hist = dump && g_blocks == 0 && b.n >= FINE_MIN_VOXELS ? HIST_FINE : HIST_GLOBAL;
+            // One block fills a CU's LDS, so it takes all the CU's wavefronts;
+            // four vectors per lane and tile spill beside the counters' words.
+            if (p->hist == HIST_FINE && automatic) {
+                p->threads = threads = 1024;
+                p->unroll = 2;
+            }
         } else {
             p->hist = HIST_LDS;
             int c = copies_req;
@@ -473,6 +508,7 @@ int make_plan(const Box &b, bool stats, int hist_kind_req, int nbins, Plan *p)
         }
         if (blocks > chunks) blocks = chunks;
         if (blocks > MAX_BLOCKS) blocks = MAX_BLOCKS;
+        if (p->hist == HIST_FINE && blocks > 256) blocks = 256;  // rows of the dump
         if (blocks < 1) blocks = 1;
         p->chunks = (int)chunks;
         p->blocks = (int)blocks;
@@ -508,6 +544,7 @@ int make_plan(const Box &b, bool stats, int hist_kind_req, int nbins, Plan *p)
         }
         if (blocks > cap) blocks = cap;
     }
+    if (p->hist == HIST_FINE && blocks > 256) blocks = 256;  // rows of the dump
     // Per-block LDS counters are 32-bit: keep every block under 2^31 voxels.
     const long long min_blocks = (long long)(b.n >> 31) + 1;
     if (blocks < min_blocks) blocks = min_blocks;
@@ -564,11 +601,31 @@ __global__ void k_write_empty(cube_stats_t *out, unsigned long long *counts, int
         for (int i = threadIdx.x; i < nbins + 3; i += blockDim.x) counts[i] = 0ull;
 }
 
-int launch(const PassArgs &a, const Plan &p, bool stats, hipStream_t s)
+// A histogram pass of many bins leaves them to a second kernel, which spreads
+// over the chip what the pass's last block would do alone (copying and
+// clearing 65536 accumulators takes one 256-thread block 80 us).  Its blocks
+// write their counts out as rows instead of adding them with one 64-bit atomic
+// per block and non-empty bin where that is less: measured (microseconds,
+// atomics / rows) 8192 bins: 2^20 voxels 36.8 / 30.2, 2^24 56.8 / 51.7, 2^26
+// 77.8 / 85.1; 16384 bins: 49.0 / 34.4, 75.7 / 56.7, 94.4 / 89.7; 2048 bins:
+// 23.2 / 24.2, 41.8 / 43.2, 72.4 / 80.7.
+bool wants_dump(int nbins, uint64_t n)
 {
+    return nbins >= 16384 || (nbins >= DEFER_MIN_BINS && n <= ((uint64_t)1 << 24));
+}
+
+int launch(PassArgs a, const Plan &p, bool stats, Workspace *w, hipStream_t s)
+{
+    if (p.hist == HIST_FINE ||
+        (p.hist == HIST_LDS && wants_dump(a.nbins, a.g.n_total) && w->dump &&
+         (size_t)p.blocks * (size_t)a.nbins * 4 <= DUMP_BYTES))
+        a.dump = w->dump;
+    a.defer_bins = a.dump || (p.hist != HIST_NONE && a.nbins >= DEFER_MIN_BINS) ? 1 : 0;
     hipError_t e =
         launch_pass(a, stats, p.hist, p.threads, p.blocks, p.lds, p.unroll, s);
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
+    if (a.defer_bins && (e = launch_hist_sum(a, p.hist, p.blocks, s)) != hipSuccess)
+        return hip_fail(e, "histogram sum launch");
     return CUBE_OK;
 }
 
@@ -615,30 +672,31 @@ int run_async(Op op, const float *ptr, const int64_t *dims, float lo, float hi, 
         return e == hipSuccess ? CUBE_OK : hip_fail(e, "empty-box launch");
     }
     Plan p;
+    const bool dump = op != OP_STATS && wants_dump(nbins, b.n) && have_dump(w, s);
     if (op == OP_STATS || op == OP_MINMAX) {
-        if ((rc = make_plan(b, true, 0, nbins, &p))) return rc;
+        if ((rc = make_plan(b, true, 0, nbins, &p, false))) return rc;
         PassArgs a = base_args(w, p, nbins);
         a.out = dev_out;
         if (op == OP_MINMAX) {
             a.want_range = 1;
             a.out_range = w->d_range;
         }
-        if ((rc = launch(a, p, true, s))) return rc;
+        if ((rc = launch(a, p, true, w, s))) return rc;
         if (op == OP_STATS) return CUBE_OK;
         Plan p2;
-        if ((rc = make_plan(b, false, 1, nbins, &p2))) return rc;
+        if ((rc = make_plan(b, false, 1, nbins, &p2, dump))) return rc;
         PassArgs a2 = base_args(w, p2, nbins);
         a2.dev_range = w->d_range;
         a2.counts = dev_counts;
-        return launch(a2, p2, false, s);
+        return launch(a2, p2, false, w, s);
     }
     const bool stats = op == OP_FUSED;
-    if ((rc = make_plan(b, stats, 1, nbins, &p))) return rc;
+    if ((rc = make_plan(b, stats, 1, nbins, &p, dump))) return rc;
     PassArgs a = base_args(w, p, nbins);
     a.range = range;
     a.out = dev_out;
     a.counts = dev_counts;
-    return launch(a, p, stats, s);
+    return launch(a, p, stats, w, s);
 }
 
 int run_pass(const Box &b, bool stats, bool hist, int nbins, const HistRange &range,
@@ -650,14 +708,15 @@ int run_pass(const Box &b, bool stats, bool hist, int nbins, const HistRange &ra
     int rc = get_ws(s, &w);
     if (rc) return rc;
     Plan p;
-    if ((rc = make_plan(b, stats, hist ? 1 : 0, nbins, &p))) return rc;
+    const bool dump = hist && wants_dump(nbins, b.n) && have_dump(w, s);
+    if ((rc = make_plan(b, stats, hist ? 1 : 0, nbins, &p, dump))) return rc;
     PassArgs a = base_args(w, p, nbins);
     a.range = range;
     a.dev_range = dev_range;
     a.out = stats ? dev_out : nullptr;
     a.counts = hist ? dev_counts : nullptr;
     a.accumulate = accumulate ? 1 : 0;
-    if ((rc = launch(a, p, stats, s))) return rc;
+    if ((rc = launch(a, p, stats, w, s))) return rc;
     return mark_ws(w, s);
 }
 
@@ -846,9 +905,10 @@ int cube_describe_plan(const float *ptr, const int64_t *dims, int32_t kind, int3
     if ((rc = check_box_device(&b))) return rc;
     if (b.n == 0) return fail(CUBE_EINVAL, "an empty box launches nothing");
     Plan p;
-    if ((rc = make_plan(b, kind != CUBE_Q_HIST, kind == CUBE_Q_STATS ? 0 : 1, nbins, &p)))
+    if ((rc = make_plan(b, kind != CUBE_Q_HIST, kind == CUBE_Q_STATS ? 0 : 1, nbins, &p,
+                        true)))
         return rc;
-    static const char *forms[] = {"none", "lds", "global", "hot"};
+    static const char *forms[] = {"none", "lds", "global", "hot", "fine"};
     const int n = snprintf(out, cap,
                            "{\"threads\": %d, \"blocks\": %d, \"unroll\": %d, \"copies\": %d, "
                            "\"hist\": \"%s\", \"partition\": \"%s\", \"chunks\": %d, "

@@ -152,6 +152,40 @@ __device__ __forceinline__ int keep_or_minus1(int v, unsigned long long m)
     return r;
 }
 
+// HIST_FINE: every bin is a 16-bit counter, two to a word: at 32768 words a
+// block's histogram of up to 65536 bins fits LDS, where 32-bit counters would
+// not and every voxel would be one 64-bit global atomic (23 G/s on an MI355X).
+// A counter that has reached 0x8000 is seen by whoever adds to it next (the
+// add returns the old word), and the wavefront that saw it moves 0x8000 from
+// the counter to the global accumulators before its next step.  No counter
+// can pass 0xffff meanwhile: a wavefront adds at most 64 * 16 to one counter
+// in the step in which it sees the mark, so at most 16 * 1024 = 0x4000 adds
+// fall between the mark and its removal.  Lanes without an in-range voxel add
+// 0 to a word of their own after the counters (one per lane: no conflicts).
+// Measured on 2^28 noise voxels, 65536 bins: 11.0 -> 0.215 ms (2^26: 2.79 ->
+// 0.097), against 0.181 ms for 1024 bins: HBM, then the rows' write and sum.
+__device__ __forceinline__ unsigned int fine_word(float u, int nbins, unsigned int *half)
+{
+    const int b = min(cvt_flr_i32(u), nbins - 1);
+    *half = (unsigned int)b >> 15;
+    return (unsigned int)b & (unsigned int)(FINE_WORDS - 1);
+}
+
+template <int NV>
+__device__ __forceinline__ void fine_move(const float (&x)[NV], const Hist &H)
+{
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+        if (!(x[j] >= H.lo && x[j] <= H.hi)) continue;
+        unsigned int half;
+        const unsigned int w =
+            fine_word(__fmul_rn(__fsub_rn(x[j], H.lo), H.scale), H.nbins, &half);
+        const unsigned int was = atomicAnd(&H.lds[w], 0x7fff7fffu);
+        if (was & 0x8000u) atomicAdd(&H.global[w], 0x8000ull);
+        if (was & 0x80000000u) atomicAdd(&H.global[w + FINE_WORDS], 0x8000ull);
+    }
+}
+
 // One step over NV voxels per lane.  With a histogram, two compares decide
 // everything: A = (x >= lo), B = (x <= hi) are both false for a NaN and,
 // since lo <= hi, not both false otherwise, so valid = A|B, in-range = A&B,
@@ -175,6 +209,7 @@ __device__ __forceinline__ void process(const float (&x)[NV], Lane &L, Wave &W,
     }
     // Ballot counts of this step in 32-bit scalars (at most 64 * NV each).
     unsigned int cvalid = 0, cge = 0, cle = 0;
+    unsigned int fine_seen = 0;  // HIST_FINE: the words added to, as they were
     float t1 = L.p1, t2 = L.p2;
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
@@ -216,12 +251,20 @@ __device__ __forceinline__ void process(const float (&x)[NV], Lane &L, Wave &W,
                 const int b = cvt_flr_i32(u);
                 const unsigned long long off_hot = __builtin_amdgcn_ballot_w64(b != H.hot);
                 lds_add1_masked((unsigned int)((b << H.shift) + H.base_abs), inr & off_hot);
+            } else if (HIST == HIST_FINE) {
+                unsigned int half;
+                int w = (int)fine_word(u, H.nbins, &half);
+                const bool in = ge && le;
+                w = in ? w : H.base;
+                fine_seen |= atomicAdd(&H.lds[w], in ? 1u << (half << 4) : 0u);
             } else {
                 const int b = min(cvt_flr_i32(u), H.nbins - 1);
                 if ((inr >> (threadIdx.x & 63)) & 1ull) atomicAdd(&H.global[b], 1ull);
             }
         }
     }
+    if (HIST == HIST_FINE && __builtin_amdgcn_ballot_w64((fine_seen & 0x80008000u) != 0u))
+        fine_move<NV>(x, H);
     // Keep the step counts 32-bit (the compiler would otherwise widen every
     // per-voxel add to 64 bits).
     asm("" : "+s"(cvalid), "+s"(cge), "+s"(cle));
@@ -526,6 +569,30 @@ __device__ __forceinline__ void hist_setup(Hist &H, const HistRange &r, int nbin
     H.lo = r.lo;
     H.hi = r.hi;
     H.scale = r.scale;
+}
+
+// HIST_FINE: one layout, one copy, a word per lane after the counters.
+__device__ __forceinline__ void fine_setup(Hist &H)
+{
+    H.base = FINE_WORDS + (int)(threadIdx.x & 63);
+}
+
+__device__ __forceinline__ void fine_zero(unsigned int *lds)
+{
+    uint4 *l4 = reinterpret_cast<uint4 *>(lds);
+    for (int i = threadIdx.x; i < (FINE_WORDS + 64) / 4; i += blockDim.x)
+        l4[i] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+}
+
+// The block's counters as they are, to its row of the dump.  Starts with a
+// barrier.
+__device__ __forceinline__ void fine_dump(const unsigned int *lds, unsigned int *row)
+{
+    __syncthreads();
+    const uint4 *l4 = reinterpret_cast<const uint4 *>(lds);
+    uint4 *r4 = reinterpret_cast<uint4 *>(row);
+    for (int i = threadIdx.x; i < FINE_WORDS / 4; i += blockDim.x) r4[i] = l4[i];
 }
 
 // Zero the LDS sub-histograms (nbins + 2 slots per copy); ends with a barrier.
@@ -859,9 +926,10 @@ __device__ __forceinline__ void write_chunk_record(const WaveRec *parts, int nw,
 }
 
 // Add the block's LDS sub-histograms into the global accumulators (one
-// atomic per non-empty bin).  Starts with a barrier.
+// atomic per non-empty bin), or write them to its row of the dump when there
+// is one.  Starts with a barrier.
 __device__ __forceinline__ void hist_flush(const unsigned int *lds, int nbins, int copies_log2,
-                                           unsigned long long *acc)
+                                           unsigned long long *acc, unsigned int *row = nullptr)
 {
     __syncthreads();
     const int C = 1 << copies_log2;
@@ -873,7 +941,10 @@ __device__ __forceinline__ void hist_flush(const unsigned int *lds, int nbins, i
         for (int c = 0; c < C; ++c) sum += lds[((b + 1) << copies_log2) + ((c + rot) & (C - 1))];
         if (b == nbins - 1)  // floor(u) == nbins belongs to the last bin
             for (int c = 0; c < C; ++c) sum += lds[((nbins + 1) << copies_log2) + c];
-        if (sum) atomicAdd(&acc[b], (unsigned long long)sum);
+        if (row)
+            row[b] = sum;
+        else if (sum)
+            atomicAdd(&acc[b], (unsigned long long)sum);
     }
 }
 
@@ -1032,13 +1103,13 @@ __device__ void finish_stats(const R *recs, int n_recs, int accum_mode,
 
 // Copy the global accumulators to the caller's counts (or, with `add`, add
 // them to the counts already there) and return them to zero; thread 0 writes
-// below / above / NaN.
+// below / above / NaN.  `deferred`: the bins are left to launch_hist_sum.
 __device__ __forceinline__ void finish_hist(unsigned long long *acc, unsigned long long *counts,
                                             int nbins, bool on, unsigned long long below,
                                             unsigned long long above, unsigned long long n_nan,
-                                            bool add = false)
+                                            bool add = false, bool deferred = false)
 {
-    for (int b = threadIdx.x; b < nbins; b += blockDim.x) {
+    for (int b = threadIdx.x; b < nbins && !deferred; b += blockDim.x) {
         counts[b] = (add ? counts[b] : 0ull) + acc[b];
         acc[b] = 0ull;
     }

@@ -65,7 +65,10 @@ struct Geom {
 // first in-range voxel it meets) is never written to LDS -- its count is the
 // block's in-range count, known from the ballots, minus every other bin --
 // so a skewed histogram costs almost no LDS atomics.
-enum : int32_t { HIST_NONE = 0, HIST_LDS = 1, HIST_GLOBAL = 2, HIST_HOT = 3 };
+// HIST_FINE: more bins than LDS holds as 32-bit words, as 16-bit counters in
+// pairs (word w holds bins w and w + FINE_WORDS).
+enum : int32_t { HIST_NONE = 0, HIST_LDS = 1, HIST_GLOBAL = 2, HIST_HOT = 3, HIST_FINE = 4 };
+constexpr int FINE_WORDS = 32768;
 
 struct PassArgs {
     Geom g;
@@ -85,7 +88,11 @@ struct PassArgs {
     int32_t want_range;          // pass 1 of a two-pass call: write out_range
     int32_t accumulate;          // add the counts to `counts` instead of writing them
     int32_t n_chunks;            // 0: static partition; else chunks claimed at run time
+    unsigned int *dump;          // a row of counts per block; null: atomics on hist_acc
+    int32_t defer_bins;          // the bins are left to launch_hist_sum after the pass
 };
+// Words in a block's row of PassArgs::dump.
+inline int dump_words(int hist, int nbins) { return hist == HIST_FINE ? FINE_WORDS : nbins; }
 
 // Kernel launchers (cube_kernels.hip).  `stats`: compute the statistics;
 // `hist`: HIST_NONE / HIST_LDS / HIST_GLOBAL / HIST_HOT.  Returns the launch
@@ -94,15 +101,21 @@ struct PassArgs {
 hipError_t launch_pass(const PassArgs &a, bool stats, int hist, int threads,
                        int blocks, size_t lds_bytes, int unroll, hipStream_t s);
 
+// The bins of a pass with defer_bins: the global accumulators plus the rows its
+// `blocks` blocks left in a.dump, to a.counts (the pass itself writes the
+// below / above / NaN counters).
+hipError_t launch_hist_sum(const PassArgs &a, int hist, int blocks, hipStream_t s);
+
 // Dynamic LDS bytes a pass needs (`dynamic`: of the dynamic-partition
 // kernel, which keeps a ring of wavefront records after its histogram).
 size_t pass_lds_bytes(bool stats, int hist, int nbins, int copies_log2, int threads,
                       bool dynamic = false);
 // Where that ring starts in the dynamic LDS, in 32-bit words (16-byte
 // aligned, after the LDS histogram if there is one).
-__host__ __device__ inline int dyn_ring_offset_words(bool lds_hist, int nbins, int copies_log2)
+__host__ __device__ inline int dyn_ring_offset_words(int hist, int nbins, int copies_log2)
 {
-    return lds_hist ? (((nbins + 2) << copies_log2) + 3) & ~3 : 0;
+    if (hist == HIST_FINE) return FINE_WORDS + 64;
+    return hist == HIST_LDS ? (((nbins + 2) << copies_log2) + 3) & ~3 : 0;
 }
 
 // Occupancy of one pass configuration: resident blocks per CU.
@@ -172,7 +185,9 @@ void get_launch(int *threads, int *blocks, int *copies, int *unroll);
 // The launch shape of one pass over a validated box: statistics (`stats`)
 // and/or a histogram (hist_kind_req 1) of nbins bins; the explicit shape of
 // cube_set_launch, else the tuned one, else the default rules.
-int make_plan(const Box &b, bool stats, int hist_kind_req, int nbins, Plan *p);
+// `dump`: the caller has a buffer for the blocks' rows of counts (without it
+// more than 32768 bins take global atomics).
+int make_plan(const Box &b, bool stats, int hist_kind_req, int nbins, Plan *p, bool dump);
 // Cut the rows of a collapsed box into segments so that there are at least
 // `blocks` work units (a row is never cut below 4 floats).
 void cut_rows(Geom &g, long long blocks);

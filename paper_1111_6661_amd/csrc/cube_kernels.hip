@@ -45,6 +45,10 @@ __global__ void __launch_bounds__(1024) k_pass(PassArgs a)
     }
     if (HIST == HIST_LDS || HIST == HIST_HOT) lds_zero(lds, a.nbins, a.copies_log2);
     if (HIST == HIST_HOT) H.hot = s_hot;
+    if (HIST == HIST_FINE) {
+        fine_setup(H);
+        fine_zero(lds);
+    }
 
     Lane L = {INFINITY, -INFINITY, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     Wave W = {0.f, ACC == CUBE_ACCUM_NAIVE32 ? 1 : 0, 0ull, 0ull, 0ull};
@@ -55,7 +59,10 @@ __global__ void __launch_bounds__(1024) k_pass(PassArgs a)
         scan<STATS, HIST_NONE, ACC, U, PACKED>(g, u0, u1, L, W, H);
 
     write_wave_record<STATS, ACC>(L, W, &a.recs[(long long)blockIdx.x * nw + wid]);
-    if (HIST == HIST_LDS) hist_flush(lds, a.nbins, a.copies_log2, a.hist_acc);
+    unsigned int *row =
+        a.dump ? a.dump + (size_t)blockIdx.x * (HIST == HIST_FINE ? FINE_WORDS : a.nbins) : nullptr;
+    if (HIST == HIST_LDS) hist_flush(lds, a.nbins, a.copies_log2, a.hist_acc, row);
+    if (HIST == HIST_FINE) fine_dump(lds, row);
     if (HIST == HIST_HOT) {
         if (hist_on) add_in_range(W, &s_inr);
         hist_flush_hot(lds, a.nbins, a.copies_log2, a.hist_acc, H.hot, &s_inr, &s_tot);
@@ -80,7 +87,7 @@ __global__ void __launch_bounds__(1024) k_pass(PassArgs a)
     }
     if (HIST != HIST_NONE)
         finish_hist(a.hist_acc, a.counts, a.nbins, hist_on, below, above, g.n_total - nv,
-                    a.accumulate != 0);
+                    a.accumulate != 0, a.defer_bins != 0);
     if (tid == 0) *a.ticket = 0u;
 }
 
@@ -108,7 +115,7 @@ __global__ void __launch_bounds__(1024) k_pass_dyn(PassArgs a)
     // The ring of wavefront records (dynamic LDS after the histogram): nw
     // chunks of nw records each.
     WaveRec *ring = reinterpret_cast<WaveRec *>(
-        lds + dyn_ring_offset_words(HIST == HIST_LDS, a.nbins, a.copies_log2));
+        lds + dyn_ring_offset_words(HIST, a.nbins, a.copies_log2));
 
     Hist H;
     const HistRange r0 = {0.f, 0.f, 0.f, 0};
@@ -123,8 +130,14 @@ __global__ void __launch_bounds__(1024) k_pass_dyn(PassArgs a)
     const long long chunk_max =
         (long long)((g.n_units + (unsigned long long)nc - 1) / (unsigned long long)nc) * g.seg_len;
     if (tid == 0) s_chunk = (int)atomicAdd(ctr, 1u);
-    if (HIST == HIST_LDS) lds_zero(lds, a.nbins, a.copies_log2);  // ends with a barrier
-    else __syncthreads();
+    if (HIST == HIST_FINE) {
+        fine_setup(H);
+        fine_zero(lds);  // ends with a barrier
+    } else if (HIST == HIST_LDS) {
+        lds_zero(lds, a.nbins, a.copies_log2);  // ends with a barrier
+    } else {
+        __syncthreads();
+    }
 
     long long since_flush = 0;  // voxels counted in LDS since it was last zeroed
     int filled = 0;             // chunks in the ring (uniform)
@@ -173,7 +186,10 @@ __global__ void __launch_bounds__(1024) k_pass_dyn(PassArgs a)
     if (wid < filled)
         write_chunk_record<STATS>(&ring[wid * nw], nw,
                                   reinterpret_cast<ChunkRec *>(a.recs) + s_ids[wid]);
-    if (HIST == HIST_LDS) hist_flush(lds, a.nbins, a.copies_log2, a.hist_acc);
+    unsigned int *row =
+        a.dump ? a.dump + (size_t)blockIdx.x * (HIST == HIST_FINE ? FINE_WORDS : a.nbins) : nullptr;
+    if (HIST == HIST_LDS) hist_flush(lds, a.nbins, a.copies_log2, a.hist_acc, row);
+    if (HIST == HIST_FINE) fine_dump(lds, row);
 
     if (!last_to_arrive(a.ticket, gridDim.x, &s_last)) return;
 
@@ -191,11 +207,72 @@ __global__ void __launch_bounds__(1024) k_pass_dyn(PassArgs a)
     }
     if (HIST != HIST_NONE)
         finish_hist(a.hist_acc, a.counts, a.nbins, hist_on, below, above, g.n_total - nv,
-                    a.accumulate != 0);
+                    a.accumulate != 0, a.defer_bins != 0);
     if (tid == 0) {
         *a.ticket = 0u;
         *ctr = 0u;
     }
+}
+
+// The bins of a pass that left them to this kernel: the global accumulators
+// plus the blocks' rows of counts (rows == 0: the accumulators alone, spread
+// over the chip instead of copied by the pass's last block).  A block takes 64 words; its four
+// wavefronts take every fourth row each (16 loads in flight per lane, 256
+// contiguous bytes per wavefront), then add up through LDS.  Bound by the
+// latency of its row reads: the rows are at most 32 MiB, just written.
+template <bool FINE>
+__global__ void __launch_bounds__(256) k_hist_sum(const unsigned int *dump, int rows, int words,
+                                                  int nbins, unsigned long long *acc,
+                                                  unsigned long long *counts, int add)
+{
+    __shared__ unsigned long long part[2][4][64];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int w = (int)blockIdx.x * 64 + lane;
+    unsigned long long lo = 0ull, hi = 0ull;
+    if (w < words) {
+        const unsigned int *p = dump + w;
+        auto take = [&](unsigned int v) {
+            lo += FINE ? v & 0xffffu : v;
+            if (FINE) hi += v >> 16;
+        };
+        int r = wid;
+        for (; r + 60 < rows; r += 64) {
+            unsigned int v[16];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) v[k] = p[(size_t)(r + 4 * k) * words];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) take(v[k]);
+        }
+        for (; r < rows; r += 4) take(p[(size_t)r * words]);
+    }
+    part[0][wid][lane] = lo;
+    part[1][wid][lane] = hi;
+    __syncthreads();
+    if (wid >= (FINE ? 2 : 1)) return;
+    const int b = w + wid * FINE_WORDS;
+    if (w >= words || b >= nbins) return;
+    unsigned long long sum = acc[b];  // what the pass moved out before its end
+    for (int k = 0; k < 4; ++k) sum += part[wid][k][lane];
+    acc[b] = 0ull;
+    counts[b] = (add ? counts[b] : 0ull) + sum;
+}
+
+hipError_t launch_hist_sum(const PassArgs &a, int hist, int blocks, hipStream_t s)
+{
+    const int words = dump_words(hist, a.nbins);
+    if (!a.dump) {
+        hipLaunchKernelGGL(k_hist_sum<false>, dim3((unsigned)((a.nbins + 63) / 64)), dim3(256), 0,
+                           s, nullptr, 0, a.nbins, a.nbins, a.hist_acc, a.counts, a.accumulate);
+        return hipGetLastError();
+    }
+    const dim3 grid((unsigned)((words + 63) / 64));
+    if (hist == HIST_FINE)
+        hipLaunchKernelGGL(k_hist_sum<true>, grid, dim3(256), 0, s, a.dump, blocks, words, a.nbins,
+                           a.hist_acc, a.counts, a.accumulate);
+    else
+        hipLaunchKernelGGL(k_hist_sum<false>, grid, dim3(256), 0, s, a.dump, blocks, words,
+                           a.nbins, a.hist_acc, a.counts, a.accumulate);
+    return hipGetLastError();
 }
 
 size_t pass_lds_bytes(bool stats, int hist, int nbins, int copies_log2, int threads,
@@ -204,11 +281,12 @@ size_t pass_lds_bytes(bool stats, int hist, int nbins, int copies_log2, int thre
     (void)stats;
     if (dynamic) {
         const size_t nw = (size_t)threads / 64;
-        return (size_t)dyn_ring_offset_words(hist == HIST_LDS, nbins, copies_log2) * 4u +
+        return (size_t)dyn_ring_offset_words(hist, nbins, copies_log2) * 4u +
                nw * nw * sizeof(WaveRec);
     }
     if (hist == HIST_LDS || hist == HIST_HOT)
         return (size_t)(nbins + 2) * ((size_t)1 << copies_log2) * 4u;
+    if (hist == HIST_FINE) return (size_t)(FINE_WORDS + 64) * 4u;
     return 0;
 }
 
@@ -246,9 +324,11 @@ static const void *pick_dyn(bool stats, int hist, int u, bool pk)
     if (stats) {
         if (hist == HIST_NONE) return dyn_kernel_of<true, HIST_NONE>(u, pk);
         if (hist == HIST_LDS) return dyn_kernel_of<true, HIST_LDS>(u, pk);
+        if (hist == HIST_FINE) return dyn_kernel_of<true, HIST_FINE>(u, pk);
         return dyn_kernel_of<true, HIST_GLOBAL>(u, pk);
     }
     if (hist == HIST_LDS) return dyn_kernel_of<false, HIST_LDS>(u, pk);
+    if (hist == HIST_FINE) return dyn_kernel_of<false, HIST_FINE>(u, pk);
     return dyn_kernel_of<false, HIST_GLOBAL>(u, pk);
 }
 
@@ -265,11 +345,15 @@ static const void *pick(bool stats, int hist, int acc, int u, bool pk)
         if (hist == HIST_HOT)
             return naive ? kernel_of<true, HIST_HOT, CUBE_ACCUM_NAIVE32>(u, pk)
                          : kernel_of<true, HIST_HOT, CUBE_ACCUM_FP64MERGE>(u, pk);
+        if (hist == HIST_FINE)
+            return naive ? kernel_of<true, HIST_FINE, CUBE_ACCUM_NAIVE32>(u, pk)
+                         : kernel_of<true, HIST_FINE, CUBE_ACCUM_FP64MERGE>(u, pk);
         return naive ? kernel_of<true, HIST_GLOBAL, CUBE_ACCUM_NAIVE32>(u, pk)
                      : kernel_of<true, HIST_GLOBAL, CUBE_ACCUM_FP64MERGE>(u, pk);
     }
     if (hist == HIST_LDS) return kernel_of<false, HIST_LDS, CUBE_ACCUM_FP64MERGE>(u, pk);
     if (hist == HIST_HOT) return kernel_of<false, HIST_HOT, CUBE_ACCUM_FP64MERGE>(u, pk);
+    if (hist == HIST_FINE) return kernel_of<false, HIST_FINE, CUBE_ACCUM_FP64MERGE>(u, pk);
     return kernel_of<false, HIST_GLOBAL, CUBE_ACCUM_FP64MERGE>(u, pk);
 }
 

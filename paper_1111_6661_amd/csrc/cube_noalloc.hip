@@ -92,7 +92,7 @@ extern "C" int cube_stats_hist_noalloc(const float *ptr, const int64_t *dims, fl
     if (b.n == 0) return write_empty(dev_out, (unsigned long long *)dev_counts, nbins, s);
 
     Plan p;
-    if ((rc = make_plan(b, true, 1, nbins, &p))) return rc;
+    if ((rc = make_plan(b, true, 1, nbins, &p, false))) return rc;
     const long long waves = p.threads / 64;
     if (p.chunks > 0) {
         // A dynamic partition keeps one record per chunk: at most NA_RECS

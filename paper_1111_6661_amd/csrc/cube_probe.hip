@@ -168,7 +168,7 @@ int cube_read_probe(const float *ptr, const int64_t *dims, int32_t nbins, uint32
     if (b.n == 0) return CUBE_OK;
     if ((rc = check_box_device(&b))) return rc;
     Plan p;
-    if ((rc = make_plan(b, true, 1, nbins, &p))) return rc;
+    if ((rc = make_plan(b, true, 1, nbins, &p, true))) return rc;
     hipStream_t s = (hipStream_t)stream;
     const bool dyn = p.chunks > 0;
     const void *k = dyn ? (p.unroll == 2 ? reinterpret_cast<const void *>(&k_probe_dyn<2>)
