@@ -87,7 +87,7 @@ void get_launch(int *threads, int *blocks, int *copies, int *unroll)
 constexpr int MAX_BLOCKS = 4096;
 constexpr int MAX_WAVES_PER_BLOCK = 16;
 constexpr size_t REC_CAP = (size_t)MAX_BLOCKS * MAX_WAVES_PER_BLOCK;
-constexpr size_t LDS_BUDGET = 132 * 1024;  // one 1024-thread histogram block per CU
+constexpr size_t LDS_MAX = 156 * 1024;     // of a block's 160 KiB, its static part aside
 
 // One workspace per (device, stream): partial records, the ticket, the
 // histogram accumulators (kept at zero between launches by the kernel) and
@@ -412,16 +412,44 @@ void collapse(const Box &b, Geom *g)
 // block costs more than an atomic per voxel.
 constexpr uint64_t FINE_MIN_VOXELS = (uint64_t)1 << 20;
 
-// The partition of a fully automatic launch (no explicit shape, no tuned
-// entry): dynamic for large boxes, where blocks on the slower XCDs would
-// otherwise set the end of the pass.  Measured with the default shapes on
-// dense boxes of 2^25 to 2^31 voxels: chunks of 2^18 voxels beat the static
-// partition from 2^27 voxels on for histogram passes (by 1-10 %, growing
-// with the box), and chunks of 2^19 from 2^30 on for the statistics pass.
-static int default_chunk_log2(bool hist, uint64_t n)
+// The shape and partition of a fully automatic launch (no explicit shape, no
+// tuned entry), from the voxel count and whether the rows are short (packed).
+// blocks: per CU, the most of a static partition and the resident ones of a
+// dynamic one.  Measured, microseconds, GPU time per pass:
+//
+// Threads.  Histogram passes, 256 bins: 512 under 2^24 voxels (2^20: 256 /
+// 512 / 1024 threads 15.6 / 13.8 / 15.2; 2^22: 20.5 / 17.8 / 19.7), then 1024
+// with two vectors per lane and tile (2^24: 26.4 against 26.6 for 512 and 28.9
+// for 256; 2^26: 53.9 against 57.7 with four vectors).  Statistics: 256 under
+// 2^22 (2^20: 11.5 / 11.9 / 13.5), then 512 (2^23: 17.5 / 16.5 / 17.7; 2^26:
+// 49.3 / 47.8 / 51.3).
+//
+// Partition.  Dynamic for large boxes, where blocks on the slower XCDs would
+// otherwise set the end of the pass: for histogram passes from 2^27 voxels on
+// with chunks of 2^18 (two vectors until 2^30: 2^28 181 against 193 with four;
+// 2^32: 2581 against 2434), for statistics from 2^30 on with chunks of 2^19
+// (one 512-thread block per CU, two vectors: 2^30 618 against 675 with four
+// vectors and two blocks).  Packed rows take it from 2^30 voxels only, and
+// more wavefronts per CU for statistics, since their loads wait longer: a 1187
+// x 911 x 263 box, statistics 285 with one 512-thread block per CU, 190 with
+// two; with 1024 bins 237 dynamic, 211 static with four vectors.
+struct Shape {
+    int threads, unroll, per_cu, chunk_log2;
+};
+
+static Shape default_shape(bool hist, uint64_t n, bool short_rows)
 {
-    if (hist) return n >= ((uint64_t)1 << 27) ? 18 : 0;
-    return n >= ((uint64_t)1 << 30) ? 19 : 0;
+    const auto below = [n](int k) { return n < (uint64_t)1 << k; };
+    if (hist) {
+        if (below(24)) return {512, 4, 1, 0};
+        if (short_rows) return below(30) ? Shape{1024, 4, 1, 0} : Shape{512, 4, 2, 18};
+        if (below(27)) return {1024, 2, 1, 0};
+        return {1024, below(30) ? 2 : 4, 1, 18};
+    }
+    if (below(22)) return {256, 4, 1, 0};
+    if (short_rows) return below(30) ? Shape{512, 4, 2, 0} : Shape{1024, 4, 1, 19};
+    if (below(30)) return {512, 4, 1, 0};
+    return {512, 2, 1, 19};
 }
 
 int make_plan(const Box &b, bool stats, int hist_kind_req, int nbins, Plan *p, bool dump)
@@ -432,9 +460,12 @@ int make_plan(const Box &b, bool stats, int hist_kind_req, int nbins, Plan *p, b
     // With no explicit shape, use the autotuner's choice for this class.
     TunedShape ts;
     const int kind = stats ? (hist_kind_req ? CUBE_Q_FUSED : CUBE_Q_STATS) : CUBE_Q_HIST;
-    int hot = 0, chunk_log2 = 0, resident = 0;
+    int hot = 0, chunk_log2 = 0;
     const bool automatic = threads == 0 && unroll == 0 && copies_req == 0 && blocks == 0;
-    if (automatic) chunk_log2 = default_chunk_log2(hist_kind_req != 0, b.n);
+    const bool short_rows = p->g.ny * p->g.nz > 1 && p->g.row_len <= 4 * 512 * 4;
+    const Shape def = default_shape(hist_kind_req != 0, b.n, short_rows);
+    int per_cu = 0;
+    if (automatic) chunk_log2 = def.chunk_log2;
     if (automatic && tuned_shape(kind, hist_kind_req ? nbins : 1, b.n, &ts)) {
         threads = ts.threads;
         unroll = ts.unroll;
@@ -442,17 +473,15 @@ int make_plan(const Box &b, bool stats, int hist_kind_req, int nbins, Plan *p, b
         blocks = (long long)cu_count() * ts.blocks_per_cu;
         hot = ts.hot;
         chunk_log2 = ts.chunk_log2;
-        resident = ts.blocks_per_cu;
+        per_cu = ts.blocks_per_cu;
+    } else if (automatic) {
+        per_cu = def.per_cu;
     }
     if (g_hot >= 0) hot = g_hot;
     if (g_chunk >= 0) chunk_log2 = g_chunk;
-    // Histogram passes over boxes under 2^25 voxels default to 256 threads:
-    // their launches are short enough that per-block costs dominate (below).
-    const bool small = b.n < ((uint64_t)1 << 25);
-    if (threads != 256 && threads != 512 && threads != 1024)
-        threads = (hist_kind_req && !small) ? 1024 : 256;
+    if (threads != 256 && threads != 512 && threads != 1024) threads = def.threads;
     p->threads = threads;
-    p->unroll = (unroll == 2 || unroll == 4) ? unroll : 4;
+    p->unroll = (unroll == 2 || unroll == 4) ? unroll : (automatic ? def.unroll : 4);
     p->hist = HIST_NONE;
     p->copies_log2 = 0;
     if (hist_kind_req) {
@@ -471,10 +500,19 @@ int make_plan(const Box &b, bool stats, int hist_kind_req, int nbins, Plan *p, b
             if (c > 0) {
                 while ((1 << (clog + 1)) <= c && clog < 5) ++clog;
             } else {
-                const size_t words = LDS_BUDGET / 4;
-                while (clog < 5 && (size_t)(nbins + 2) << (clog + 1) <= words) ++clog;
+                // Copies spread one bin over as many LDS banks, but every
+                // block clears and adds up all of them: 1024 bins of 2^20
+                // noise voxels take 18.3 us with 32 copies, 15.4 with 4 and
+                // 15.2 with 2; 2^26 voxels 56.2 with 32, 54.9 with 8, 55.5
+                // with 2.  Two at least, as skewed data want some (nearly all
+                // voxels in ten bins, 2^23: 8 copies 20.2, 2 copies 21.6).
+                const size_t words = b.n < ((uint64_t)1 << 22)   ? 4608
+                                     : b.n < ((uint64_t)1 << 26) ? 8704
+                                                                 : 17408;
+                while (clog < 3 && (size_t)(nbins + 2) << (clog + 1) <= words) ++clog;
+                if (clog == 0 && (size_t)(nbins + 2) * 2 <= 8704) clog = 1;
             }
-            while (clog > 0 && ((size_t)(nbins + 2) << clog) * 4 > 160 * 1024) --clog;
+            while (clog > 0 && ((size_t)(nbins + 2) << clog) * 4 > LDS_MAX) --clog;
             p->copies_log2 = clog;
             if (hot) p->hist = HIST_HOT;
         }
@@ -496,16 +534,19 @@ int make_plan(const Box &b, bool stats, int hist_kind_req, int nbins, Plan *p, b
         // (its static LDS is about 1 KB).
         while (true) {
             p->lds = pass_lds_bytes(stats, p->hist, nbins, p->copies_log2, threads, true);
-            if (p->lds + 4096 <= 160 * 1024 || p->hist != HIST_LDS || p->copies_log2 == 0) break;
+            if (p->lds <= LDS_MAX || p->hist != HIST_LDS || p->copies_log2 == 0) break;
             --p->copies_log2;
         }
         const int fit =
             pass_blocks_per_cu(stats, p->hist, threads, p->lds, p->unroll, true, packed);
-        const long long chunks = chunks_of(b.n, chunk_log2);
+        long long chunks = chunks_of(b.n, chunk_log2);
         if (g_blocks == 0) {
-            const int per_cu = resident > 0 && resident < fit ? resident : fit;
-            blocks = (long long)cu_count() * per_cu;
+            blocks = (long long)cu_count() * (per_cu > 0 && per_cu < fit ? per_cu : fit);
         }
+        // A few chunks per block: as many for each, not one more for some
+        // (150 M voxels, 1024 bins: 573 chunks on 256 blocks 124 us, 768 115).
+        if (automatic && g_chunk < 0 && chunks > blocks && chunks < 8 * blocks)
+            chunks = (chunks + blocks - 1) / blocks * blocks;
         if (blocks > chunks) blocks = chunks;
         if (blocks > MAX_BLOCKS) blocks = MAX_BLOCKS;
         if (p->hist == HIST_FINE && blocks > 256) blocks = 256;  // rows of the dump
@@ -523,22 +564,19 @@ int make_plan(const Box &b, bool stats, int hist_kind_req, int nbins, Plan *p, b
     // persistent wave on large boxes (shorter per-block ranges, overlapped
     // tails).
     const long long cap = (long long)cu_count() * (bpc < 4 ? 4 : bpc);
-    const long long per_block_min = (long long)threads * 16 * 2;  // two main-loop steps
+    const long long per_block_min = 4096;  // voxels
     if (blocks <= 0) {
         blocks = (long long)((b.n + per_block_min - 1) / per_block_min);
-        // Every block adds a fixed cost at the end of the pass (its ticket
-        // atomic on one address, its release fence, its records for the
-        // final merge, and for histograms one flush of every bin; measured
-        // at 9-30 ns per block for the first three), while the streaming
-        // time falls as n / blocks: the sum is least near sqrt(n) blocks.
-        // Measured on boxes of 2^16 to 2^30 voxels, the fastest counts were
-        // about sqrt(n) / 16, up to one block per CU for histogram passes
-        // (each block flushes its whole LDS histogram) and two for the
-        // statistics pass; the largest boxes keep the CU cap (or the tuned
-        // shape).
+        // Every block adds a fixed cost at the end of the pass (its ticket,
+        // its flush of every bin, its record for the final merge), while the
+        // streaming time falls as n / blocks: the sum is least near sqrt(n)
+        // blocks.  Measured on boxes of 2^17 to 2^27 voxels with the shapes
+        // above, the fastest counts were about sqrt(n) / 11 for histogram
+        // passes and sqrt(n) / 8 for statistics, up to one block per CU; the
+        // largest boxes keep the CU cap (or the tuned shape).
         if (b.n < ((uint64_t)1 << 31)) {
-            long long root = (long long)sqrt((double)b.n) / 16;
-            const long long mid = (long long)cu_count() * (hist_kind_req ? 1 : 2);
+            long long root = (long long)sqrt((double)b.n) / (hist_kind_req ? 11 : 8);
+            const long long mid = (long long)cu_count() * (automatic ? def.per_cu : 1);
             if (root > mid) root = mid;
             if (blocks > root) blocks = root < 1 ? 1 : root;
         }

@@ -2,7 +2,7 @@
 //
 // k_pass streams one box once (the device code is in cube_device.h): each
 // block scans a contiguous range of work units, reduces its wavefronts into
-// records (the local stage of the paper's two-stage gather, Section 2),
+// one record (the local stage of the paper's two-stage gather, Section 2),
 // flushes its LDS histogram with one 64-bit atomic per non-empty bin, and the
 // last block to finish (a ticket counter) merges every record in a fixed
 // order in FP64 (the global stage) and writes the results.  Results are
@@ -17,6 +17,7 @@ __global__ void __launch_bounds__(1024) k_pass(PassArgs a)
 {
     extern __shared__ unsigned int lds[];
     __shared__ unsigned int s_last;
+    __shared__ WaveRec s_parts[MAX_WAVES];
     __shared__ unsigned int s_inr, s_tot;  // HIST_HOT: in-range and LDS-counted voxels
     __shared__ int s_hot;
     const int tid = threadIdx.x;
@@ -58,29 +59,44 @@ __global__ void __launch_bounds__(1024) k_pass(PassArgs a)
     else  // an invalid range bins nothing: count valid voxels only
         scan<STATS, HIST_NONE, ACC, U, PACKED>(g, u0, u1, L, W, H);
 
-    write_wave_record<STATS, ACC>(L, W, &a.recs[(long long)blockIdx.x * nw + wid]);
+    // One record per block; the modes whose final merge is in FP32 keep one
+    // per wavefront.
+    const bool fp32_merge = STATS && a.accum_mode != CUBE_ACCUM_FP64MERGE;
+    if (fp32_merge)
+        write_wave_record<STATS, ACC, true>(L, W, &a.recs[(long long)blockIdx.x * nw + wid]);
+    else
+        write_wave_record<STATS, ACC>(L, W, &s_parts[wid]);
     unsigned int *row =
         a.dump ? a.dump + (size_t)blockIdx.x * (HIST == HIST_FINE ? FINE_WORDS : a.nbins) : nullptr;
+    // The flushes start with a barrier, which publishes s_parts as well.
     if (HIST == HIST_LDS) hist_flush(lds, a.nbins, a.copies_log2, a.hist_acc, row);
     if (HIST == HIST_FINE) fine_dump(lds, row);
     if (HIST == HIST_HOT) {
         if (hist_on) add_in_range(W, &s_inr);
         hist_flush_hot(lds, a.nbins, a.copies_log2, a.hist_acc, H.hot, &s_inr, &s_tot);
     }
+    if (HIST == HIST_NONE || HIST == HIST_GLOBAL) __syncthreads();
+    ChunkRec *brecs = reinterpret_cast<ChunkRec *>(a.recs);
+    if (!fp32_merge && wid == nw - 1)
+        write_chunk_record<STATS, true>(s_parts, nw, brecs + blockIdx.x);
 
-    // Ticket: the last block to arrive performs the global stage.  One
-    // release fence per block, not per thread: a fence in every thread costs
-    // a write-back of the L2 per wavefront (measured: about a tenth of the
-    // pass).
-    if (!last_to_arrive(a.ticket, gridDim.x, &s_last)) return;
+    // Ticket: the last block to arrive performs the global stage.  What it
+    // reads are write-through records and atomics, so no block writes its L2
+    // back (a release fence here: 2 to 4.5 us at the end of every pass).
+    if (!last_to_arrive_wt(a.ticket, gridDim.x, &s_last)) return;
 
-    const int n_recs = (int)gridDim.x * nw;
     unsigned long long nv, below, above;
     if (STATS) {
-        finish_stats<ACC>(a.recs, n_recs, a.accum_mode, g.n_total, a.out,
-                          a.want_range ? a.out_range : nullptr, a.nbins, nv, below, above);
+        cube_stats_t *out = a.out;
+        HistRange *out_range = a.want_range ? a.out_range : nullptr;
+        if (fp32_merge)
+            finish_stats<ACC>(a.recs, (int)gridDim.x * nw, a.accum_mode, g.n_total, out, out_range,
+                              a.nbins, nv, below, above);
+        else
+            finish_stats<ACC, ChunkRec>(brecs, (int)gridDim.x, CUBE_ACCUM_FP64MERGE, g.n_total,
+                                        out, out_range, a.nbins, nv, below, above);
     } else {
-        const Summary<float> S = merge_records<float, CUBE_ACCUM_KAHAN32>(a.recs, n_recs);
+        const BlockSums S = merge_counts<ChunkRec>(brecs, (int)gridDim.x);
         nv = S.nv;
         below = S.below;
         above = S.above;
@@ -107,7 +123,7 @@ __global__ void __launch_bounds__(1024) k_pass_dyn(PassArgs a)
 {
     extern __shared__ unsigned int lds[];
     __shared__ unsigned int s_last;
-    __shared__ int s_chunk;
+    __shared__ int s_chunk[2];        // the chunk at work and the one after it, in turn
     __shared__ int s_ids[MAX_WAVES];  // the chunks whose parts the ring holds
     const int tid = threadIdx.x;
     const int wid = tid >> 6, nw = blockDim.x >> 6;
@@ -129,7 +145,7 @@ __global__ void __launch_bounds__(1024) k_pass_dyn(PassArgs a)
     // A chunk spans at most this many voxels (whole units of seg_len floats).
     const long long chunk_max =
         (long long)((g.n_units + (unsigned long long)nc - 1) / (unsigned long long)nc) * g.seg_len;
-    if (tid == 0) s_chunk = (int)atomicAdd(ctr, 1u);
+    if (tid == 0) s_chunk[0] = (int)atomicAdd(ctr, 1u);
     if (HIST == HIST_FINE) {
         fine_setup(H);
         fine_zero(lds);  // ends with a barrier
@@ -141,8 +157,8 @@ __global__ void __launch_bounds__(1024) k_pass_dyn(PassArgs a)
 
     long long since_flush = 0;  // voxels counted in LDS since it was last zeroed
     int filled = 0;             // chunks in the ring (uniform)
-    while (true) {
-        const int c = s_chunk;
+    for (int turn = 0;; turn ^= 1) {
+        const int c = s_chunk[turn];
         if (c >= nc) break;
         // Claim the next chunk now, unless the list is near its end (a block
         // holding a claimed chunk while others run out would idle them).
@@ -168,15 +184,17 @@ __global__ void __launch_bounds__(1024) k_pass_dyn(PassArgs a)
         else
             scan<STATS, HIST_NONE, ACC, U, PACKED>(g, u0, u1, L, W, H);
         write_wave_record<STATS, ACC>(L, W, &ring[filled * nw + wid]);
-        if (tid == 0) s_ids[filled] = c;
-        __syncthreads();  // every part written; every thread has read s_chunk
-        if (tid == 0) s_chunk = (int)(early ? next : atomicAdd(ctr, 1u));
-        __syncthreads();
+        // The other word was last read before the previous chunk's barrier.
+        if (tid == 0) {
+            s_ids[filled] = c;
+            s_chunk[turn ^ 1] = (int)(early ? next : atomicAdd(ctr, 1u));
+        }
+        __syncthreads();  // every part and the next chunk written
         // When the ring is full, every wavefront merges one of its chunks
         // (one merge time per nw chunks, not one per chunk on the critical
         // path), and a barrier frees the ring.
         if (++filled == nw) {
-            write_chunk_record<STATS>(&ring[wid * nw], nw,
+            write_chunk_record<STATS, true>(&ring[wid * nw], nw,
                                       reinterpret_cast<ChunkRec *>(a.recs) + s_ids[wid]);
             __syncthreads();
             filled = 0;
@@ -184,14 +202,14 @@ __global__ void __launch_bounds__(1024) k_pass_dyn(PassArgs a)
     }
     // The chunks left in the ring (published by the loop's last barrier).
     if (wid < filled)
-        write_chunk_record<STATS>(&ring[wid * nw], nw,
+        write_chunk_record<STATS, true>(&ring[wid * nw], nw,
                                   reinterpret_cast<ChunkRec *>(a.recs) + s_ids[wid]);
     unsigned int *row =
         a.dump ? a.dump + (size_t)blockIdx.x * (HIST == HIST_FINE ? FINE_WORDS : a.nbins) : nullptr;
     if (HIST == HIST_LDS) hist_flush(lds, a.nbins, a.copies_log2, a.hist_acc, row);
     if (HIST == HIST_FINE) fine_dump(lds, row);
 
-    if (!last_to_arrive(a.ticket, gridDim.x, &s_last)) return;
+    if (!last_to_arrive_wt(a.ticket, gridDim.x, &s_last)) return;
 
     const ChunkRec *recs = reinterpret_cast<const ChunkRec *>(a.recs);
     unsigned long long nv, below, above;
@@ -200,7 +218,7 @@ __global__ void __launch_bounds__(1024) k_pass_dyn(PassArgs a)
                                     a.want_range ? a.out_range : nullptr, a.nbins, nv, below,
                                     above);
     } else {
-        const Summary<double> S = merge_two_sweep<ChunkRec>(recs, nc);
+        const BlockSums S = merge_counts<ChunkRec>(recs, nc);
         nv = S.nv;
         below = S.below;
         above = S.above;

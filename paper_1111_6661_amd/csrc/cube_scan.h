@@ -54,9 +54,7 @@ __device__ __forceinline__ void scan_units_of(const Geom &g, long long u0, long 
         const f4 *q4 = (const f4 *)(q + h);
         const long long T = (long long)B * SEL_U;
         long long i0 = 0;
-        for (; i0 + T <= n4; i0 += T) {
-            f4 v[SEL_U];
-            load_tile<SEL_U>(v, q4, i0, B, tid);
+        auto tile = [&](const f4 (&v)[SEL_U]) {
             float xv[4 * SEL_U];
 #pragma unroll
             for (int k = 0; k < SEL_U; ++k) {
@@ -66,8 +64,20 @@ __device__ __forceinline__ void scan_units_of(const Geom &g, long long u0, long 
                 xv[4 * k + 3] = v[k].w;
             }
             step(xv);
+        };
+        for (; i0 + T <= n4; i0 += T) {
+            f4 v[SEL_U];
+            load_tile<SEL_U>(v, q4, i0, B, tid);
+            tile(v);
         }
-        for (; i0 < n4; i0 += B) {
+        // A remainder of more than one vector per lane is one more tile.
+        if (n4 - i0 > B) {
+            f4 v[SEL_U];
+            load_part<SEL_U>(v, q4 + i0, (int)(n4 - i0), B, tid);
+            tile(v);
+            i0 = n4;
+        }
+        if (i0 < n4) {
             const long long i = i0 + tid;
             const bool have = i < n4;
             const f4 v = __builtin_nontemporal_load(q4 + (have ? i : n4 - 1));
