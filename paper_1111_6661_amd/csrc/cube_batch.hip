@@ -334,8 +334,8 @@ __global__ void __launch_bounds__(1024) k_batch(BatchArgs a)
             Hist H;
             hist_on = hist && range.ok == 1;
             hist_setup(H, range, it.nbins, a.copies_log2, lds, acc);
-            Lane L = {INFINITY, -INFINITY, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            Wave W = {0.f, 0, 0ull, 0ull, 0ull};
+            Lane L = LANE_ZERO;
+            Wave W = {0.f, 0, 0ull, 0ull, 0ull, 0ull};
             if (!skip) {
                 if (stats && hist_on)
                     batch_scan<true, HIST_LDS, U>(it, u0, u1, L, W, H);

@@ -7,10 +7,13 @@
 //   * blank test (x != x), counted with a wavefront ballot on the scalar unit;
 //   * min / max of the quieted value (v_min3/v_max3 order -0 before +0 and
 //     skip quiet NaNs; a signalling NaN is quieted first);
-//   * moments d = x - K and d^2 about a per-wavefront pivot K (the first
-//     valid voxel the wavefront meets), summed in FP32 over a chunk of at most
-//     two tiles and folded into a TwoSum-compensated lane accumulator
-//     (Knuth's TwoSum);
+//   * moments about a per-wavefront pivot K (the first valid voxel the
+//     wavefront meets): (x - K)^2 in FP32 over a chunk of at most two tiles,
+//     folded into a TwoSum-compensated lane accumulator (Knuth's TwoSum), and
+//     the sum of x in FP64.  An FP64 add issues at the rate of an FP32 add;
+//     it makes the mean exact to about 1e-15, where FP32 sums of 32 voxels
+//     leave it an error of 5e-7 / sqrt(n) standard deviations (400 boxes of
+//     2^17 to 2^26 noise voxels);
 //   * the histogram bin min(nbins-1, floor((x - lo) * scale)) in FP32 (two
 //     rounded operations, then v_cvt_flr_i32_f32), counted in LDS
 //     sub-histograms interleaved per lane; blank and out-of-range voxels go
@@ -123,10 +126,21 @@ __device__ __forceinline__ float from_lane(float x, int l)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
 }
 
+// How a pass sums x: CUBE_ACCUM_FP64MERGE in FP64 per voxel; CUBE_ACCUM_NAIVE32
+// in FP32; ACC_FP32_SUMS as FP32 deviations from the pivot over a chunk of at
+// most two tiles, folded into a TwoSum pair.  The passes with a dynamic
+// partition take the last one: their arithmetic is the bound beside HBM, and
+// the FP64 sum's one more instruction per voxel costs them 2 % (2^32 voxels,
+// 1024 bins: 2.49 against 2.44 ms; the others measure the same with either).
+constexpr int ACC_FP32_SUMS = 3;
+
 struct Lane {
-    float mn, mx, s1, c1, s2, c2;
-    float p1, p2;  // FP32 chunk sums not yet folded into (s1, c1), (s2, c2)
+    float mn, mx, s2, c2;
+    float p2;      // FP32 chunk sum not yet folded into (s2, c2)
+    float s1, c1, p1;  // the same of the first moment (ACC_FP32_SUMS; s1 alone: naive)
+    double x;      // sum of x (CUBE_ACCUM_FP64MERGE)
 };
+constexpr Lane LANE_ZERO = {INFINITY, -INFINITY, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.0};
 
 // Fold the pending FP32 chunk sums into the compensated lane accumulators
 // (TwoSum).  Called after every second tile and at the end of every unit, so
@@ -134,10 +148,12 @@ struct Lane {
 template <bool STATS, int ACC>
 __device__ __forceinline__ void fold(Lane &L)
 {
-    if (STATS && ACC != CUBE_ACCUM_NAIVE32) {
+    if (STATS && ACC == ACC_FP32_SUMS) {
         two_sum_acc(L.s1, L.c1, L.p1);
-        two_sum_acc(L.s2, L.c2, L.p2);
         L.p1 = 0.f;
+    }
+    if (STATS && ACC != CUBE_ACCUM_NAIVE32) {
+        two_sum_acc(L.s2, L.c2, L.p2);
         L.p2 = 0.f;
     }
 }
@@ -145,6 +161,7 @@ __device__ __forceinline__ void fold(Lane &L)
 struct Wave {  // wavefront-uniform
     float K;
     int has_k;
+    unsigned long long slots;  // CUBE_ACCUM_FP64MERGE: voxel slots since K was set, valid or not
     unsigned long long valid, ge, le;  // ballot counts: valid, x >= lo, x <= hi
 };
 
@@ -200,12 +217,18 @@ __device__ __forceinline__ unsigned int lds_offset(const unsigned int *p)
     return (unsigned int)(size_t)(__attribute__((address_space(3))) const unsigned int *)p;
 }
 
-// m[lane] ? v : 0, and m[lane] ? v : -1 -- one v_cndmask_b32 reading a
+// m[lane] ? v : 0, m[lane] ? v : k, and m[lane] ? v : -1 -- one v_cndmask_b32 reading a
 // ballot mask directly, so a mask a ballot already produced is reused.
 __device__ __forceinline__ float keep_where(float v, unsigned long long m)
 {
     float r;
     asm("v_cndmask_b32_e64 %0, 0, %1, %2" : "=v"(r) : "v"(v), "s"(m));
+    return r;
+}
+__device__ __forceinline__ float keep_or(float v, float k, unsigned long long m)
+{
+    float r;
+    asm("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "v"(k), "v"(v), "s"(m));
     return r;
 }
 __device__ __forceinline__ int keep_or_minus1(int v, unsigned long long m)
@@ -273,7 +296,10 @@ __device__ __forceinline__ void process(const float (&x)[NV], Lane &L, Wave &W,
     // Ballot counts of this step in 32-bit scalars (at most 64 * NV each).
     unsigned int cvalid = 0, cge = 0, cle = 0;
     unsigned int fine_seen = 0;  // HIST_FINE: the words added to, as they were
-    float t1 = L.p1, t2 = L.p2;
+    float t2 = L.p2;
+    const float K = W.K;
+    float t1 = L.p1;
+    if (STATS && ACC == CUBE_ACCUM_FP64MERGE) W.slots += W.has_k ? 64ull * NV : 0ull;
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
         const float v = x[j];
@@ -298,9 +324,16 @@ __device__ __forceinline__ void process(const float (&x)[NV], Lane &L, Wave &W,
                 const float d = keep_where(v, mvalid);
                 L.s1 += d;
                 L.s2 = __fmaf_rn(d, d, L.s2);
-            } else {
-                const float d = keep_where(__fsub_rn(v, W.K), mvalid);
+            } else if (ACC == ACC_FP32_SUMS) {
+                const float d = keep_where(__fsub_rn(v, K), mvalid);
                 t1 += d;
+                t2 = __fmaf_rn(d, d, t2);
+            } else {
+                // Slots without a valid voxel take K: no deviation, and a
+                // known part of the sum.
+                const float w = keep_or(v, K, mvalid);
+                L.x += (double)w;
+                const float d = __fsub_rn(w, K);
                 t2 = __fmaf_rn(d, d, t2);
             }
         }
@@ -392,19 +425,18 @@ __device__ __forceinline__ Summary<T> shfl_xor_summary(const Summary<T> &s, int 
     return o;
 }
 
-// The (count, mean, m2) of one wavefront record: its pivoted sums
-// S1 = sum(x - K), S2 = sum((x - K)^2) give mean = K + S1/n and
-// m2 = S2 - S1^2/n (clamped at 0).
+// The (count, mean, m2) of one wavefront record: S1 = sum(x - K) and
+// S2 = sum((x - K)^2) give mean = K + S1/n and m2 = S2 - S1^2/n (clamped at 0).
 template <typename T, int ACC>
 __device__ __forceinline__ void moments_of(const WaveRec &w, T &mb, T &m2b)
 {
     const double nb = (double)w.n_valid;
     if (ACC == CUBE_ACCUM_NAIVE32) {
-        const T S1 = (T)w.s1h, S2 = (T)w.s2h, n = (T)nb;
+        const T S1 = (T)w.s1, S2 = (T)w.s2h, n = (T)nb;
         mb = S1 / n;
         m2b = S2 - S1 * S1 / n;
     } else {
-        const T S1 = (T)w.s1h + (T)w.s1l;
+        const T S1 = (T)(w.s1 - nb * (double)w.K);
         const T S2 = (T)w.s2h + (T)w.s2l;
         mb = (T)w.K + S1 / (T)nb;
         m2b = S2 - S1 * S1 / (T)nb;
@@ -525,8 +557,8 @@ __device__ __forceinline__ double block_sum(double s, double *ws)
 // The two terms each record adds to the two sweeps of the FP64 global
 // stage below: its sum of x, and its sum of (x - mean)^2 about the global
 // mean.  A chunk record holds (n, mean_c, m2_c): n * mean_c and
-// m2_c + n * (mean_c - mean)^2.  A wavefront record holds the pivoted sums
-// S1 = sum(x - K), S2 = sum((x - K)^2): n * K + S1 and, with d = K - mean,
+// m2_c + n * (mean_c - mean)^2.  A wavefront record holds sum(x) itself and
+// S2 = sum((x - K)^2): with S1 = sum(x) - n K and d = K - mean,
 // sum((x - K) + d)^2 = S2 + 2 d S1 + n d^2.  Both forms are exact identities;
 // neither divides.
 __device__ __forceinline__ double sweep1_term(const ChunkRec &c)
@@ -540,12 +572,12 @@ __device__ __forceinline__ double sweep2_term(const ChunkRec &c, double mean)
 }
 __device__ __forceinline__ double sweep1_term(const WaveRec &w)
 {
-    return (double)w.n_valid * (double)w.K + ((double)w.s1h + (double)w.s1l);
+    return w.s1;
 }
 __device__ __forceinline__ double sweep2_term(const WaveRec &w, double mean)
 {
     const double d = (double)w.K - mean;
-    const double S1 = (double)w.s1h + (double)w.s1l;
+    const double S1 = w.s1 - (double)w.n_valid * (double)w.K;
     const double S2 = (double)w.s2h + (double)w.s2l;
     return S2 + 2.0 * d * S1 + (double)w.n_valid * d * d;
 }
@@ -971,20 +1003,24 @@ __device__ __forceinline__ void store_record(const R &r, R *dst)
 
 template <int ACC>
 struct LaneStep {
-    float &mn, &mx, &s1h, &s1l, &s2h, &s2l;
+    Lane &l;
     template <class C, class R>
     __device__ __forceinline__ void operator()(C, R)
     {
-        mn = fminf(mn, dpp<C::value, R::value>(INFINITY, mn));
-        mx = fmaxf(mx, dpp<C::value, R::value>(-INFINITY, mx));
-        const float o1h = dpp<C::value, R::value>(0.f, s1h);
-        const float o2h = dpp<C::value, R::value>(0.f, s2h);
+        l.mn = fminf(l.mn, dpp<C::value, R::value>(INFINITY, l.mn));
+        l.mx = fmaxf(l.mx, dpp<C::value, R::value>(-INFINITY, l.mx));
+        const float o2 = dpp<C::value, R::value>(0.f, l.s2);
+        if (ACC == CUBE_ACCUM_FP64MERGE)
+            l.x = dpp<C::value, R::value>(0.0, l.x) + l.x;
         if (ACC == CUBE_ACCUM_NAIVE32) {
-            s1h += o1h;
-            s2h += o2h;
+            l.s1 += dpp<C::value, R::value>(0.f, l.s1);
+            l.s2 += o2;
         } else {
-            df_add(s1h, s1l, o1h, dpp<C::value, R::value>(0.f, s1l));
-            df_add(s2h, s2l, o2h, dpp<C::value, R::value>(0.f, s2l));
+            df_add(l.s2, l.c2, o2, dpp<C::value, R::value>(0.f, l.c2));
+            if (ACC == ACC_FP32_SUMS) {
+                const float o1 = dpp<C::value, R::value>(0.f, l.s1);
+                df_add(l.s1, l.c1, o1, dpp<C::value, R::value>(0.f, l.c1));
+            }
         }
     }
 };
@@ -994,20 +1030,22 @@ struct LaneStep {
 template <bool STATS, int ACC, bool WT = false>
 __device__ __forceinline__ void write_wave_record(const Lane &L, const Wave &W, WaveRec *dst)
 {
-    float mn = L.mn, mx = L.mx, s1h = L.s1, s1l = L.c1, s2h = L.s2, s2l = L.c2;
-    if (STATS) wave_reduce(LaneStep<ACC>{mn, mx, s1h, s1l, s2h, s2l});
+    Lane l = L;
+    if (STATS) wave_reduce(LaneStep<ACC>{l});
     if ((threadIdx.x & 63) == WAVE_LAST) {
         WaveRec r;
         r.n_valid = W.valid;
         r.below = W.valid - W.ge;
         r.above = W.valid - W.le;
         r.K = W.K;
-        r.s1h = s1h;
-        r.s1l = s1l;
-        r.s2h = s2h;
-        r.s2l = s2l;
-        r.mn = mn;
-        r.mx = mx;
+        r.s1 = ACC == CUBE_ACCUM_NAIVE32 ? (double)l.s1
+               : ACC == ACC_FP32_SUMS
+                   ? (double)W.K * (double)W.valid + ((double)l.s1 + (double)l.c1)
+                   : l.x - (double)W.K * (double)(W.slots - W.valid);
+        r.s2h = l.s2;
+        r.s2l = l.c2;
+        r.mn = l.mn;
+        r.mx = l.mx;
         r.pad = 0.f;
         r.pad2 = 0ull;
         store_record<WT>(r, dst);

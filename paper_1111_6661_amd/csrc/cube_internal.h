@@ -15,10 +15,12 @@
 namespace cube {
 
 // One partial result per wavefront (the local stage of the paper's two-stage
-// gather, Section 2).  Moments are FP32 double-float pairs relative to the
-// wavefront's pivot K; in the naive mode K = 0 and the lo parts are 0.
+// gather, Section 2): the sum of its valid voxels in FP64 and the sum of their
+// squared deviations from its pivot K as an FP32 double-float pair; in the
+// naive mode both are plain FP32 sums, K = 0 and s2l = 0.
 struct alignas(16) WaveRec {
-    float K, s1h, s1l, s2h, s2l, mn, mx, pad;
+    float K, s2h, s2l, mn, mx, pad;
+    double s1;
     unsigned long long n_valid, below, above, pad2;
 };
 static_assert(sizeof(WaveRec) == 64, "WaveRec is 64 bytes");

@@ -51,8 +51,8 @@ __global__ void __launch_bounds__(1024) k_pass(PassArgs a)
         fine_zero(lds);
     }
 
-    Lane L = {INFINITY, -INFINITY, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    Wave W = {0.f, ACC == CUBE_ACCUM_NAIVE32 ? 1 : 0, 0ull, 0ull, 0ull};
+    Lane L = LANE_ZERO;
+    Wave W = {0.f, ACC == CUBE_ACCUM_NAIVE32 ? 1 : 0, 0ull, 0ull, 0ull, 0ull};
 
     if (HIST == HIST_NONE || hist_on)
         scan<STATS, HIST, ACC, U, PACKED>(g, u0, u1, L, W, H);
@@ -127,7 +127,7 @@ __global__ void __launch_bounds__(1024) k_pass_dyn(PassArgs a)
     __shared__ int s_ids[MAX_WAVES];  // the chunks whose parts the ring holds
     const int tid = threadIdx.x;
     const int wid = tid >> 6, nw = blockDim.x >> 6;
-    constexpr int ACC = CUBE_ACCUM_FP64MERGE;
+    constexpr int ACC = ACC_FP32_SUMS;
     // The ring of wavefront records (dynamic LDS after the histogram): nw
     // chunks of nw records each.
     WaveRec *ring = reinterpret_cast<WaveRec *>(
@@ -177,8 +177,8 @@ __global__ void __launch_bounds__(1024) k_pass_dyn(PassArgs a)
         }
         since_flush += chunk_max;
 
-        Lane L = {INFINITY, -INFINITY, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        Wave W = {0.f, 0, 0ull, 0ull, 0ull};
+        Lane L = LANE_ZERO;
+        Wave W = {0.f, 0, 0ull, 0ull, 0ull, 0ull};
         if (HIST == HIST_NONE || hist_on)
             scan<STATS, HIST, ACC, U, PACKED>(g, u0, u1, L, W, H);
         else
@@ -214,7 +214,7 @@ __global__ void __launch_bounds__(1024) k_pass_dyn(PassArgs a)
     const ChunkRec *recs = reinterpret_cast<const ChunkRec *>(a.recs);
     unsigned long long nv, below, above;
     if (STATS) {
-        finish_stats<ACC, ChunkRec>(recs, nc, CUBE_ACCUM_FP64MERGE, g.n_total, a.out,
+        finish_stats<CUBE_ACCUM_FP64MERGE, ChunkRec>(recs, nc, CUBE_ACCUM_FP64MERGE, g.n_total, a.out,
                                     a.want_range ? a.out_range : nullptr, a.nbins, nv, below,
                                     above);
     } else {
