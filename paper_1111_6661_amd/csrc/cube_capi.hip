@@ -8,6 +8,7 @@
 #include <string.h>
 
 #include <atomic>
+#include <chrono>
 #include <map>
 #include <mutex>
 #include <string>
@@ -101,8 +102,12 @@ struct Workspace {
     cube_stats_t *d_out = nullptr;
     unsigned long long *d_counts = nullptr;
     HistRange *d_range = nullptr;
-    cube_stats_t *h_out = nullptr;        // pinned
+    // Results of the synchronous calls: pinned host memory that the kernels
+    // write directly (d_*: the same memory as the device sees it).
+    cube_stats_t *h_out = nullptr;
     unsigned long long *h_counts = nullptr;
+    unsigned int *h_done = nullptr, *d_done = nullptr;  // the call whose results are there
+    unsigned int calls = 0;
     unsigned int *dump = nullptr;         // blocks' rows of counts (many bins), DUMP_BYTES
     hipEvent_t used = nullptr;            // recorded after the last work queued with it
     std::mutex mu;                        // held by synchronous calls
@@ -111,6 +116,8 @@ struct Workspace {
 std::mutex g_mu;
 std::map<std::pair<int, hipStream_t>, Workspace *> g_ws;
 std::map<int, int> g_cus;
+
+constexpr unsigned int RESULT_MEM = hipHostMallocMapped | hipHostMallocCoherent;
 
 // Waits for the last work queued with the workspace through its event, not
 // through its stream: the caller may have destroyed that stream already.
@@ -126,12 +133,11 @@ void free_ws(Workspace *w)
     hipFree(w->recs);
     hipFree(w->ticket);
     hipFree(w->hist_acc);
-    hipFree(w->d_out);
-    hipFree(w->d_counts);
     hipFree(w->d_range);
     hipFree(w->dump);
     hipHostFree(w->h_out);
     hipHostFree(w->h_counts);
+    hipHostFree(w->h_done);
     hipSetDevice(prev);
     delete w;
 }
@@ -156,11 +162,13 @@ int get_ws(hipStream_t s, Workspace **out)
               hipMalloc(&w->recs, REC_CAP * sizeof(WaveRec)) == hipSuccess &&
               hipMalloc(&w->ticket, 256) == hipSuccess &&
               hipMalloc(&w->hist_acc, nacc * 8) == hipSuccess &&
-              hipMalloc(&w->d_out, sizeof(cube_stats_t)) == hipSuccess &&
-              hipMalloc(&w->d_counts, nacc * 8) == hipSuccess &&
               hipMalloc(&w->d_range, 256) == hipSuccess &&
-              hipHostMalloc(&w->h_out, sizeof(cube_stats_t)) == hipSuccess &&
-              hipHostMalloc(&w->h_counts, nacc * 8) == hipSuccess;
+              hipHostMalloc(&w->h_out, sizeof(cube_stats_t), RESULT_MEM) == hipSuccess &&
+              hipHostMalloc(&w->h_counts, nacc * 8, RESULT_MEM) == hipSuccess &&
+              hipHostMalloc(&w->h_done, 64, RESULT_MEM) == hipSuccess &&
+              hipHostGetDevicePointer((void **)&w->d_done, w->h_done, 0) == hipSuccess &&
+              hipHostGetDevicePointer((void **)&w->d_out, w->h_out, 0) == hipSuccess &&
+              hipHostGetDevicePointer((void **)&w->d_counts, w->h_counts, 0) == hipSuccess;
     if (!ok) {
         hipGetLastError();
         free_ws(w);
@@ -172,6 +180,7 @@ int get_ws(hipStream_t s, Workspace **out)
         free_ws(w);
         return hip_fail(e, "workspace initialisation");
     }
+    *w->h_done = 0u;
     g_ws[key] = w;
     *out = w;
     return CUBE_OK;
@@ -682,12 +691,39 @@ PassArgs base_args(const Workspace *w, const Plan &p, int nbins)
     return a;
 }
 
+// A synchronous call's last pass tells the CPU when its results are there
+// (*done_gen, 0 where it cannot: many bins are finished by a second kernel).
+void ask_done(PassArgs &a, Workspace *w, unsigned int *done_gen)
+{
+    if (!done_gen || (a.counts && a.nbins >= DEFER_MIN_BINS)) return;
+    if (++w->calls == 0u) w->calls = 1u;
+    *done_gen = a.done_gen = w->calls;
+    a.done = w->d_done;
+}
+
+// Wait for it.  Polling sees the results about 4 us before the stream's own
+// completion does; after 100 us without them (a large box, or a failure) the
+// stream is waited for instead.
+hipError_t wait_done(const Workspace *w, unsigned int gen)
+{
+    if (gen) {
+        const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(100);
+        do {
+            for (int k = 0; k < 64; ++k) {
+                if (__atomic_load_n(w->h_done, __ATOMIC_ACQUIRE) == gen) return hipSuccess;
+                __builtin_ia32_pause();
+            }
+        } while (std::chrono::steady_clock::now() < until);
+    }
+    return hipStreamSynchronize(nullptr);
+}
+
 // The four operations, stream-ordered, with device outputs.
 enum Op { OP_STATS, OP_HIST, OP_FUSED, OP_MINMAX };
 
 int run_async(Op op, const float *ptr, const int64_t *dims, float lo, float hi, int32_t nbins,
               cube_stats_t *dev_out, unsigned long long *dev_counts, hipStream_t s,
-              Workspace *w)
+              Workspace *w, unsigned int *done_gen = nullptr)
 {
     Box b;
     int rc = check_box(ptr, dims, &b);
@@ -719,6 +755,7 @@ int run_async(Op op, const float *ptr, const int64_t *dims, float lo, float hi, 
             a.want_range = 1;
             a.out_range = w->d_range;
         }
+        if (op == OP_STATS) ask_done(a, w, done_gen);
         if ((rc = launch(a, p, true, w, s))) return rc;
         if (op == OP_STATS) return CUBE_OK;
         Plan p2;
@@ -726,6 +763,7 @@ int run_async(Op op, const float *ptr, const int64_t *dims, float lo, float hi, 
         PassArgs a2 = base_args(w, p2, nbins);
         a2.dev_range = w->d_range;
         a2.counts = dev_counts;
+        ask_done(a2, w, done_gen);
         return launch(a2, p2, false, w, s);
     }
     const bool stats = op == OP_FUSED;
@@ -734,6 +772,7 @@ int run_async(Op op, const float *ptr, const int64_t *dims, float lo, float hi, 
     a.range = range;
     a.out = dev_out;
     a.counts = dev_counts;
+    ask_done(a, w, done_gen);
     return launch(a, p, stats, w, s);
 }
 
@@ -789,19 +828,13 @@ int run_sync(Op op, const float *ptr, const int64_t *dims, float lo, float hi, i
     rc = get_ws(nullptr, &w);
     if (rc) return rc;
     std::lock_guard<std::mutex> lk(w->mu);
-    rc = run_async(op, ptr, dims, lo, hi, nbins, w->d_out, w->d_counts, nullptr, w);
+    unsigned int gen = 0u;
+    rc = run_async(op, ptr, dims, lo, hi, nbins, w->d_out, w->d_counts, nullptr, w, &gen);
     if (rc) return rc;
-    hipError_t e;
-    if (op != OP_HIST &&
-        (e = hipMemcpyAsync(w->h_out, w->d_out, sizeof(cube_stats_t), hipMemcpyDeviceToHost,
-                            nullptr)) != hipSuccess)
-        return hip_fail(e, "result copy");
-    if (op != OP_STATS &&
-        (e = hipMemcpyAsync(w->h_counts, w->d_counts, ((size_t)nbins + 3) * 8,
-                            hipMemcpyDeviceToHost, nullptr)) != hipSuccess)
-        return hip_fail(e, "counts copy");
-    if ((e = hipStreamSynchronize(nullptr)) != hipSuccess) return hip_fail(e, "synchronize");
-    if ((rc = mark_ws(w, nullptr))) return rc;
+    // The kernels wrote the results to host memory (a copy of each took 3-5
+    // us), and nothing of this call is left to wait for afterwards.
+    const hipError_t e = wait_done(w, gen);
+    if (e != hipSuccess) return hip_fail(e, "synchronize");
     if (op != OP_HIST) *out = *w->h_out;
     if (op != OP_STATS) memcpy(counts, w->h_counts, ((size_t)nbins + 3) * 8);
     if (op == OP_MINMAX && (w->h_out->flags & CUBE_HIST_BAD_RANGE))

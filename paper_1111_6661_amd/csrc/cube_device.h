@@ -1206,6 +1206,28 @@ __device__ __forceinline__ HistRange range_of_extrema(float fmn, float fmx, unsi
     return r;
 }
 
+// A result word to memory; with HOST to host memory that the CPU polls, as a
+// system-scope atomic store (written through; a plain store may stay in the L2
+// until the kernel ends).
+template <bool HOST, class T>
+__device__ __forceinline__ void store_result(T *dst, T v)
+{
+    if (HOST)
+        __hip_atomic_store(dst, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    else
+        *dst = v;
+}
+
+// Tell the polling CPU that the block's results are in host memory: every
+// thread has waited for its own write-through stores before the barrier.
+__device__ __forceinline__ void tell_host(unsigned int *done, unsigned int gen)
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0)
+        __hip_atomic_store(done, gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Moments over the extended reals.  An infinite voxel is a valid value and
 // always one of the extrema, so the exact min and max show whether any are
 // present, at no cost per voxel: +Inf alone makes the mean +Inf, -Inf alone
@@ -1228,7 +1250,8 @@ template <int ACC, typename R = WaveRec>
 __device__ void finish_stats(const R *recs, int n_recs, int accum_mode,
                              unsigned long long n_total, cube_stats_t *out,
                              HistRange *range_out, int nbins, unsigned long long &nv,
-                             unsigned long long &below, unsigned long long &above)
+                             unsigned long long &below, unsigned long long &above,
+                             bool host = false)
 {
     float fmn, fmx;
     double mean, m2;
@@ -1272,25 +1295,44 @@ __device__ void finish_stats(const R *recs, int n_recs, int accum_mode,
         if (r.ok == 0) o.flags |= CUBE_HIST_BAD_RANGE;
         *range_out = r;
     }
-    *out = o;
+    if (host) {
+        const unsigned long long *w = reinterpret_cast<const unsigned long long *>(&o);
+        for (int i = 0; i < (int)(sizeof o / 8); ++i)
+            store_result<true>(reinterpret_cast<unsigned long long *>(out) + i, w[i]);
+    } else {
+        *out = o;
+    }
 }
 
 // Copy the global accumulators to the caller's counts (or, with `add`, add
 // them to the counts already there) and return them to zero; thread 0 writes
 // below / above / NaN.  `deferred`: the bins are left to launch_hist_sum.
+// `host`: the counts are host memory that the CPU polls (store_result).
 __device__ __forceinline__ void finish_hist(unsigned long long *acc, unsigned long long *counts,
                                             int nbins, bool on, unsigned long long below,
                                             unsigned long long above, unsigned long long n_nan,
-                                            bool add = false, bool deferred = false)
+                                            bool add = false, bool deferred = false,
+                                            bool host = false)
 {
-    for (int b = threadIdx.x; b < nbins && !deferred; b += blockDim.x) {
-        counts[b] = (add ? counts[b] : 0ull) + acc[b];
-        acc[b] = 0ull;
+    if (host) {
+        for (int b = threadIdx.x; b < nbins; b += blockDim.x) {
+            store_result<true>(&counts[b], acc[b]);
+            acc[b] = 0ull;
+        }
+    } else {
+        for (int b = threadIdx.x; b < nbins && !deferred; b += blockDim.x) {
+            counts[b] = (add ? counts[b] : 0ull) + acc[b];
+            acc[b] = 0ull;
+        }
     }
     if (threadIdx.x == 0) {
-        counts[nbins] = (add ? counts[nbins] : 0ull) + (on ? below : 0ull);
-        counts[nbins + 1] = (add ? counts[nbins + 1] : 0ull) + (on ? above : 0ull);
-        counts[nbins + 2] = (add ? counts[nbins + 2] : 0ull) + n_nan;
+        const unsigned long long last[3] = {on ? below : 0ull, on ? above : 0ull, n_nan};
+        for (int i = 0; i < 3; ++i) {
+            if (host)
+                store_result<true>(&counts[nbins + i], last[i]);
+            else
+                counts[nbins + i] = (add ? counts[nbins + i] : 0ull) + last[i];
+        }
     }
 }
 

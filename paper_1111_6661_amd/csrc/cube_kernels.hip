@@ -91,10 +91,11 @@ __global__ void __launch_bounds__(1024) k_pass(PassArgs a)
         HistRange *out_range = a.want_range ? a.out_range : nullptr;
         if (fp32_merge)
             finish_stats<ACC>(a.recs, (int)gridDim.x * nw, a.accum_mode, g.n_total, out, out_range,
-                              a.nbins, nv, below, above);
+                              a.nbins, nv, below, above, a.done != nullptr);
         else
             finish_stats<ACC, ChunkRec>(brecs, (int)gridDim.x, CUBE_ACCUM_FP64MERGE, g.n_total,
-                                        out, out_range, a.nbins, nv, below, above);
+                                        out, out_range, a.nbins, nv, below, above,
+                                        a.done != nullptr);
     } else {
         const BlockSums S = merge_counts<ChunkRec>(brecs, (int)gridDim.x);
         nv = S.nv;
@@ -103,8 +104,9 @@ __global__ void __launch_bounds__(1024) k_pass(PassArgs a)
     }
     if (HIST != HIST_NONE)
         finish_hist(a.hist_acc, a.counts, a.nbins, hist_on, below, above, g.n_total - nv,
-                    a.accumulate != 0, a.defer_bins != 0);
+                    a.accumulate != 0, a.defer_bins != 0, a.done != nullptr);
     if (tid == 0) *a.ticket = 0u;
+    if (a.done) tell_host(a.done, a.done_gen);
 }
 
 // k_pass_dyn is the same pass with a dynamic partition: the box is cut into
@@ -216,7 +218,7 @@ __global__ void __launch_bounds__(1024) k_pass_dyn(PassArgs a)
     if (STATS) {
         finish_stats<CUBE_ACCUM_FP64MERGE, ChunkRec>(recs, nc, CUBE_ACCUM_FP64MERGE, g.n_total, a.out,
                                     a.want_range ? a.out_range : nullptr, a.nbins, nv, below,
-                                    above);
+                                    above, a.done != nullptr);
     } else {
         const BlockSums S = merge_counts<ChunkRec>(recs, nc);
         nv = S.nv;
@@ -225,11 +227,12 @@ __global__ void __launch_bounds__(1024) k_pass_dyn(PassArgs a)
     }
     if (HIST != HIST_NONE)
         finish_hist(a.hist_acc, a.counts, a.nbins, hist_on, below, above, g.n_total - nv,
-                    a.accumulate != 0, a.defer_bins != 0);
+                    a.accumulate != 0, a.defer_bins != 0, a.done != nullptr);
     if (tid == 0) {
         *a.ticket = 0u;
         *ctr = 0u;
     }
+    if (a.done) tell_host(a.done, a.done_gen);
 }
 
 // The bins of a pass that left them to this kernel: the global accumulators
