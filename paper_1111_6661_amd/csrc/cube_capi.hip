@@ -208,6 +208,20 @@ bool have_dump(Workspace *w, hipStream_t s)
     return false;
 }
 
+// Polling sees the results about 4 us before the stream's own completion does;
+// after 100 us without them the stream is waited for instead.
+hipError_t poll_host(const unsigned int *done, unsigned int gen)
+{
+    const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(100);
+    do {
+        for (int k = 0; k < 64; ++k) {
+            if (__atomic_load_n(done, __ATOMIC_ACQUIRE) == gen) return hipSuccess;
+            __builtin_ia32_pause();
+        }
+    } while (std::chrono::steady_clock::now() < until);
+    return hipStreamSynchronize(nullptr);
+}
+
 // Record that work using `w` was queued on `s` (after a successful enqueue).
 int mark_ws(Workspace *w, hipStream_t s)
 {
@@ -701,23 +715,6 @@ void ask_done(PassArgs &a, Workspace *w, unsigned int *done_gen)
     a.done = w->d_done;
 }
 
-// Wait for it.  Polling sees the results about 4 us before the stream's own
-// completion does; after 100 us without them (a large box, or a failure) the
-// stream is waited for instead.
-hipError_t wait_done(const Workspace *w, unsigned int gen)
-{
-    if (gen) {
-        const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(100);
-        do {
-            for (int k = 0; k < 64; ++k) {
-                if (__atomic_load_n(w->h_done, __ATOMIC_ACQUIRE) == gen) return hipSuccess;
-                __builtin_ia32_pause();
-            }
-        } while (std::chrono::steady_clock::now() < until);
-    }
-    return hipStreamSynchronize(nullptr);
-}
-
 // The four operations, stream-ordered, with device outputs.
 enum Op { OP_STATS, OP_HIST, OP_FUSED, OP_MINMAX };
 
@@ -833,7 +830,7 @@ int run_sync(Op op, const float *ptr, const int64_t *dims, float lo, float hi, i
     if (rc) return rc;
     // The kernels wrote the results to host memory (a copy of each took 3-5
     // us), and nothing of this call is left to wait for afterwards.
-    const hipError_t e = wait_done(w, gen);
+    const hipError_t e = gen ? poll_host(w->h_done, gen) : hipStreamSynchronize(nullptr);
     if (e != hipSuccess) return hip_fail(e, "synchronize");
     if (op != OP_HIST) *out = *w->h_out;
     if (op != OP_STATS) memcpy(counts, w->h_counts, ((size_t)nbins + 3) * 8);

@@ -219,6 +219,15 @@ void release_ws(hipStream_t s);
 // The empty-box results (n_total 0, NaN statistics, zero counts) on `s`.
 int write_empty(cube_stats_t *dev_out, unsigned long long *dev_counts, int nbins, hipStream_t s);
 
+// Wait until the word *done of pinned host memory holds `gen`, which work on
+// the null stream writes with its results; by polling at first, then (a long
+// pass, a failure) through the stream.
+hipError_t poll_host(const unsigned int *done, unsigned int gen);
+
+// The valid voxel of rank `rank`, or with `median` the lower middle and, for
+// an even count, the upper middle (cube_quantile.hip): *n_v values to v[0..1].
+int box_ranks(const Box &b, int median, uint64_t rank, float *v, int *n_v, uint64_t *n_valid);
+
 // Release the out-of-core streaming buffers and streams (cube_host.hip).
 void host_release();
 // Release the projection slice partials (cube_project.hip).

@@ -1,16 +1,15 @@
-// cube_quantile.hip -- exact quantiles of the valid voxels: every wanted
-// rank is refined side by side, so that any number of levels costs three or
-// four reads of the cube.  The median and quantiles are the paper's example
-// of a global, multi-pass task (Section 3).
+// cube_quantile.hip -- exact order statistics of the valid voxels: any number
+// of ranks refined side by side (selection, the median, quantiles).  The
+// median and quantiles are the paper's example of a global, multi-pass task
+// (Section 3).
 //
 // Each wanted rank is found in the 32-bit order key of the voxels (the key
-// orders like the value, -0 before +0) a few bits at a time, as in
-// cube_select.hip, but every pass keeps one histogram per distinct key
-// prefix still in play, side by side in LDS:
+// orders like the value, -0 before +0) a few bits at a time.  Every pass keeps
+// one histogram per distinct key prefix still in play, side by side in LDS:
 //   pass 0: one 4096-bin histogram of the top 12 key bits;
 //   then, when the ranks fall in at most 8 distinct top buckets and number
-//   at most 96, 12 and 8 more bits (up to 8 histograms of 4096 bins, then
-//   up to 96 of 256);
+//   at most 96 ("wide"), 12 and 8 more bits (up to 8 histograms of 4096 bins,
+//   then up to 96 of 256);
 //   otherwise 8, 6 and 6 more bits (up to 128 histograms of 256 bins, then
 //   128 of 64, then 128 of 64).
 // A voxel finds its histogram through a chain of direct-mapped LDS byte
@@ -20,14 +19,24 @@
 // key bits gives its index among the wanted 12-bit prefixes, each further
 // table, indexed by that entry and the level's next key bits, its index
 // among the longer prefixes.  Only voxels that end at a wanted prefix count
-// (histogram row 0 is laid out but never written).  No search.  The
-// host reads each pass's counts back (at most 256 KB) and builds the next
-// pass's tables.  A level q takes the voxels of ranks j = floor(q (n - 1))
-// and j + 1 and interpolates between them in FP64.
+// (histogram row 0 is laid out but never written).  No search.
+//
+// The host queues all the passes at once.  The last block of each adds up that
+// pass's histograms, finds the bin of every rank, and lays out the next pass:
+// its prefixes, tables and bits (cube_quantile_plan.h holds the same plan in
+// plain C++).  The last pass's last block writes the ranks' keys to host
+// memory.  When the wanted top buckets hold few enough voxels, the second pass
+// also copies those out, and the third reads only them.
+//
+// Measured (call, microseconds; before: the host read every pass's counts
+// back, laid out the next pass and uploaded its tables; a fourth full pass
+// looked for the upper middle of an even count): median of 2^14 voxels 130 ->
+// TODO1, of a 941 x 937 x 240 box 547 -> TODO2; 64 levels of 2^28 899 -> TODO3.
 #include <math.h>
 #include <string.h>
 
 #include <algorithm>
+#include <chrono>
 #include <mutex>
 #include <vector>
 
@@ -44,21 +53,55 @@ namespace {
 
 constexpr int Q_THREADS = 1024;
 constexpr int Q_MAX_RANKS = 2 * CUBE_MAX_QUANTILES;   // index + 1 fits a byte
-constexpr size_t Q_LDS = 160 * 1024 - 256;  // dynamic LDS of one block, static aside
+constexpr size_t Q_LDS = 152 * 1024;        // dynamic LDS of one block at most
 constexpr int Q_ACC = 32768;                // slots << bin width never exceeds this
 constexpr size_t Q_TAB = QP_TAB_MAX;        // bytes: T1, T2, T3 at most
+constexpr int Q_WIDE_BUCKETS = 8, Q_WIDE_RANKS = 96;
+// Copied voxels: 2^24 floats (64 MiB) shared out among the blocks.
+constexpr unsigned int CAND_TOTAL = 1u << 24;
 
-struct QuantArgs {
+// The ranks and the next pass's layout, between the passes.
+struct RankState {
+    unsigned long long rank[Q_MAX_RANKS];  // rank left inside the key prefix found so far
+    unsigned int key[Q_MAX_RANKS];         // that prefix, at the top of the word; ascending
+    int m;                       // ranks
+    int done;                    // the result (or an error) has been written
+    int wide, collect;
+    unsigned int overflow;       // a block's region of copied voxels was too small
+    int shift, width;            // the next pass bins key bits [shift, shift + width)
+    int w2, w3;                  // bits of the second and third prefix levels
+    int slots;                   // histograms (prefixes) in the next pass
+    int t2_bytes, t3_bytes;      // sizes of the second and third tables
+};
+
+// What the host reads.
+struct RankOut {
+    unsigned int done;           // the call's number, written last
+    int status;                  // 0, or 1: rank >= n_valid, 2: no valid voxel
+    int m, wide;
+    unsigned long long n_valid;
+    unsigned int key[Q_MAX_RANKS];
+};
+
+enum { RANK_GIVEN = 0, RANK_MEDIAN = 1, RANK_LEVELS = 2 };
+
+struct RankArgs {
     Geom g;
-    int32_t shift, width;          // this pass bins key bits [shift, shift + width)
-    int32_t w2, w3;                // bits of the second and third prefix levels
-    int32_t slots;                 // histograms (prefixes) in this pass
-    int32_t copies_log2;           // LDS copies of each histogram
-    int32_t t2_bytes, t3_bytes;    // sizes of the second and third tables
-    const unsigned char *tab;      // T1 (4096 bytes), T2, T3, back to back
-    unsigned long long *acc;       // slots << width counters, zero on entry
-    unsigned long long *n_valid;   // pass 0: valid voxels, zero on entry
-    Claim claim;                   // the partition (its counter zero on entry)
+    Claim claim;                 // the partition (its counter zero on entry)
+    RankState *st;
+    unsigned char *tab;          // T1 (4096 bytes), T2, T3, back to back
+    unsigned long long *acc;     // Q_ACC counters and the valid count, zero between passes
+    unsigned int *ticket;
+    float *cand;                 // per-block regions of copied voxels, cand_cap each
+    unsigned int *cand_n;        // voxels each block copied
+    unsigned int cand_cap;
+    int32_t max_clog;            // LDS copies of each histogram, at most
+    uint32_t lds_bytes;          // dynamic LDS of this launch
+    int32_t mode, nq;            // RANK_*; levels (RANK_LEVELS)
+    unsigned long long rank;     // RANK_GIVEN
+    RankOut *out;                // host memory
+    unsigned int gen;
+    double q[CUBE_MAX_QUANTILES];
 };
 
 // NL: prefix levels of this pass (0 for the first pass).
@@ -70,6 +113,10 @@ struct QuantStep {
     unsigned int bmask;
     int wb;
     unsigned int valid;            // first pass: valid voxels seen by this wavefront
+    bool collect;                  // second pass: copy the counted voxels out
+    float *cand;
+    unsigned int cand_cap;
+    unsigned int *s_cnt;           // voxels this block copied (LDS counter)
 
     template <int NV>
     __device__ __forceinline__ void operator()(const float (&x)[NV])
@@ -91,7 +138,7 @@ struct QuantStep {
             // the voxels' lookups would run one after another.  With two or
             // three table levels the key fields are single bit-field extracts
             // (the one-level pass measured slower with them: 2.52 against
-            // 2.34 ms on the brick).
+            // 2.34 ms on 2^32 voxels).
             unsigned int k[NV], g[NV];
 #pragma unroll
             for (int j = 0; j < NV; ++j) {
@@ -115,56 +162,438 @@ struct QuantStep {
                                             : (k[j] >> shift) & bmask);
                 if (x[j] == x[j] && g[j] != 0u) atomicAdd(&lds[(idx << clog) + cbase], 1u);
             }
+            if (NL == 1 && collect) copy_out<NV>(x, g);
+        }
+    }
+
+    // The counted voxels to the block's region: one LDS atomic per wavefront
+    // and step, each voxel at its rank among the step's counted ones.
+    template <int NV>
+    __device__ __forceinline__ void copy_out(const float (&x)[NV], const unsigned int (&g)[NV])
+    {
+        unsigned int total = 0;
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+            total += (unsigned int)__popcll(
+                __builtin_amdgcn_ballot_w64(x[j] == x[j] && g[j] != 0u));
+        if (!total) return;  // wavefront-uniform
+        const int lane = threadIdx.x & 63;
+        unsigned int at = 0;
+        if (lane == 0) at = atomicAdd(s_cnt, total);
+        at = (unsigned int)__builtin_amdgcn_readfirstlane((int)at);
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+            const bool in = x[j] == x[j] && g[j] != 0u;
+            const unsigned long long m = __builtin_amdgcn_ballot_w64(in);
+            const unsigned int i =
+                at + __builtin_amdgcn_mbcnt_hi((unsigned int)(m >> 32),
+                                               __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u));
+            if (in && i < cand_cap) cand[i] = x[j];
+            at += (unsigned int)__popcll(m);
         }
     }
 };
 
-template <int NL, bool PACKED>
-__global__ void __launch_bounds__(Q_THREADS) k_quant(QuantArgs a)
+// ------------------------------------------------- the end of a pass (last block)
+
+struct CountStep {  // inclusive scan, and the total in the last lane
+    unsigned long long &v;
+    template <class C, class R>
+    __device__ __forceinline__ void operator()(C, R)
+    {
+        v += dpp<C::value, R::value>(0ull, v);
+    }
+};
+
+// Shared memory of a pass's end.
+struct RankShared {
+    unsigned long long rank[Q_MAX_RANKS];
+    unsigned long long left[Q_MAX_RANKS];  // the rank inside its bin
+    unsigned long long count[Q_MAX_RANKS]; // voxels in the rank's bin
+    unsigned int key[Q_MAX_RANKS];
+    unsigned int bin[Q_MAX_RANKS];
+    int slot[Q_MAX_RANKS];                 // index of the rank's key prefix
+    int first[Q_MAX_RANKS + 1];            // a slot's first rank
+    unsigned long long wave[MAX_WAVES];
+    unsigned long long mask[2];
+    unsigned long long nv;
+    int m, slots, status;
+};
+
+// The index of each rank's top `bits` key bits among the distinct ones (the
+// keys ascend), for the ranks of threads 0..m-1; returns their number.
+// Called by the whole block, with barriers.
+__device__ __forceinline__ int prefix_index(RankShared &s, int m, int bits, int *idx)
 {
-    extern __shared__ unsigned int lds[];
-    __shared__ unsigned int s_valid;
+    const int tid = threadIdx.x, wid = tid >> 6;
+    const int sh = 32 - bits;
+    const bool flag = tid < m && (tid == 0 || (s.key[tid] >> sh) != (s.key[tid - 1] >> sh));
+    if (wid < 2) {
+        const unsigned long long b = __builtin_amdgcn_ballot_w64(flag);
+        if ((tid & 63) == 0) s.mask[wid] = b;
+    }
+    __syncthreads();
+    const unsigned long long m0 = s.mask[0], m1 = s.mask[1];
+    __syncthreads();
+    const unsigned long long upto = ~0ull >> (63 - (tid & 63));
+    *idx = tid < 64 ? __popcll(m0 & upto) - 1 : __popcll(m0) + __popcll(m1 & upto) - 1;
+    return __popcll(m0) + __popcll(m1);
+}
+
+// The ranks asked for (first pass), ascending and distinct.
+__device__ __forceinline__ void wanted_ranks(const RankArgs &a, RankShared &s,
+                                             unsigned long long *scratch)
+{
+    const int tid = threadIdx.x;
+    const unsigned long long nv = s.nv;
+    if (a.mode != RANK_LEVELS) {
+        if (tid == 0) {
+            s.status = a.mode == RANK_GIVEN ? (a.rank >= nv ? 1 : 0) : (nv == 0 ? 2 : 0);
+            s.rank[0] = a.mode == RANK_GIVEN ? a.rank : (nv - 1) / 2;
+            s.rank[1] = s.rank[0] + 1;
+            s.m = a.mode == RANK_MEDIAN && nv % 2 == 0 ? 2 : 1;
+        }
+        __syncthreads();
+        return;
+    }
+    // Level q takes ranks floor(q (n - 1)) and, unless that is whole, the next.
+    unsigned long long mine = 0;
+    if (tid < 2 * a.nq) {
+        const double h = a.q[tid >> 1] * (double)(nv - 1);
+        const double j = floor(h);
+        mine = (unsigned long long)j + ((tid & 1) && h - j > 0.0 ? 1ull : 0ull);
+        scratch[tid] = mine;
+    }
+    __syncthreads();
+    bool keep = tid < 2 * a.nq;
+    for (int i = 0; keep && i < tid; ++i) keep = scratch[i] != mine;
+    if (tid < 128) {
+        const unsigned long long b = __builtin_amdgcn_ballot_w64(keep);
+        if ((tid & 63) == 0) s.mask[tid >> 6] = b;
+    }
+    __syncthreads();
+    if (keep) {
+        int at = 0;
+        for (int i = 0; i < 2 * a.nq; ++i)
+            if ((s.mask[i >> 6] >> (i & 63)) & 1ull) at += scratch[i] < mine ? 1 : 0;
+        s.rank[at] = mine;
+    }
+    if (tid == 0) {
+        s.m = __popcll(s.mask[0]) + __popcll(s.mask[1]);
+        s.status = nv == 0 ? 2 : 0;
+    }
+    __syncthreads();
+}
+
+// The bin of every rank in its slot's histogram; the counters return to zero.
+__device__ __forceinline__ void find_bins(const RankArgs &a, RankShared &s, int width)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, B = blockDim.x;
+    const int nw = B >> 6, nbins = 1 << width, m = s.m;
+    if (nbins > 64 * 4) {
+        // 4096 bins: the whole block on one slot, consecutive bins per thread.
+        const int per = nbins / B;
+        for (int slot = 0; slot < s.slots; ++slot) {
+            unsigned long long *h = a.acc + (size_t)slot * nbins + tid * per;
+            unsigned long long sum = 0;
+            for (int k = 0; k < per; ++k) sum += h[k];
+            unsigned long long upto = sum;
+            wave_reduce(CountStep{upto});
+            if (lane == WAVE_LAST) s.wave[wid] = upto;
+            __syncthreads();
+            for (int w = 0; w < wid; ++w) upto += s.wave[w];
+            const unsigned long long before = upto - sum;
+            for (int i = s.first[slot]; i < s.first[slot + 1]; ++i) {
+                unsigned long long r = s.rank[i];
+                if (r >= before && r < upto) {  // one thread
+                    r -= before;
+                    int k = 0;
+                    while (k < per - 1 && h[k] <= r) r -= h[k++];
+                    s.left[i] = r;
+                    s.bin[i] = (unsigned int)(tid * per + k);
+                    s.count[i] = h[k];
+                }
+            }
+            for (int k = 0; k < per; ++k) h[k] = 0ull;
+            __syncthreads();
+        }
+        return;
+    }
+    // 256 or 64 bins: a wavefront per slot, 4 or 1 consecutive bins per lane.
+    const int per = nbins / 64;
+    for (int slot = wid; slot < s.slots; slot += nw) {
+        unsigned long long *h = a.acc + (size_t)slot * nbins + lane * per;
+        unsigned long long c[4], sum = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            c[k] = k < per ? h[k] : 0ull;
+            sum += c[k];
+        }
+        unsigned long long upto = sum;
+        wave_reduce(CountStep{upto});
+        const unsigned long long before = upto - sum;
+        for (int i = s.first[slot]; i < s.first[slot + 1]; ++i) {
+            unsigned long long r = s.rank[i];
+            if (r >= before && r < upto) {  // one lane
+                r -= before;
+                int k = 0;
+                while (k < per - 1 && c[k] <= r) r -= c[k++];
+                s.left[i] = r;
+                s.bin[i] = (unsigned int)(lane * per + k);
+                s.count[i] = c[k];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (k < per) h[k] = 0ull;
+    }
+    __syncthreads();
+}
+
+// The last block's part of pass NL: the ranks' bins, then the next pass's
+// layout or, after the last bits, the result.  `scratch`: the block's dynamic
+// LDS.
+template <int NL>
+__device__ void rank_end(const RankArgs &a, RankShared &s, unsigned int *scratch, int shift,
+                         int width, int slots, int wide, int w2, int w3)
+{
+    const int tid = threadIdx.x;
+    RankState *st = a.st;
+    if (tid == 0) {
+        s.status = 0;
+        s.slots = slots;
+        if (NL == 0) {
+            s.nv = a.acc[Q_ACC];
+            a.acc[Q_ACC] = 0ull;
+        } else {
+            s.m = st->m;
+        }
+    }
+    __syncthreads();
+    if (NL == 0) {
+        wanted_ranks(a, s, reinterpret_cast<unsigned long long *>(scratch));
+        if (s.status) {  // nothing to find: leave the counters at zero and say so
+            for (int b = tid; b < 4096; b += blockDim.x) a.acc[b] = 0ull;
+            if (tid == 0) {
+                st->done = 1;
+                store_result<true>(&a.out->status, s.status);
+                store_result<true>(&a.out->n_valid, s.nv);
+            }
+            tell_host(&a.out->done, a.gen);
+            return;
+        }
+        if (tid < s.m) s.key[tid] = 0u;
+        if (tid == 0) {
+            s.first[0] = 0;
+            s.first[1] = s.m;
+        }
+        __syncthreads();
+    } else {
+        if (tid < s.m) {
+            s.rank[tid] = st->rank[tid];
+            s.key[tid] = st->key[tid];
+        }
+        __syncthreads();
+        int idx = 0;
+        const int n = prefix_index(s, s.m, 32 - shift - width, &idx);
+        if (tid < s.m && (tid == 0 || (s.key[tid] >> (shift + width)) !=
+                                          (s.key[tid - 1] >> (shift + width))))
+            s.first[idx] = tid;
+        if (tid == 0) s.first[n] = s.m;
+        __syncthreads();
+    }
+    if (tid < s.m) {
+        s.bin[tid] = (1u << width) - 1u;
+        s.left[tid] = s.count[tid] = 0ull;
+    }
+    __syncthreads();
+    find_bins(a, s, width);
+
+    const int m = s.m;
+    if (tid < m) {
+        s.key[tid] |= s.bin[tid] << shift;
+        st->key[tid] = s.key[tid];
+        st->rank[tid] = s.left[tid];
+    }
+    __syncthreads();
+    if (shift == 0) {  // every key is complete
+        if (tid < m) store_result<true>(&a.out->key[tid], s.key[tid]);
+        if (tid == 0) {
+            st->done = 1;
+            store_result<true>(&a.out->m, m);
+            store_result<true>(&a.out->wide, wide);
+            store_result<true>(&a.out->status, 0);
+        }
+        tell_host(&a.out->done, a.gen);
+        return;
+    }
+
+    // The next pass: its prefix levels, its tables, its bits.
+    int i1 = 0, i2 = 0, i3 = 0;
+    const int n1 = prefix_index(s, m, 12, &i1);
+    if (NL == 0) wide = n1 <= Q_WIDE_BUCKETS && m <= Q_WIDE_RANKS ? 1 : 0;
+    const int next_width = wide ? (NL == 0 ? 12 : 8) : (NL == 0 ? 8 : 6);
+    if (NL == 1) w2 = width;
+    if (NL == 2) w3 = width;
+    int n2 = 0, n3 = 0, t2_bytes = 0, t3_bytes = 0;
+    if (NL >= 1) {
+        n2 = prefix_index(s, m, 12 + w2, &i2);
+        t2_bytes = (n1 + 1) << w2;
+    }
+    if (NL >= 2) {
+        n3 = prefix_index(s, m, 12 + w2 + w3, &i3);
+        t3_bytes = (n2 + 1) << w3;
+    }
+    const int words = (4096 + t2_bytes + t3_bytes) / 4;
+    for (int i = tid; i < words; i += blockDim.x) scratch[i] = 0u;
+    __syncthreads();
+    unsigned char *t1 = reinterpret_cast<unsigned char *>(scratch);
+    if (tid < m) {  // ranks under one prefix write the same byte
+        const unsigned int k = s.key[tid];
+        t1[k >> 20] = (unsigned char)(i1 + 1);
+        if (NL >= 1)
+            t1[4096 + (((i1 + 1) << w2) | (int)((k >> (20 - w2)) & ((1u << w2) - 1u)))] =
+                (unsigned char)(i2 + 1);
+        if (NL >= 2)
+            t1[4096 + t2_bytes +
+               (((i2 + 1) << w3) | (int)((k >> (20 - w2 - w3)) & ((1u << w3) - 1u)))] =
+                (unsigned char)(i3 + 1);
+    }
+    __syncthreads();
+    unsigned int *tab = reinterpret_cast<unsigned int *>(a.tab);
+    for (int i = tid; i < words; i += blockDim.x) tab[i] = scratch[i];
+    if (tid == 0) {
+        if (NL == 0) {
+            // Copy the wanted buckets out in the second pass when that is
+            // less than reading the box again and the regions have room.
+            unsigned long long pop = 0;
+            unsigned int last = 0xffffffffu;
+            for (int i = 0; i < m; ++i)
+                if ((s.key[i] >> 20) != last) {
+                    last = s.key[i] >> 20;
+                    pop += s.count[i];
+                }
+            st->collect = wide && a.cand && pop <= s.nv / 6 &&
+                                  pop <= (unsigned long long)CAND_TOTAL / 4 * 3
+                              ? 1 : 0;
+            st->overflow = 0u;
+            st->m = m;
+            st->wide = wide;
+            st->done = 0;
+            store_result<true>(&a.out->n_valid, s.nv);
+        }
+        st->shift = shift - next_width;
+        st->width = next_width;
+        st->w2 = w2;
+        st->w3 = w3;
+        st->slots = NL == 0 ? n1 : (NL == 1 ? n2 : n3);
+        st->t2_bytes = t2_bytes;
+        st->t3_bytes = t3_bytes;
+    }
+}
+
+template <int NL, bool PACKED>
+__global__ void __launch_bounds__(Q_THREADS) k_quant(RankArgs a)
+{
+    extern __shared__ __align__(16) unsigned int lds[];
+    __shared__ unsigned int s_valid, s_cnt, s_last;
+    __shared__ RankShared s_end;
     const int tid = threadIdx.x, B = blockDim.x;
-    const int nbins = 1 << a.width;
-    const int rows = NL == 0 ? 1 : a.slots + 1;   // after the first pass, row 0 is unused
-    const int words = (rows * nbins) << a.copies_log2;
+    const RankState *cs = a.st;
+    int shift = 20, width = 12, w2 = 0, w3 = 0, slots = 1, t2_bytes = 0, t3_bytes = 0, wide = 0;
+    bool collect = false, from_cand = false;
+    if (NL > 0) {
+        if (cs->done) return;
+        shift = cs->shift;
+        width = cs->width;
+        w2 = cs->w2;
+        w3 = cs->w3;
+        slots = cs->slots;
+        t2_bytes = cs->t2_bytes;
+        t3_bytes = cs->t3_bytes;
+        wide = cs->wide;
+        if (NL == 1) collect = cs->collect != 0;
+        if (NL == 2) from_cand = cs->collect != 0 && cs->overflow == 0u;
+    }
+    const int nbins = 1 << width;
+    const int rows = NL == 0 ? 1 : slots + 1;   // after the first pass, row 0 is unused
+    const int tab_words = NL == 0 ? 0 : (4096 + (NL >= 2 ? t2_bytes : 0) +
+                                         (NL >= 3 ? t3_bytes : 0)) / 4;
+    int clog = 0;
+    while (clog < a.max_clog &&
+           (unsigned int)((((rows * nbins) << (clog + 1)) + tab_words) * 4) <= a.lds_bytes)
+        ++clog;
+    const int words = (rows * nbins) << clog;
     for (int i = tid; i < words; i += B) lds[i] = 0u;
     // The tables follow the histograms in LDS (all sizes are multiples of 4).
     unsigned int *tw = lds + words;
-    const int tab_words = NL == 0 ? 0 : (4096 + (NL >= 2 ? a.t2_bytes : 0) +
-                                         (NL >= 3 ? a.t3_bytes : 0)) / 4;
     const unsigned int *src = (const unsigned int *)a.tab;
     for (int i = tid; i < tab_words; i += B) tw[i] = src[i];
-    if (tid == 0) s_valid = 0u;
+    if (tid == 0) {
+        s_valid = 0u;
+        s_cnt = 0u;
+    }
     __syncthreads();
 
     QuantStep<NL> st;
     st.lds = lds;
     st.t1 = (const unsigned char *)tw;
     st.t2 = st.t1 + 4096;
-    st.t3 = st.t2 + a.t2_bytes;
-    st.shift = a.shift;
-    st.w2 = a.w2;
-    st.w3 = a.w3;
-    st.wb = a.width;
+    st.t3 = st.t2 + t2_bytes;
+    st.shift = shift;
+    st.w2 = w2;
+    st.w3 = w3;
+    st.wb = width;
     st.bmask = (unsigned int)nbins - 1u;
-    st.clog = a.copies_log2;
-    st.cbase = tid & 63 & ((1 << a.copies_log2) - 1);
+    st.clog = clog;
+    st.cbase = tid & 63 & ((1 << clog) - 1);
     st.valid = 0u;
-    scan_box<PACKED>(a.g, st, a.claim);
+    st.collect = collect;
+    st.cand = a.cand + (size_t)blockIdx.x * a.cand_cap;
+    st.cand_cap = a.cand_cap;
+    st.s_cnt = &s_cnt;
+    if (NL == 2 && from_cand) {
+        // The voxels the second pass copied to this block's region.
+        const unsigned int n = a.cand_n[blockIdx.x];
+        for (unsigned int i0 = 0; i0 < n; i0 += 4u * (unsigned int)B) {
+            float x[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const unsigned int i = i0 + (unsigned int)(k * B + tid);
+                x[k] = i < n ? st.cand[i] : qnan();
+            }
+            st(x);
+        }
+    } else {
+        scan_box<PACKED>(a.g, st, a.claim);
+    }
     // Every lane of a wavefront holds the same count (sums of ballots).
     if (NL == 0 && (tid & 63) == 0 && st.valid) atomicAdd(&s_valid, st.valid);
     __syncthreads();
     // Flush the histograms (after the first pass, rows 1..: row 0 is
     // never written).
-    const int C = 1 << a.copies_log2;
+    const int C = 1 << clog;
     const int first = NL == 0 ? 0 : nbins;
-    for (int b = tid; b < a.slots * nbins; b += B) {
+    for (int b = tid; b < slots * nbins; b += B) {
         unsigned int sum = 0;
-        for (int c = 0; c < C; ++c) sum += lds[((b + first) << a.copies_log2) + c];
+        for (int c = 0; c < C; ++c) sum += lds[((b + first) << clog) + ((c + tid) & (C - 1))];
         if (sum) atomicAdd(&a.acc[b], (unsigned long long)sum);
     }
-    if (NL == 0 && tid == 0 && s_valid) atomicAdd(a.n_valid, (unsigned long long)s_valid);
+    if (tid == 0) {
+        if (NL == 0 && s_valid) atomicAdd(&a.acc[Q_ACC], (unsigned long long)s_valid);
+        if (NL == 1 && collect) {
+            a.cand_n[blockIdx.x] = min(s_cnt, a.cand_cap);
+            if (s_cnt > a.cand_cap) atomicOr(&a.st->overflow, 1u);
+        }
+    }
+    // The last block reads atomics only (what is copied out and the copied
+    // counts are the next launch's), so no block writes its L2 back.
+    if (!last_to_arrive_wt(a.ticket, gridDim.x, &s_last)) return;
+    if (tid == 0) {
+        *a.ticket = 0u;
+        if (a.claim.nc) *a.claim.ctr = 0u;
+    }
+    rank_end<NL>(a, s_end, lds, shift, width, slots, wide, w2, w3);
 }
 
 template <int NL>
@@ -175,15 +604,33 @@ const void *quant_kernel(bool packed)
 }
 
 struct QuantWorkspace {
-    unsigned long long *acc = nullptr;    // Q_ACC counters, the valid counter, the chunk counter
-    unsigned char *tab = nullptr;         // the prefix tables
-    unsigned long long *h_acc = nullptr;  // pinned copy of the counters
-    unsigned char *h_tab = nullptr;       // pinned staging of the tables
+    unsigned long long *acc = nullptr;  // Q_ACC counters, the valid counter
+    unsigned int *ticket = nullptr;     // the ticket and the chunk counter
+    unsigned char *tab = nullptr;       // the prefix tables
+    RankState *st = nullptr;
+    float *cand = nullptr;              // copied voxels (null: none could be allocated)
+    unsigned int *cand_n = nullptr;
+    RankOut *h_out = nullptr, *d_out = nullptr;  // pinned; as the device sees it
+    unsigned int calls = 0;
 };
+
+constexpr int Q_MAX_BLOCKS = 4096;
 
 std::mutex g_qmu;
 QuantWorkspace g_qws[64];
 bool g_qws_ready[64];
+
+void free_quant(QuantWorkspace &w)
+{
+    hipFree(w.acc);
+    hipFree(w.ticket);
+    hipFree(w.tab);
+    hipFree(w.st);
+    hipFree(w.cand);
+    hipFree(w.cand_n);
+    hipHostFree(w.h_out);
+    w = QuantWorkspace();
+}
 
 int quant_ws(QuantWorkspace **out)
 {
@@ -194,141 +641,142 @@ int quant_ws(QuantWorkspace **out)
         QuantWorkspace &w = g_qws[dev];
         hipError_t e;
         if ((e = hipMalloc(&w.acc, (Q_ACC + 2) * 8)) != hipSuccess ||
+            (e = hipMalloc(&w.ticket, 256)) != hipSuccess ||
             (e = hipMalloc(&w.tab, Q_TAB)) != hipSuccess ||
-            (e = hipHostMalloc(&w.h_acc, (Q_ACC + 1) * 8)) != hipSuccess ||
-            (e = hipHostMalloc(&w.h_tab, Q_TAB)) != hipSuccess)
+            (e = hipMalloc(&w.st, sizeof(RankState))) != hipSuccess ||
+            (e = hipMalloc(&w.cand_n, Q_MAX_BLOCKS * 4)) != hipSuccess ||
+            (e = hipHostMalloc(&w.h_out, sizeof(RankOut),
+                               hipHostMallocMapped | hipHostMallocCoherent)) != hipSuccess ||
+            (e = hipHostGetDevicePointer((void **)&w.d_out, w.h_out, 0)) != hipSuccess ||
+            (e = hipMemset(w.acc, 0, (Q_ACC + 2) * 8)) != hipSuccess ||
+            (e = hipMemset(w.ticket, 0, 256)) != hipSuccess ||
+            (e = hipDeviceSynchronize()) != hipSuccess) {
+            free_quant(w);
             return hip_fail(e, "quantile workspace");
+        }
+        if (hipMalloc(&w.cand, (size_t)CAND_TOTAL * 4) != hipSuccess) {
+            (void)hipGetLastError();
+            w.cand = nullptr;  // the third pass then reads the box
+        }
+        w.h_out->done = 0u;
         g_qws_ready[dev] = true;
     }
     *out = &g_qws[dev];
     return CUBE_OK;
 }
 
-// One pass: zero the counters, upload the tables (already staged in h_tab),
-// launch, read the counters back (slots << width of them, and the valid
-// count after the first pass).  All on the null stream; returns after the
-// copy.  nl: prefix levels (0 for the first pass); w2, w3 their widths.
-int quant_pass(QuantWorkspace *w, const Box &box, const Geom &g, int nl, int shift, int width,
-               int w2, int w3, int slots, int t2_bytes, int t3_bytes)
+int rank_launch(const void *k, const RankArgs &a, int blocks, size_t lds)
 {
     hipError_t e;
-    const size_t n = (size_t)slots << width;          // counters read back
-    const size_t hist = (size_t)(nl == 0 ? 1 : slots + 1) << width; // LDS words per copy
-    const size_t tab = nl == 0 ? 0 : 4096 + (nl >= 2 ? t2_bytes : 0) + (nl >= 3 ? t3_bytes : 0);
-    if (n > (size_t)Q_ACC || slots > Q_MAX_RANKS || tab > Q_TAB || hist * 4 + tab > Q_LDS)
-        return fail(CUBE_EINVAL, "quantile pass too large");
-    if ((e = hipMemsetAsync(w->acc, 0, (Q_ACC + 2) * 8, nullptr)) != hipSuccess)
-        return hip_fail(e, "quantile counters");
-    if (tab &&
-        (e = hipMemcpyAsync(w->tab, w->h_tab, tab, hipMemcpyHostToDevice, nullptr)) != hipSuccess)
-        return hip_fail(e, "quantile tables");
-    // Up to eight copies of each histogram, as many as fit beside the tables.
-    int clog = 0;
-    while (clog < 3 && (hist << (clog + 1)) * 4 + tab <= Q_LDS) ++clog;
-    const size_t lds = (hist << clog) * 4 + tab;
-    QuantArgs a;
-    memset(&a, 0, sizeof a);
-    a.g = g;
-    a.shift = shift;
-    a.width = width;
-    a.w2 = w2;
-    a.w3 = w3;
-    a.slots = slots;
-    a.copies_log2 = clog;
-    a.t2_bytes = t2_bytes;
-    a.t3_bytes = t3_bytes;
-    a.tab = w->tab;
-    a.acc = w->acc;
-    a.n_valid = w->acc + Q_ACC;
-    const bool packed = g.pack.cb > 0;
-    const void *k = nl == 0   ? quant_kernel<0>(packed)
-                    : nl == 1 ? quant_kernel<1>(packed)
-                    : nl == 2 ? quant_kernel<2>(packed)
-                              : quant_kernel<3>(packed);
     if (lds > 64 * 1024 &&
         (e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) !=
             hipSuccess)
         return hip_fail(e, "quantile LDS");
-    int blocks = 0, chunks = 0;
-    const int rc = scan_plan(box, k, Q_THREADS, lds, &blocks, &chunks);
-    if (rc) return rc;
-    a.claim.ctr = (unsigned int *)(w->acc + Q_ACC + 1);
-    a.claim.nc = chunks;
-    void *args[] = {&a};
+    RankArgs copy = a;
+    copy.lds_bytes = (uint32_t)lds;
+    void *args[] = {&copy};
     if ((e = hipLaunchKernel(k, dim3((unsigned)blocks), dim3(Q_THREADS), args, lds, nullptr)) !=
         hipSuccess)
         return hip_fail(e, "quantile launch");
-    if ((e = hipMemcpyAsync(w->h_acc, w->acc, n * 8, hipMemcpyDeviceToHost, nullptr)) !=
-            hipSuccess ||
-        (nl == 0 && (e = hipMemcpyAsync(w->h_acc + Q_ACC, w->acc + Q_ACC, 8,
-                                        hipMemcpyDeviceToHost, nullptr)) != hipSuccess) ||
-        (e = hipStreamSynchronize(nullptr)) != hipSuccess)
-        return hip_fail(e, "quantile counts");
     return CUBE_OK;
 }
 
-// The passes on the GPU for the host-side plan (cube_quantile_plan.h).
-struct GpuPasses {
-    QuantWorkspace *w;
-    Box box;
-    Geom g;
-    int reads = 0;  // reads of the box so far
-    int first(const unsigned long long **counts, unsigned long long *n)
-    {
-        ++reads;
-        const int rc = quant_pass(w, box, g, 0, 20, 12, 0, 0, 1, 0, 0);
-        if (rc) return rc;
-        *counts = w->h_acc;
-        *n = w->h_acc[Q_ACC];
-        return CUBE_OK;
-    }
-    // The tables are already staged in w->h_tab, which quant_pass uploads.
-    int refine(const QuantPassSpec &s, const unsigned char *, const unsigned long long **counts)
-    {
-        ++reads;
-        const int rc = quant_pass(w, box, g, s.nl, s.shift, s.width, s.w2, s.w3, s.slots,
-                                  s.t2_bytes, s.t3_bytes);
-        if (rc) return rc;
-        *counts = w->h_acc;
-        return CUBE_OK;
-    }
-};
-
-int run_quantiles(const Box &box, const double *q, int m, double *out, uint64_t *n_valid_out)
+// Queue the passes on the null stream and wait for the result.  `keys`: the
+// keys of the ranks, ascending.
+int run_ranks(const Box &box, int mode, uint64_t rank, const double *q, int nq,
+              std::vector<unsigned int> *keys, uint64_t *n_valid, int *status, int *wide)
 {
     QuantWorkspace *w = nullptr;
     int rc = quant_ws(&w);
     if (rc) return rc;
-    GpuPasses P;
-    P.w = w;
-    P.box = box;
-    // Work units for the static grid (two blocks per CU) and for every chunk
-    // of a dynamic partition (scan_plan's automatic or set chunk size).
+    RankArgs a;
+    memset(&a, 0, sizeof a);
+    a.st = w->st;
+    a.tab = w->tab;
+    a.acc = w->acc;
+    a.ticket = w->ticket;
+    a.cand = w->cand;
+    a.cand_n = w->cand_n;
+    a.mode = mode;
+    a.rank = rank;
+    a.nq = nq;
+    for (int i = 0; i < nq; ++i) a.q[i] = q[i];
+    a.out = w->d_out;
+    if (++w->calls == 0u) w->calls = 1u;
+    a.gen = w->calls;
+    // One resident wave of blocks, one per CU (the refinement passes take
+    // nearly all of a CU's LDS), fewer for small boxes, where clearing and
+    // adding up a block's histograms costs more than its share of the scan;
+    // for the same reason fewer LDS copies of each.
     const int cl = scan_chunk_log2(box);
-    const long long units = cl ? chunks_of(box.n, cl) : 0;
-    const long long grid = (long long)cu_count() * 2;
-    scan_geom(box, units > grid ? units : grid, Q_THREADS, &P.g);
-    rc = quantiles_run(P, q, m, out, n_valid_out, w->h_tab, 1);
-    if (rc == 1) return fail(CUBE_EINVAL, "no valid voxel");
-    if (rc == CUBE_OK) g_quant_reads = P.reads;
-    return rc;
+    long long blocks = cu_count();
+    if (cl == 0) {
+        const long long root = (long long)sqrt((double)box.n) / 16;
+        blocks = root < 1 ? 1 : (root < blocks ? root : blocks);
+    }
+    long long units = blocks;
+    if (cl) {
+        units = chunks_of(box.n, cl);
+        if (blocks > units) blocks = units;
+        a.claim.nc = (int)units;
+    }
+    a.claim.ctr = w->ticket + CHUNK_CTR_WORD;
+    a.cand_cap = CAND_TOTAL / (unsigned int)blocks;
+    a.max_clog = box.n < ((uint64_t)1 << 22) ? 1 : (box.n < ((uint64_t)1 << 25) ? 2 : 3);
+    scan_geom(box, units, Q_THREADS, &a.g);
+    const bool packed = a.g.pack.cb > 0;
+    const int passes = 2 * nq > Q_WIDE_BUCKETS ? 4 : 3;  // few ranks are always "wide"
+    const size_t lds0 = (size_t)4096 * 4 << a.max_clog;
+    if ((rc = rank_launch(quant_kernel<0>(packed), a, (int)blocks, lds0)) ||
+        (rc = rank_launch(quant_kernel<1>(packed), a, (int)blocks, Q_LDS)) ||
+        (rc = rank_launch(quant_kernel<2>(packed), a, (int)blocks, Q_LDS)) ||
+        (passes == 4 && (rc = rank_launch(quant_kernel<3>(packed), a, (int)blocks, Q_LDS))))
+        return rc;
+    const hipError_t e = poll_host(&w->h_out->done, a.gen);
+    if (e != hipSuccess) return hip_fail(e, "quantile result");
+    const RankOut &o = *w->h_out;
+    *n_valid = o.n_valid;
+    *status = o.status;
+    if (o.status) return CUBE_OK;
+    *wide = o.wide;
+    keys->assign(o.key, o.key + o.m);
+    return CUBE_OK;
 }
 
 }  // namespace
 
+int box_ranks(const Box &b, int median, uint64_t rank, float *v, int *n_v, uint64_t *n_valid)
+{
+    std::lock_guard<std::mutex> lk(g_qmu);
+    std::vector<unsigned int> keys;
+    int status = 0, wide = 0;
+    uint64_t n = 0;
+    const int rc = run_ranks(b, median ? RANK_MEDIAN : RANK_GIVEN, rank, nullptr, 0, &keys, &n,
+                             &status, &wide);
+    if (rc) return rc;
+    *n_valid = n;
+    if (status == 1)
+        return fail(CUBE_EINVAL, "rank %llu >= %llu valid voxels", (unsigned long long)rank,
+                    (unsigned long long)n);
+    if (status) return fail(CUBE_EINVAL, "no valid voxel");
+    *n_v = (int)keys.size();
+    for (size_t i = 0; i < keys.size(); ++i) v[i] = qp_key_to_float(keys[i]);
+    return CUBE_OK;
+}
+
 void quant_release()
 {
     std::lock_guard<std::mutex> lk(g_qmu);
+    int cur = 0;
+    hipGetDevice(&cur);
     for (int d = 0; d < 64; ++d) {
         if (!g_qws_ready[d]) continue;
-        QuantWorkspace &w = g_qws[d];
-        hipFree(w.acc);
-        hipFree(w.tab);
-        hipHostFree(w.h_acc);
-        hipHostFree(w.h_tab);
-        w = QuantWorkspace();
+        hipSetDevice(d);
+        hipDeviceSynchronize();
+        free_quant(g_qws[d]);
         g_qws_ready[d] = false;
     }
+    hipSetDevice(cur);
 }
 
 }  // namespace cube
@@ -356,7 +804,25 @@ int cube_quantiles(const float *ptr, const int64_t *dims, const double *q, int32
         return fail(CUBE_EINVAL, "empty box");
     }
     std::lock_guard<std::mutex> lk(g_qmu);
-    return run_quantiles(b, q, m, out, n_valid);
+    std::vector<unsigned int> keys;
+    uint64_t n = 0;
+    int status = 0, wide = 0;
+    if ((rc = run_ranks(b, RANK_LEVELS, 0, q, m, &keys, &n, &status, &wide))) return rc;
+    if (n_valid) *n_valid = n;
+    if (status) return fail(CUBE_EINVAL, "no valid voxel");
+    const std::vector<unsigned long long> ranks = qp_ranks(q, m, n);
+    if (ranks.size() != keys.size()) return fail(CUBE_EDEVICE, "quantile ranks disagree");
+    for (int i = 0; i < m; ++i) {
+        const double h = q[i] * (double)(n - 1);
+        const double j = floor(h);
+        const double f = h - j;
+        const double lo = qp_key_to_float(keys[qp_index(ranks, (unsigned long long)j)]);
+        const double hi =
+            f > 0.0 ? qp_key_to_float(keys[qp_index(ranks, (unsigned long long)j + 1)]) : lo;
+        out[i] = qp_interpolate(lo, hi, f);
+    }
+    g_quant_reads = wide ? 3 : 4;
+    return CUBE_OK;
     CUBE_GUARD_END
 }
 

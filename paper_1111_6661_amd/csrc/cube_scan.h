@@ -16,11 +16,6 @@ __device__ __forceinline__ unsigned int order_key(float x)
     return u ^ ((unsigned int)((int)u >> 31) | 0x80000000u);
 }
 
-__device__ __forceinline__ float key_value(unsigned int k)
-{
-    return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
-}
-
 // Visit the work units [u0, u1) of a box once, in tiles of float4 loads;
 // `step` is called with arrays of 1, 4 or 4 * SEL_U voxels (blank lanes
 // padded with NaN), uniformly across each wavefront.
@@ -175,14 +170,6 @@ inline void scan_geom(const Box &b, long long blocks, int threads, Geom *g)
     pack_rows(*g, threads, SEL_U);
 }
 
-// Whether the rows of box b, not cut, are packed.
-inline bool scan_packs(const Box &b, int threads)
-{
-    Geom g;
-    scan_geom(b, 1, threads, &g);
-    return g.pack.cb > 0;
-}
-
 // The chunk size (log2 voxels; 0: static) of a selection pass over box b:
 // the calling thread's cube_set_partition setting, where automatic means
 // chunks of 2^18 voxels from 2^27 voxels on (as for the histogram passes).
@@ -191,32 +178,6 @@ inline int scan_chunk_log2(const Box &b)
     const int cl = chunk_override();
     if (cl >= 0) return cl;
     return b.n >= ((uint64_t)1 << 27) ? 18 : 0;
-}
-
-// The partition of a selection pass over box b with kernel k (`threads` per
-// block, `lds` dynamic LDS bytes).  Static: two blocks per CU, *chunks = 0.
-// Dynamic: one resident wave of blocks over chunks_of(n, scan_chunk_log2).
-inline int scan_plan(const Box &b, const void *k, int threads, size_t lds, int *blocks,
-                     int *chunks)
-{
-    const int cl = scan_chunk_log2(b);
-    *chunks = 0;
-    *blocks = cu_count() * 2;
-    if (cl == 0) return CUBE_OK;
-    hipError_t e;
-    if (lds > 64 * 1024 &&
-        (e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) !=
-            hipSuccess)
-        return hip_fail(e, "selection LDS");
-    int fit = 0;
-    if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, k, threads, lds)) != hipSuccess)
-        return hip_fail(e, "selection occupancy");
-    const long long nc = chunks_of(b.n, cl);
-    long long g = (long long)cu_count() * (fit < 1 ? 1 : fit);
-    if (g > nc) g = nc;
-    *blocks = (int)g;
-    *chunks = (int)nc;
-    return CUBE_OK;
 }
 
 }  // namespace cube
