@@ -281,10 +281,10 @@ CUBE_API int cube_describe_plan(const float *ptr, const int64_t *dims, int32_t k
  * n_valid (and n_valid in *n_valid when not NULL); CUBE_EINVAL when no voxel
  * is valid.  Three histogram passes over 32-bit order keys (12 + 12 + 8
  * bits), with the bucket choice made on the device; the second pass copies
- * the first pass's bucket out when it fits (64 MiB of device memory kept by
- * the library), and the third then reads only that; for an even count the
- * upper middle comes from the same passes or from at most one more
- * (minimum) pass.  Synchronous, on the default stream; results are exact.
+ * the wanted buckets' voxels out when they fit (64 MiB of device memory kept
+ * by the library until cube_shutdown), and the third then reads only those;
+ * for an even count both middles come from the same passes.  Synchronous, on
+ * the default stream; results are exact.
  */
 CUBE_API int cube_select(const float *ptr, const int64_t *dims, uint64_t rank, float *value);
 CUBE_API int cube_median(const float *ptr, const int64_t *dims, double *median,
@@ -304,8 +304,9 @@ CUBE_API int cube_median(const float *ptr, const int64_t *dims, double *median,
  * Results go to out[0..m-1] (host), the valid count to *n_valid (host; may
  * be NULL).  Three reads of the box when the ranks wanted (two per level at
  * most) fall in at most eight distinct leading 12-bit key buckets and number
- * at most 96, four otherwise; synchronous on the null stream.  Keeps about 300 KB of device and
- * pinned host memory per device until cube_shutdown.  Errors: CUBE_EINVAL
+ * at most 96 (the third of a copy of the wanted buckets, when it fits), four
+ * otherwise; synchronous on the null stream.  Shares the memory that
+ * cube_select keeps.  Errors: CUBE_EINVAL
  * for the box errors of the other calls, an empty box, no valid voxel (with
  * *n_valid = 0), NULL q or out, m outside its range or a level outside
  * [0, 1] (NaN included); CUBE_EDEVICE for a HIP error.

@@ -30,8 +30,9 @@
 //
 // Measured (call, microseconds; before: the host read every pass's counts
 // back, laid out the next pass and uploaded its tables; a fourth full pass
-// looked for the upper middle of an even count): median of 2^14 voxels 130 ->
-// TODO1, of a 941 x 937 x 240 box 547 -> TODO2; 64 levels of 2^28 899 -> TODO3.
+// looked for the upper middle of an even count): median of 2^17 voxels 133 ->
+// 42, of 2^28 611 -> 370, of a 941 x 937 x 240 box 547 -> 362; 64 levels of
+// 2^20 302 -> 85, of 2^28 910 -> 737 (four reads at 5.9 TB/s).
 #include <math.h>
 #include <string.h>
 
@@ -256,28 +257,38 @@ __device__ __forceinline__ void wanted_ranks(const RankArgs &a, RankShared &s,
         __syncthreads();
         return;
     }
-    // Level q takes ranks floor(q (n - 1)) and, unless that is whole, the next.
-    unsigned long long mine = 0;
-    if (tid < 2 * a.nq) {
+    // Level q takes ranks floor(q (n - 1)) and, unless that is whole, the
+    // next.  Sorted and made distinct by counting: of B threads, 8 (or 4, 2)
+    // share a rank's comparisons.
+    const int n = 2 * a.nq, B = blockDim.x;
+    unsigned int *dup = reinterpret_cast<unsigned int *>(scratch + Q_MAX_RANKS);
+    unsigned int *below = dup + Q_MAX_RANKS;
+    if (tid < n) {
         const double h = a.q[tid >> 1] * (double)(nv - 1);
         const double j = floor(h);
-        mine = (unsigned long long)j + ((tid & 1) && h - j > 0.0 ? 1ull : 0ull);
-        scratch[tid] = mine;
+        scratch[tid] = (unsigned long long)j + ((tid & 1) && h - j > 0.0 ? 1ull : 0ull);
+        dup[tid] = below[tid] = 0u;
     }
     __syncthreads();
-    bool keep = tid < 2 * a.nq;
-    for (int i = 0; keep && i < tid; ++i) keep = scratch[i] != mine;
+    const int share = B / Q_MAX_RANKS, i = tid / share, part = tid % share;
+    const unsigned long long mine = i < n ? scratch[i] : 0ull;
+    if (i < n) {
+        unsigned int same = 0u;
+        for (int k = part; k < i; k += share) same |= scratch[k] == mine ? 1u : 0u;
+        if (same) atomicOr(&dup[i], 1u);
+    }
+    __syncthreads();
+    if (i < n && !dup[i]) {
+        unsigned int less = 0u;
+        for (int k = part; k < n; k += share) less += !dup[k] && scratch[k] < mine ? 1u : 0u;
+        if (less) atomicAdd(&below[i], less);
+    }
     if (tid < 128) {
-        const unsigned long long b = __builtin_amdgcn_ballot_w64(keep);
-        if ((tid & 63) == 0) s.mask[tid >> 6] = b;
+        const unsigned long long m = __builtin_amdgcn_ballot_w64(tid < n && !dup[tid]);
+        if ((tid & 63) == 0) s.mask[tid >> 6] = m;
     }
     __syncthreads();
-    if (keep) {
-        int at = 0;
-        for (int i = 0; i < 2 * a.nq; ++i)
-            if ((s.mask[i >> 6] >> (i & 63)) & 1ull) at += scratch[i] < mine ? 1 : 0;
-        s.rank[at] = mine;
-    }
+    if (tid < n && !dup[tid]) s.rank[below[tid]] = scratch[tid];
     if (tid == 0) {
         s.m = __popcll(s.mask[0]) + __popcll(s.mask[1]);
         s.status = nv == 0 ? 2 : 0;
@@ -286,37 +297,48 @@ __device__ __forceinline__ void wanted_ranks(const RankArgs &a, RankShared &s,
 }
 
 // The bin of every rank in its slot's histogram; the counters return to zero.
-__device__ __forceinline__ void find_bins(const RankArgs &a, RankShared &s, int width)
+// `sums`: blockDim.x words of LDS.
+__device__ __forceinline__ void find_bins(const RankArgs &a, RankShared &s, int width,
+                                          unsigned long long *sums)
 {
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, B = blockDim.x;
     const int nw = B >> 6, nbins = 1 << width, m = s.m;
     if (nbins > 64 * 4) {
-        // 4096 bins: the whole block on one slot, consecutive bins per thread.
+        // 4096 bins: the whole block on one slot, consecutive bins per thread;
+        // the threads' inclusive sums go to LDS, where each rank searches.
         const int per = nbins / B;
         for (int slot = 0; slot < s.slots; ++slot) {
-            unsigned long long *h = a.acc + (size_t)slot * nbins + tid * per;
+            unsigned long long *h = a.acc + (size_t)slot * nbins;
             unsigned long long sum = 0;
-            for (int k = 0; k < per; ++k) sum += h[k];
+            for (int k = 0; k < per; ++k) sum += h[tid * per + k];
             unsigned long long upto = sum;
             wave_reduce(CountStep{upto});
             if (lane == WAVE_LAST) s.wave[wid] = upto;
             __syncthreads();
             for (int w = 0; w < wid; ++w) upto += s.wave[w];
-            const unsigned long long before = upto - sum;
-            for (int i = s.first[slot]; i < s.first[slot + 1]; ++i) {
-                unsigned long long r = s.rank[i];
-                if (r >= before && r < upto) {  // one thread
-                    r -= before;
-                    int k = 0;
-                    while (k < per - 1 && h[k] <= r) r -= h[k++];
-                    s.left[i] = r;
-                    s.bin[i] = (unsigned int)(tid * per + k);
-                    s.count[i] = h[k];
-                }
-            }
-            for (int k = 0; k < per; ++k) h[k] = 0ull;
+            sums[tid] = upto;
             __syncthreads();
+            const int i = s.first[slot] + tid;
+            if (i < s.first[slot + 1]) {
+                unsigned long long r = s.rank[i];
+                int lo = 0, hi = B - 1;  // the first thread whose sum passes r
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (sums[mid] > r) hi = mid;
+                    else lo = mid + 1;
+                }
+                if (lo > 0) r -= sums[lo - 1];
+                const unsigned long long *c = h + lo * per;
+                int k = 0;
+                while (k < per - 1 && c[k] <= r) r -= c[k++];
+                s.left[i] = r;
+                s.bin[i] = (unsigned int)(lo * per + k);
+                s.count[i] = c[k];
+            }
+            __syncthreads();
+            for (int k = 0; k < per; ++k) h[tid * per + k] = 0ull;
         }
+        __syncthreads();
         return;
     }
     // 256 or 64 bins: a wavefront per slot, 4 or 1 consecutive bins per lane.
@@ -407,7 +429,7 @@ __device__ void rank_end(const RankArgs &a, RankShared &s, unsigned int *scratch
         s.left[tid] = s.count[tid] = 0ull;
     }
     __syncthreads();
-    find_bins(a, s, width);
+    find_bins(a, s, width, reinterpret_cast<unsigned long long *>(scratch));
 
     const int m = s.m;
     if (tid < m) {
@@ -460,19 +482,21 @@ __device__ void rank_end(const RankArgs &a, RankShared &s, unsigned int *scratch
                 (unsigned char)(i3 + 1);
     }
     __syncthreads();
+    if (NL == 0 && tid < 128) {  // the voxels in the wanted buckets
+        unsigned long long pop =
+            tid < m && (tid == 0 || (s.key[tid] >> 20) != (s.key[tid - 1] >> 20)) ? s.count[tid]
+                                                                                 : 0ull;
+        wave_reduce(CountStep{pop});
+        if ((tid & 63) == WAVE_LAST) s.wave[tid >> 6] = pop;
+    }
+    __syncthreads();
     unsigned int *tab = reinterpret_cast<unsigned int *>(a.tab);
     for (int i = tid; i < words; i += blockDim.x) tab[i] = scratch[i];
     if (tid == 0) {
         if (NL == 0) {
             // Copy the wanted buckets out in the second pass when that is
             // less than reading the box again and the regions have room.
-            unsigned long long pop = 0;
-            unsigned int last = 0xffffffffu;
-            for (int i = 0; i < m; ++i)
-                if ((s.key[i] >> 20) != last) {
-                    last = s.key[i] >> 20;
-                    pop += s.count[i];
-                }
+            const unsigned long long pop = s.wave[0] + s.wave[1];
             st->collect = wide && a.cand && pop <= s.nv / 6 &&
                                   pop <= (unsigned long long)CAND_TOTAL / 4 * 3
                               ? 1 : 0;
