@@ -6,18 +6,21 @@
 // moment-0 map up to the channel width) and the number of valid channels.
 // One streaming read of the cube makes all three.
 //
-// When the rows are contiguous and 16-byte aligned, lanes own quads of pixels
-// numbered over the whole image, Q quads per lane 1 KB apart, so that per
-// channel a wavefront reads Q KB of contiguous memory (k_project_quads).
-// Otherwise each lane owns V adjacent pixels of one row (V = 4 when rows,
-// planes and the base are 16-byte aligned, else 1), four channels in flight
-// (k_project).  Each lane walks the channels of its pixels.  The
-// sums are taken in FP64: on CDNA4 an FP64 add issues at the rate of an FP32
-// add, so this costs no more than compensated FP32 and is exact to about
-// n * 2^-53.  When the image has too few pixels to fill the device the
-// channels are split into slices, each slice writes per-pixel partials, and a
-// second kernel merges them in slice order, so the result never depends on
-// timing.
+// Lanes own quads of pixels numbered over the image row by row (rows that
+// follow each other in memory count as one), Q quads per lane 64 apart, so
+// that per channel a wavefront reads Q KB of the image, contiguous along a
+// row; long runs keep HBM pages open (a probe of 16 GiB: 5.97 TB/s with 1 KB
+// per wavefront and channel, 7.26 with 16 KB).  A quad is one float4 load at
+// any alignment; a row's last quad overlaps the one before it, and only its
+// own pixels are written.  Q * ZU loads are in flight per lane (ZU channels).
+// Each lane walks the channels of its pixels.  The sums are taken in FP64: on
+// CDNA4 an FP64 add issues at the rate of an FP32 add, so this costs no more
+// than compensated FP32 and is exact to about n * 2^-53.  When the image has
+// too few pixels to fill the device the channels are split into slices, each
+// slice writes per-pixel partials, and a second kernel merges them in slice
+// order, so the result never depends on timing.  Images that quads do not fit
+// (rows under four pixels, or pitches beyond 32-bit offsets) take one pixel
+// per lane (k_project).
 #include <string.h>
 
 #include <map>
@@ -32,9 +35,10 @@ namespace {
 
 struct ProjArgs {
     const float *ptr;
-    int64_t nx, ny, nz, sy, sz;
-    int64_t units;           // lanes' work items: pixels (V = 1) or quads (V = 4)
-    int64_t u0;              // k_project: first unit; k_project_quads: units it covers
+    int64_t nx, ny, nz, sy, sz;  // rows that follow each other merged into one
+    int64_t units;           // lanes' work items: quads, or pixels (k_project)
+    int64_t quads_row;       // quads per row
+    int64_t per;             // quads per wavefront
     int64_t zps;             // channels per slice
     int32_t slices;
     float *mip;              // outputs, dense nx * ny (any may be null)
@@ -48,141 +52,171 @@ struct ProjArgs {
 constexpr int PROJ_THREADS = 256;
 constexpr int PROJ_ZU = 4;
 
-template <int V>
-__global__ void __launch_bounds__(PROJ_THREADS) k_project(ProjArgs a)
+struct Pixel {
+    float m;
+    double s;
+    uint32_t n;
+    __device__ __forceinline__ void take(float x)
+    {
+        const bool ok = x == x;
+        m = fmaxf(m, __builtin_canonicalizef(x));  // a (quieted) NaN is skipped
+        s += (double)(ok ? x : 0.f);
+        n += (uint32_t)ok;
+    }
+};
+constexpr Pixel PIXEL_NONE = {-INFINITY, 0.0, 0u};
+
+// Pixel p (of npix) of slice `slice`: the maps, or its partial.
+__device__ __forceinline__ void put_pixel(const ProjArgs &a, int64_t p, int slice, const Pixel &v)
 {
-    const int64_t u = a.u0 + (int64_t)blockIdx.x * PROJ_THREADS + threadIdx.x;
-    if (u >= a.units) return;
-    const int64_t row_units = a.nx / V;
-    const int64_t y = u / row_units;
-    const int64_t x = (u - y * row_units) * V;
-    const int64_t z0 = (int64_t)blockIdx.y * a.zps;
-    const int64_t z1 = min(a.nz, z0 + a.zps);
-    const float *q = a.ptr + y * a.sy + x + z0 * a.sz;
-    float m[V];
-    double s[V];
-    uint32_t n[V];
-#pragma unroll
-    for (int k = 0; k < V; ++k) {
-        m[k] = -INFINITY;
-        s[k] = 0.0;
-        n[k] = 0u;
-    }
-    auto take = [&](const float (&v)[V]) {
-#pragma unroll
-        for (int k = 0; k < V; ++k) {
-            const bool ok = v[k] == v[k];
-            m[k] = ok ? fmaxf(m[k], v[k]) : m[k];
-            s[k] += (double)(ok ? v[k] : 0.f);
-            n[k] += ok ? 1u : 0u;
-        }
-    };
-    auto load = [&](const float *p, float (&v)[V]) {
-        if constexpr (V == 4) {
-            const f4 t = __builtin_nontemporal_load((const f4 *)p);
-            v[0] = t.x;
-            v[1] = t.y;
-            v[2] = t.z;
-            v[3] = t.w;
-        } else {
-            v[0] = __builtin_nontemporal_load(p);
-        }
-    };
-    int64_t z = z0;
-    for (; z + PROJ_ZU <= z1; z += PROJ_ZU) {
-        float v[PROJ_ZU][V];
-#pragma unroll
-        for (int j = 0; j < PROJ_ZU; ++j) load(q + j * a.sz, v[j]);
-#pragma unroll
-        for (int j = 0; j < PROJ_ZU; ++j) take(v[j]);
-        q += PROJ_ZU * a.sz;
-    }
-    for (; z < z1; ++z) {
-        float v[V];
-        load(q, v);
-        take(v);
-        q += a.sz;
-    }
-    const int64_t p = y * a.nx + x;
     if (a.slices == 1) {
-#pragma unroll
-        for (int k = 0; k < V; ++k) {
-            if (a.mip) a.mip[p + k] = n[k] ? m[k] : qnan();
-            if (a.mom0) a.mom0[p + k] = n[k] ? s[k] : (double)qnan();
-            if (a.nvalid) a.nvalid[p + k] = n[k];
-        }
+        if (a.mip) a.mip[p] = v.n ? v.m : qnan();
+        if (a.mom0) a.mom0[p] = v.n ? v.s : (double)qnan();
+        if (a.nvalid) a.nvalid[p] = v.n;
     } else {
-        const int64_t o = (int64_t)blockIdx.y * a.nx * a.ny + p;
-#pragma unroll
-        for (int k = 0; k < V; ++k) {
-            a.p_max[o + k] = m[k];
-            a.p_sum[o + k] = s[k];
-            a.p_cnt[o + k] = n[k];
-        }
+        const int64_t o = (int64_t)slice * a.nx * a.ny + p;
+        a.p_max[o] = v.m;
+        a.p_sum[o] = v.s;
+        a.p_cnt[o] = v.n;
     }
 }
 
-// The fast path for images whose rows are contiguous and 16-byte aligned:
-// pixel quads are numbered over the whole image, and wavefront w owns quads
-// [64 Q w, 64 Q (w + 1)), lane l the quads 64 k + l.  Per channel a wavefront
-// then reads Q runs of 1 KB that together cover 1 KB * Q of contiguous
-// memory, which keeps HBM pages open far better than 1 KB per wavefront.
-template <int Q>
-__global__ void __launch_bounds__(PROJ_THREADS) k_project_quads(ProjArgs a)
+__global__ void __launch_bounds__(PROJ_THREADS) k_project(ProjArgs a)
 {
-    // Launched for whole wavefronts only; the remaining quads go to k_project.
-    const int lane = threadIdx.x & 63;
-    const int64_t wave = ((int64_t)blockIdx.x * PROJ_THREADS + threadIdx.x) >> 6;
-    const int64_t qb = wave * 64 * Q;
-    if (qb + 64 * Q > a.u0) return;
+    const int64_t p = (int64_t)blockIdx.x * PROJ_THREADS + threadIdx.x;
+    if (p >= a.units) return;
+    const int64_t y = p / a.nx;
+    const int64_t x = p - y * a.nx;
     const int64_t z0 = (int64_t)blockIdx.y * a.zps;
     const int64_t z1 = min(a.nz, z0 + a.zps);
-    const int64_t sz4 = a.sz >> 2;
-    const f4 *q = (const f4 *)a.ptr + qb + lane + z0 * sz4;
-    float m[Q][4];
-    double s[Q][4];
-    uint32_t n[Q][4];
+    const float *q = a.ptr + y * a.sy + x + z0 * a.sz;
+    Pixel v = PIXEL_NONE;
+    int64_t z = z0;
+    for (; z + PROJ_ZU <= z1; z += PROJ_ZU) {
+        float t[PROJ_ZU];
 #pragma unroll
-    for (int k = 0; k < Q; ++k)
+        for (int j = 0; j < PROJ_ZU; ++j) t[j] = __builtin_nontemporal_load(q + j * a.sz);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            m[k][j] = -INFINITY;
-            s[k][j] = 0.0;
-            n[k][j] = 0u;
+        for (int j = 0; j < PROJ_ZU; ++j) v.take(t[j]);
+        q += PROJ_ZU * a.sz;
+    }
+    for (; z < z1; ++z) {
+        v.take(__builtin_nontemporal_load(q));
+        q += a.sz;
+    }
+    put_pixel(a, p, (int)blockIdx.y, v);
+}
+
+// Wavefront w owns a.per quads from a.per * w on (the last one the image's last
+// a.per: what it shares with its neighbour both write alike), lane l the quads
+// 64 k + l of them.  All wavefronts have the same work and the same number
+// falls to every CU: with 64 Q quads each, 1057 wavefronts took 537 us where
+// 1024 took 362 (a CU with two blocks sets the end).  Bound by HBM from about
+// 2^26 voxels on.  Measured (async calls) on a 1187 x 911 x 512 cut-out of
+// 2048-wide rows: 490 us with one pixel per lane, 345 with quads; on 300 dense
+// planes of 2035 x 1599: 848 -> 570.
+// ONE_ROW: the image is one row, every quad but the last at its plain place.
+template <int Q, int ZU, bool ONE_ROW>
+__global__ void __launch_bounds__(PROJ_THREADS) k_project_quads(ProjArgs a)
+{
+    // Four neighbouring wavefronts per block: they stay on one CU and read
+    // side by side (blocks of one: 2418 us on 2048 x 2048 x 1024, four: 2380).
+    const int lane = threadIdx.x & 63;
+    const int64_t wave = (int64_t)blockIdx.x * (PROJ_THREADS / 64) +
+                         __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (wave * a.per >= a.units) return;
+    const int64_t qb = min(wave * a.per, a.units - a.per);
+    // The wavefront's first row, and each quad's place from its start.
+    const int64_t y0 = ONE_ROW ? 0 : qb / a.quads_row;
+    const uint32_t c0 = ONE_ROW ? 0u : (uint32_t)(qb - y0 * a.quads_row);
+    const uint32_t row = (uint32_t)min(a.quads_row, (int64_t)0xffffffff);
+    auto place = [&](int k, uint32_t *dy, uint32_t *x, uint32_t *own) {
+        const uint32_t i = (uint32_t)(64 * k + lane), last = (uint32_t)a.per - 1u;
+        const uint32_t c = c0 + min(i, last);
+        if (ONE_ROW) {  // x from quad qb on; the image's last quad ends with it
+            *dy = 0u;
+            *x = (uint32_t)min((int64_t)4 * c, a.nx - 4 - 4 * qb);
+            *own = 4u * c - *x;
+        } else {
+            *dy = c / row;
+            const uint32_t col = c - *dy * row;
+            *x = min(4u * col, (uint32_t)a.nx - 4u);
+            *own = 4u * col - *x;  // the quad's first own pixel
         }
-    for (int64_t z = z0; z < z1; ++z) {
-        f4 v[Q];
+        if (i > last) *own = 4u;
+    };
+    uint32_t off[Q];
+    Pixel v[Q][4];
 #pragma unroll
-        for (int k = 0; k < Q; ++k) v[k] = __builtin_nontemporal_load(q + 64 * k);
+    for (int k = 0; k < Q; ++k) {
+        uint32_t dy, x, own;
+        if (ONE_ROW && k < Q - 1) {
+            off[k] = (uint32_t)(lane * 16 + k * 1024);
+        } else {
+            place(k, &dy, &x, &own);
+            off[k] = (dy * (uint32_t)a.sy + x) * 4u;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[k][j] = PIXEL_NONE;
+    }
+    const int64_t z0 = (int64_t)blockIdx.y * a.zps;
+    const int64_t z1 = min(a.nz, z0 + a.zps);
+    const char *base =
+        (const char *)(a.ptr + (ONE_ROW ? 4 * qb : y0 * a.sy) + z0 * a.sz);
+    const int64_t step = a.sz * 4;
+    auto load = [&](f4 (&t)[Q], const char *b) {
+#pragma unroll
+        for (int k = 0; k < Q; ++k) t[k] = __builtin_nontemporal_load((const f4u *)(b + off[k]));
+    };
+    auto take = [&](const f4 (&t)[Q]) {
 #pragma unroll
         for (int k = 0; k < Q; ++k)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float x = v[k][j];
-                const bool ok = x == x;
-                m[k][j] = ok ? fmaxf(m[k][j], x) : m[k][j];
-                s[k][j] += (double)(ok ? x : 0.f);
-                n[k][j] += ok ? 1u : 0u;
-            }
-        q += sz4;
+            for (int j = 0; j < 4; ++j) v[k][j].take(t[k][j]);
+    };
+    int64_t z = z0;
+    if (ZU > 1)
+        for (; z + ZU <= z1; z += ZU) {
+            f4 t[ZU][Q];
+#pragma unroll
+            for (int u = 0; u < ZU; ++u) load(t[u], base + u * step);
+            // All loads first: the scheduler otherwise takes some of them one
+            // by one to save registers (twice the time with four quads).
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < ZU; ++u) take(t[u]);
+            base += ZU * step;
+        }
+    for (; z < z1; ++z) {
+        f4 t[Q];
+        load(t, base);
+        take(t);
+        base += step;
     }
-    const int64_t o = a.slices == 1 ? 0 : (int64_t)blockIdx.y * a.nx * a.ny;
 #pragma unroll
     for (int k = 0; k < Q; ++k) {
-        const int64_t p = (qb + 64 * k + lane) * 4;
+        uint32_t dy, x, own;
+        place(k, &dy, &x, &own);
+        const int64_t p = (ONE_ROW ? 4 * qb : (y0 + dy) * a.nx) + x;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (a.slices == 1) {
-                if (a.mip) a.mip[p + j] = n[k][j] ? m[k][j] : qnan();
-                if (a.mom0) a.mom0[p + j] = n[k][j] ? s[k][j] : (double)qnan();
-                if (a.nvalid) a.nvalid[p + j] = n[k][j];
-            } else {
-                a.p_max[o + p + j] = m[k][j];
-                a.p_sum[o + p + j] = s[k][j];
-                a.p_cnt[o + p + j] = n[k][j];
-            }
-        }
+        for (int j = 0; j < 4; ++j)
+            if ((uint32_t)j >= own) put_pixel(a, p + j, (int)blockIdx.y, v[k][j]);
     }
+}
+
+template <int Q>
+void launch_quads(const ProjArgs &a, hipStream_t s)
+{
+    // Channels in flight: about 16 loads with few wavefronts per CU; four
+    // with one quad per lane and many (600 x 600 x 256: 72 us, eight: 80).
+    constexpr int ZU = Q >= 9 ? 1 : (Q >= 5 ? 2 : (Q == 2 ? 8 : 4));
+    const int64_t waves = (a.units + a.per - 1) / a.per;
+    const dim3 grid((unsigned)((waves * 64 + PROJ_THREADS - 1) / PROJ_THREADS),
+                    (unsigned)a.slices);
+    if (a.ny == 1)
+        hipLaunchKernelGGL((k_project_quads<Q, ZU, true>), grid, dim3(PROJ_THREADS), 0, s, a);
+    else
+        hipLaunchKernelGGL((k_project_quads<Q, ZU, false>), grid, dim3(PROJ_THREADS), 0, s, a);
 }
 
 // Merge the slice partials of every pixel in slice order.
@@ -321,29 +355,39 @@ int cube_project(const float *ptr, const int64_t *dims, float *mip, double *mom0
         e = hipGetLastError();
         return e == hipSuccess ? CUBE_OK : hip_fail(e, "projection launch");
     }
-    // Quads when every row start is 16-byte aligned; whole-image quads when,
-    // in addition, the rows follow each other in memory.
-    const bool quad = (b.nx % 4 == 0) && ((uintptr_t)b.ptr % 16 == 0) &&
-                      (b.ny == 1 || a.sy % 4 == 0) && (b.nz == 1 || a.sz % 4 == 0);
-    const bool rows = quad && (b.ny == 1 || a.sy == b.nx);
-    const int V = quad ? 4 : 1;
-    a.units = npix / V;
-    // Quads per lane on the fast path: the most that still leaves about four
-    // wavefronts per CU (each holds Q * 16 pixels of state in registers).
-    const int64_t cus = cu_count();
-    int Q = 1;
-    if (rows) {
-        Q = 4;
-        if ((a.units + 64 * 16 - 1) / (64 * 16) >= 4 * cus) Q = 16;
-        else if ((a.units + 64 * 8 - 1) / (64 * 8) >= 4 * cus) Q = 8;
+    // Rows that follow each other are one row.
+    if (a.ny > 1 && a.sy == a.nx) {
+        a.nx = a.sy = npix;
+        a.ny = 1;
     }
-    // Slices of the channel axis until enough wavefronts are busy (16 per CU
-    // on the general path, 4 on the fast path), each slice keeping at least
-    // 64 channels.
-    const int64_t waves = (a.units + 64 * Q - 1) / (64 * Q);
-    const int64_t want = cus * (rows ? 4 : 16);
-    int64_t slices = waves >= want ? 1 : (want + waves - 1) / waves;
-    slices = std::min<int64_t>(slices, std::max<int64_t>(1, b.nz / 64));
+    a.quads_row = (a.nx + 3) / 4;
+    const int64_t quads = a.quads_row * a.ny;
+    // Quads while a wavefront's offsets from its first row fit 32 bits.
+    const bool quad = a.nx >= 4 && a.nx < ((int64_t)1 << 31) &&
+                      (64 * 16 / a.quads_row + 2) < (((int64_t)1 << 30) / (a.sy < 1 ? 1 : a.sy));
+    a.units = quad ? quads : npix;
+    // From 192 K quads on, equal shares for every CU: a multiple of one block
+    // of four wavefronts per CU, as few as up to 16 quads per lane allow (each
+    // holds 16 Q registers of state).  Below, 64 quads per wavefront: with
+    // many wavefronts per CU whole ones read better than equal shares (800 x
+    // 800 x 256 of 2048-wide rows: 2500 wavefronts 152 us, 3072 156).  Small
+    // images: slices of the channel axis until enough wavefronts are busy,
+    // each slice keeping at least 32 channels (256 x 256 x 256 with at least
+    // 64: 60 us, 32: 21).
+    const int64_t cus = cu_count();
+    int64_t waves = (a.units + 63) / 64;
+    if (quad && waves > 12 * cus) {
+        const int64_t most = 4 * cus * 64 * 16;
+        waves = 4 * cus * ((a.units + most - 1) / most);
+        a.per = (a.units + waves - 1) / waves;
+    } else {
+        a.per = std::min<int64_t>(64, a.units);
+    }
+    waves = (a.units + a.per - 1) / a.per;
+    const int Q = (int)((a.per + 63) / 64);
+    const int64_t want = cus * (Q > 1 ? 4 : (quad ? 8 : 16));
+    int64_t slices = waves * 8 >= want * 7 ? 1 : (want + waves - 1) / waves;
+    slices = std::min<int64_t>(slices, std::max<int64_t>(1, b.nz / 32));
     slices = std::min<int64_t>(slices, 64);
     a.zps = (b.nz + slices - 1) / slices;
     a.slices = (int32_t)((b.nz + a.zps - 1) / a.zps);
@@ -355,33 +399,19 @@ int cube_project(const float *ptr, const int64_t *dims, float *mip, double *mom0
         a.p_max = (float *)((char *)scr + per * 8);
         a.p_cnt = (uint32_t *)((char *)scr + per * 12);
     }
-    // Whole wavefronts of the fast path first, then every remaining unit on
-    // the general kernel (all of them when the fast path does not apply).
-    int64_t done = 0;
-    if (rows) {
-        const int64_t full = a.units / (64 * Q);
-        done = full * 64 * Q;
-        if (full) {
-            a.u0 = done;
-            const dim3 grid((unsigned)((full * 64 + PROJ_THREADS - 1) / PROJ_THREADS),
-                            (unsigned)a.slices);
-            if (Q == 16)
-                hipLaunchKernelGGL(k_project_quads<16>, grid, dim3(PROJ_THREADS), 0, s, a);
-            else if (Q == 8)
-                hipLaunchKernelGGL(k_project_quads<8>, grid, dim3(PROJ_THREADS), 0, s, a);
-            else
-                hipLaunchKernelGGL(k_project_quads<4>, grid, dim3(PROJ_THREADS), 0, s, a);
-            if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "projection launch");
-        }
-    }
-    if (done < a.units) {
-        a.u0 = done;
-        const dim3 grid((unsigned)((a.units - done + PROJ_THREADS - 1) / PROJ_THREADS),
-                        (unsigned)a.slices);
-        if (quad)
-            hipLaunchKernelGGL(k_project<4>, grid, dim3(PROJ_THREADS), 0, s, a);
-        else
-            hipLaunchKernelGGL(k_project<1>, grid, dim3(PROJ_THREADS), 0, s, a);
+    if (!quad) {
+        hipLaunchKernelGGL(k_project,
+                           dim3((unsigned)((a.units + PROJ_THREADS - 1) / PROJ_THREADS),
+                                (unsigned)a.slices),
+                           dim3(PROJ_THREADS), 0, s, a);
+    } else {
+        using Launch = void (*)(const ProjArgs &, hipStream_t);
+        static const Launch by_q[16] = {
+            launch_quads<1>,  launch_quads<2>,  launch_quads<3>,  launch_quads<4>,
+            launch_quads<5>,  launch_quads<6>,  launch_quads<7>,  launch_quads<8>,
+            launch_quads<9>,  launch_quads<10>, launch_quads<11>, launch_quads<12>,
+            launch_quads<13>, launch_quads<14>, launch_quads<15>, launch_quads<16>};
+        by_q[Q - 1](a, s);  // Q <= 16
     }
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "projection launch");
     if (a.slices > 1) {
