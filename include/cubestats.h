@@ -279,12 +279,16 @@ CUBE_API int cube_describe_plan(const float *ptr, const int64_t *dims, int32_t k
  * rank >= n_valid.  cube_median stores the median of the valid voxels: the
  * middle one for odd n_valid, the FP64 mean of the two middle ones for even
  * n_valid (and n_valid in *n_valid when not NULL); CUBE_EINVAL when no voxel
- * is valid.  Three histogram passes over 32-bit order keys (12 + 12 + 8
- * bits), with the bucket choice made on the device; the second pass copies
- * the wanted buckets' voxels out when they fit (64 MiB of device memory kept
- * by the library until cube_shutdown), and the third then reads only those;
- * for an even count both middles come from the same passes.  Synchronous, on
- * the default stream; results are exact.
+ * is valid.  A box of 3 * 2^24 voxels or more is read once: a sample gives a
+ * bracket of about 1 % of the box, the read counts what lies below it and
+ * copies it out, and two passes over the copies find the key; if its counts
+ * show that the sample misled, and for smaller boxes, three histogram passes
+ * over 32-bit order keys (12 + 12 + 8 bits), with the bucket choice made on
+ * the device; the second pass copies the wanted buckets' voxels out when they
+ * fit, and the third then reads only those.  The copies take 64 MiB of device
+ * memory kept by the library until cube_shutdown.  For an even count both
+ * middles come from the same passes.  Synchronous, on the default stream;
+ * results are exact.
  */
 CUBE_API int cube_select(const float *ptr, const int64_t *dims, uint64_t rank, float *value);
 CUBE_API int cube_median(const float *ptr, const int64_t *dims, double *median,

@@ -31,7 +31,7 @@
 // Measured (call, microseconds; before: the host read every pass's counts
 // back, laid out the next pass and uploaded its tables; a fourth full pass
 // looked for the upper middle of an even count): median of 2^17 voxels 133 ->
-// 42, of 2^28 611 -> 370, of a 941 x 937 x 240 box 547 -> 362; 64 levels of
+// 42, of 2^24 -> 68 (larger boxes: cube_bracket.h, one read); 64 levels of
 // 2^20 302 -> 85, of 2^28 910 -> 737 (four reads at 5.9 TB/s).
 #include <math.h>
 #include <string.h>
@@ -85,6 +85,8 @@ struct RankOut {
 };
 
 enum { RANK_GIVEN = 0, RANK_MEDIAN = 1, RANK_LEVELS = 2 };
+// Status of the single-read search: go on with the passes over the box.
+constexpr int RANK_MISSED = 3;
 
 struct RankArgs {
     Geom g;
@@ -620,6 +622,14 @@ __global__ void __launch_bounds__(Q_THREADS) k_quant(RankArgs a)
     rank_end<NL>(a, s_end, lds, shift, width, slots, wide, w2, w3);
 }
 
+}  // namespace
+}  // namespace cube
+
+#include "cube_bracket.h"
+
+namespace cube {
+namespace {
+
 template <int NL>
 const void *quant_kernel(bool packed)
 {
@@ -633,12 +643,14 @@ struct QuantWorkspace {
     unsigned char *tab = nullptr;       // the prefix tables
     RankState *st = nullptr;
     float *cand = nullptr;              // copied voxels (null: none could be allocated)
-    unsigned int *cand_n = nullptr;
+    unsigned int *cand_n = nullptr;     // voxels in each block's region, or piece
+    BracketState *br = nullptr;
     RankOut *h_out = nullptr, *d_out = nullptr;  // pinned; as the device sees it
     unsigned int calls = 0;
 };
 
 constexpr int Q_MAX_BLOCKS = 4096;
+constexpr unsigned int BR_PIECES = CAND_TOTAL / BR_PIECE;
 
 std::mutex g_qmu;
 QuantWorkspace g_qws[64];
@@ -652,6 +664,7 @@ void free_quant(QuantWorkspace &w)
     hipFree(w.st);
     hipFree(w.cand);
     hipFree(w.cand_n);
+    hipFree(w.br);
     hipHostFree(w.h_out);
     w = QuantWorkspace();
 }
@@ -668,7 +681,9 @@ int quant_ws(QuantWorkspace **out)
             (e = hipMalloc(&w.ticket, 256)) != hipSuccess ||
             (e = hipMalloc(&w.tab, Q_TAB)) != hipSuccess ||
             (e = hipMalloc(&w.st, sizeof(RankState))) != hipSuccess ||
-            (e = hipMalloc(&w.cand_n, Q_MAX_BLOCKS * 4)) != hipSuccess ||
+            (e = hipMalloc(&w.cand_n, std::max<size_t>(Q_MAX_BLOCKS, BR_PIECES) * 4)) !=
+                hipSuccess ||
+            (e = hipMalloc(&w.br, sizeof(BracketState))) != hipSuccess ||
             (e = hipHostMalloc(&w.h_out, sizeof(RankOut),
                                hipHostMallocMapped | hipHostMallocCoherent)) != hipSuccess ||
             (e = hipHostGetDevicePointer((void **)&w.d_out, w.h_out, 0)) != hipSuccess ||
@@ -702,6 +717,84 @@ int rank_launch(const void *k, const RankArgs &a, int blocks, size_t lds)
     if ((e = hipLaunchKernel(k, dim3((unsigned)blocks), dim3(Q_THREADS), args, lds, nullptr)) !=
         hipSuccess)
         return hip_fail(e, "quantile launch");
+    return CUBE_OK;
+}
+
+// The least box for the single-read search: its five passes cost about 65 us
+// beside the read (median of 2^24 voxels 81 us against the two reads' 68, of
+// 2^25 93 against 92, of 2^26 110 against 134).
+constexpr uint64_t BRACKET_MIN_VOXELS = (uint64_t)3 << 24;
+
+// The voxels to sample for the single-read search of box b; 0: read it twice.
+// 5 sigma either side of a rank is 5 / sqrt(sample) of the box, and the
+// copies have to fit (up to 2^32 voxels they do).  Four times the sample takes
+// 20 us more and leaves half the copies: median of 2^28 voxels 252 us against
+// 257, of 2^30 769 against 817, of 2^26 133 against 110.
+unsigned int sample_of(const Box &b, const QuantWorkspace &w)
+{
+    if (!w.cand || b.n < BRACKET_MIN_VOXELS) return 0u;
+    for (int lg = b.n < ((uint64_t)1 << 29) ? 18 : 20; lg <= 22; lg += 2)
+        if (5.0 * (double)b.n / (double)(1u << (lg / 2)) < 0.65 * CAND_TOTAL) return 1u << lg;
+    return 0u;
+}
+
+// The median or one rank in a single read of the box; status RANK_MISSED if
+// the box has to be read again.
+int run_bracket(const Box &box, unsigned int n_sample, int median, uint64_t rank,
+                QuantWorkspace *w, std::vector<unsigned int> *keys, uint64_t *n_valid, int *status)
+{
+    BracketArgs a;
+    memset(&a, 0, sizeof a);
+    a.st = w->br;
+    a.acc = w->acc;
+    a.totals = w->acc + Q_ACC;
+    a.ticket = w->ticket;
+    a.cand = w->cand;
+    a.piece_n = w->cand_n;
+    a.n_pieces = BR_PIECES;
+    a.n_sample = n_sample;
+    a.stride = (unsigned int)(box.n / n_sample);
+    a.median = median;
+    a.rank = rank;
+    a.out = w->d_out;
+    if (++w->calls == 0u) w->calls = 1u;
+    a.gen = w->calls;
+    const int cl = std::max(chunk_override(), 0);
+    // One block of 16 wavefronts on each CU: every block adds its totals, its
+    // bins and its ticket to the same few words, so with three blocks of 8
+    // the read of 2^23 voxels took 29 us against 19.  Static unless the caller
+    // asked for chunks: a region of 941 x 937 x 240 took 237 us, with 2^18-voxel
+    // chunks 270.
+    long long blocks = cu_count();
+    long long units = blocks;
+    if (cl) {
+        units = chunks_of(box.n, cl);
+        if (blocks > units) blocks = units;
+        a.claim.nc = (int)units;
+    }
+    a.claim.ctr = w->ticket + CHUNK_CTR_WORD;
+    a.waves = (unsigned int)blocks * (BR_READ_THREADS / 64);
+    scan_geom(box, units, BR_READ_THREADS, &a.g);
+    const void *read = a.g.pack.cb > 0
+                           ? reinterpret_cast<const void *>(&k_bracket<BR_BOX, true>)
+                           : reinterpret_cast<const void *>(&k_bracket<BR_BOX, false>);
+    const struct { const void *k; long long blocks; int threads; } passes[] = {
+        {reinterpret_cast<const void *>(&k_bracket<BR_SAMPLE, false>), BR_SAMPLE_BLOCKS, BR_THREADS},
+        {reinterpret_cast<const void *>(&k_bracket<BR_SAMPLED, false>), BR_SAMPLE_BLOCKS, BR_THREADS},
+        {read, blocks, BR_READ_THREADS},
+        {reinterpret_cast<const void *>(&k_bracket<BR_COPIED, false>), cu_count(), BR_THREADS},
+        {reinterpret_cast<const void *>(&k_bracket<BR_COPIED, false>), cu_count(), BR_THREADS}};
+    void *args[] = {&a};
+    hipError_t e;
+    for (const auto &p : passes)
+        if ((e = hipLaunchKernel(p.k, dim3((unsigned)p.blocks), dim3((unsigned)p.threads), args, 0,
+                                 nullptr)) != hipSuccess)
+            return hip_fail(e, "rank launch");
+    if ((e = poll_host(&w->h_out->done, a.gen)) != hipSuccess) return hip_fail(e, "rank result");
+    const RankOut &o = *w->h_out;
+    *n_valid = o.n_valid;
+    *status = o.status;
+    if (!o.status) keys->assign(o.key, o.key + o.m);
     return CUBE_OK;
 }
 
@@ -775,9 +868,18 @@ int box_ranks(const Box &b, int median, uint64_t rank, float *v, int *n_v, uint6
     std::vector<unsigned int> keys;
     int status = 0, wide = 0;
     uint64_t n = 0;
-    const int rc = run_ranks(b, median ? RANK_MEDIAN : RANK_GIVEN, rank, nullptr, 0, &keys, &n,
-                             &status, &wide);
+    QuantWorkspace *w = nullptr;
+    int rc = quant_ws(&w);
     if (rc) return rc;
+    const unsigned int n_sample = sample_of(b, *w);
+    if (n_sample) {
+        if ((rc = run_bracket(b, n_sample, median, rank, w, &keys, &n, &status))) return rc;
+    }
+    if (!n_sample || status == RANK_MISSED) {
+        rc = run_ranks(b, median ? RANK_MEDIAN : RANK_GIVEN, rank, nullptr, 0, &keys, &n, &status,
+                       &wide);
+        if (rc) return rc;
+    }
     *n_valid = n;
     if (status == 1)
         return fail(CUBE_EINVAL, "rank %llu >= %llu valid voxels", (unsigned long long)rank,

@@ -1,8 +1,8 @@
 // cube_select.hip -- exact selection (k-th smallest valid voxel) and the
 // median: the global, multi-pass median task the paper names in Section 3.
-// One or two ranks of the order-statistics passes (cube_quantile.hip): two
-// reads of the box, and the voxels of the wanted leading key buckets a third
-// time.
+// One or two ranks of the order statistics: a large box is read once
+// (cube_bracket.h); otherwise the passes of cube_quantile.hip read it twice,
+// and the voxels of the wanted leading key buckets a third time.
 #include "cube_internal.h"
 
 using namespace cube;
