@@ -306,10 +306,10 @@ CUBE_API int cube_median(const float *ptr, const int64_t *dims, double *median,
  * b = +Inf) and -Inf to +Inf gives NaN.  At q = 1/2 this is the median up to
  * rounding: cube_median averages (a + b) / 2 instead.
  * Results go to out[0..m-1] (host), the valid count to *n_valid (host; may
- * be NULL).  Three reads of the box when the ranks wanted (two per level at
- * most) fall in at most eight distinct leading 12-bit key buckets and number
- * at most 96 (the third of a copy of the wanted buckets, when it fits), four
- * otherwise; synchronous on the null stream.  Shares the memory that
+ * be NULL).  Three passes over the box when the ranks wanted (two per level
+ * at most) fall in at most eight distinct leading 12-bit key buckets and
+ * number at most 96, four otherwise; the last reads only a copy of the voxels
+ * still wanted, when it fits.  Synchronous on the null stream.  Shares the memory that
  * cube_select keeps.  Errors: CUBE_EINVAL
  * for the box errors of the other calls, an empty box, no valid voxel (with
  * *n_valid = 0), NULL q or out, m outside its range or a level outside
@@ -320,9 +320,10 @@ CUBE_API int cube_quantiles(const float *ptr, const int64_t *dims, const double 
                             double *out, uint64_t *n_valid);
 
 /*
- * Number of reads of the box (3 or 4, see cube_quantiles) that the CALLING
- * THREAD's last successful cube_quantiles call made, for measuring its bytes
- * moved; 0 before the thread's first successful call.  Never fails.
+ * Number of passes (3 or 4, see cube_quantiles) of the CALLING THREAD's last
+ * successful cube_quantiles call, each a read of the box unless the last
+ * reads copied voxels; 0 before the thread's first successful call.  Never
+ * fails.
  */
 CUBE_API int cube_last_quantile_reads(void);
 

@@ -315,7 +315,8 @@ def quantiles(t, q):
 
 
 def cube_last_quantile_reads() -> int:
-    """Reads of the box made by this thread's last successful quantiles call."""
+    """Passes of this thread's last successful quantiles call (each a read of the
+    box unless the last reads copied voxels)."""
     return int(load().cube_last_quantile_reads())
 
 

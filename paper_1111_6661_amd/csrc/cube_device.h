@@ -759,37 +759,16 @@ __device__ __forceinline__ void lds_zero(unsigned int *lds, int nbins, int copie
 }
 
 // The "last block merges" ticket.  Called by every thread of the block after
-// its writes.  After a barrier, thread 0 issues one agent-scope release fence
-// (fences are cumulative: it covers every thread's writes ordered before it
-// by the barrier; on gfx950 it writes back the L2), takes a ticket and, if it
-// is the last of `total`, one agent-scope acquire fence (an L2 and L1
-// invalidate) before the barrier that lets the block read the others' writes.
-// A full __threadfence() is both, and one in every thread costs a write-back
-// per wavefront.  Returns the same answer to every thread.
-__device__ __forceinline__ bool last_to_arrive(unsigned int *ticket, unsigned int total,
-                                               unsigned int *s_shared)
-{
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-        const bool last = atomicAdd(ticket, 1u) == total - 1u;
-        if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        *s_shared = last ? 1u : 0u;
-    }
-    __syncthreads();
-    return *s_shared != 0u;
-}
-
-// The same election without the L2 write-back of the release fence, for a
-// block whose every write that the last block reads is an agent-scope atomic
-// store (written through the XCD's L2 to the device's point of coherence) or
-// an agent-scope atomic read-modify-write (performed there).  Each wavefront
-// waits for its own such writes to complete before the barrier, so all of
-// them are performed at device scope before thread 0 takes the ticket; the
-// last block then acquires (invalidates its L2) before it reads.  The release
-// fence's buffer_wbl2 would only add the write-back of plain stores, of
-// which there are none here; it stalls a block for several microseconds per
-// call, which the batched launch pays at every tile.
+// its writes; returns the same answer to every thread.  Every write that the
+// last block reads is an agent-scope atomic store (written through the XCD's
+// L2 to the device's point of coherence) or an agent-scope atomic
+// read-modify-write (performed there).  Each wavefront waits for its own such
+// writes to complete before the barrier, so all of them are performed at
+// device scope before thread 0 takes the ticket; the last block then acquires
+// (invalidates its L2) before it reads.  A release fence's buffer_wbl2 would
+// only add the write-back of plain stores, of which there are none here; it
+// stalls a block for several microseconds per call, which the batched launch
+// pays at every tile.
 __device__ __forceinline__ bool last_to_arrive_wt(unsigned int *ticket, unsigned int total,
                                                   unsigned int *s_shared)
 {

@@ -25,14 +25,15 @@
 // pass's histograms, finds the bin of every rank, and lays out the next pass:
 // its prefixes, tables and bits (cube_quantile_plan.h holds the same plan in
 // plain C++).  The last pass's last block writes the ranks' keys to host
-// memory.  When the wanted top buckets hold few enough voxels, the second pass
-// also copies those out, and the third reads only them.
+// memory.  When the voxels under the wanted prefixes are few enough, the last
+// pass but one also copies them out, and the last reads only the copies.
 //
 // Measured (call, microseconds; before: the host read every pass's counts
 // back, laid out the next pass and uploaded its tables; a fourth full pass
 // looked for the upper middle of an even count): median of 2^17 voxels 133 ->
 // 42, of 2^24 -> 68 (larger boxes: cube_bracket.h, one read); 64 levels of
-// 2^20 302 -> 85, of 2^28 910 -> 737 (four reads at 5.9 TB/s).
+// 2^20 302 -> 85, of 2^28 910 -> 737 and, once the last of the four passes
+// read copies, 610 (9 levels 703 -> 558).
 #include <math.h>
 #include <string.h>
 
@@ -46,8 +47,7 @@
 
 namespace cube {
 
-// Reads of the box made by the calling thread's last successful
-// cube_quantiles call.
+// Passes of the calling thread's last successful cube_quantiles call.
 thread_local int g_quant_reads = 0;
 
 namespace {
@@ -67,7 +67,9 @@ struct RankState {
     unsigned int key[Q_MAX_RANKS];         // that prefix, at the top of the word; ascending
     int m;                       // ranks
     int done;                    // the result (or an error) has been written
-    int wide, collect;
+    int wide;
+    int collect;                 // the pass that copies the counted voxels out (0: none)
+    unsigned long long nv;       // valid voxels
     unsigned int overflow;       // a block's region of copied voxels was too small
     int shift, width;            // the next pass bins key bits [shift, shift + width)
     int w2, w3;                  // bits of the second and third prefix levels
@@ -116,7 +118,7 @@ struct QuantStep {
     unsigned int bmask;
     int wb;
     unsigned int valid;            // first pass: valid voxels seen by this wavefront
-    bool collect;                  // second pass: copy the counted voxels out
+    bool collect;                  // second or third pass: copy the counted voxels out
     float *cand;
     unsigned int cand_cap;
     unsigned int *s_cnt;           // voxels this block copied (LDS counter)
@@ -165,7 +167,7 @@ struct QuantStep {
                                             : (k[j] >> shift) & bmask);
                 if (x[j] == x[j] && g[j] != 0u) atomicAdd(&lds[(idx << clog) + cbase], 1u);
             }
-            if (NL == 1 && collect) copy_out<NV>(x, g);
+            if ((NL == 1 || NL == 2) && collect) copy_out<NV>(x, g);
         }
     }
 
@@ -188,6 +190,7 @@ struct QuantStep {
         for (int j = 0; j < NV; ++j) {
             const bool in = x[j] == x[j] && g[j] != 0u;
             const unsigned long long m = __builtin_amdgcn_ballot_w64(in);
+            if (!m) continue;
             const unsigned int i =
                 at + __builtin_amdgcn_mbcnt_hi((unsigned int)(m >> 32),
                                                __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u));
@@ -484,10 +487,10 @@ __device__ void rank_end(const RankArgs &a, RankShared &s, unsigned int *scratch
                 (unsigned char)(i3 + 1);
     }
     __syncthreads();
-    if (NL == 0 && tid < 128) {  // the voxels in the wanted buckets
+    if (NL < 2 && tid < 128) {  // the voxels under the wanted prefixes
         unsigned long long pop =
-            tid < m && (tid == 0 || (s.key[tid] >> 20) != (s.key[tid - 1] >> 20)) ? s.count[tid]
-                                                                                 : 0ull;
+            tid < m && (tid == 0 || (s.key[tid] >> shift) != (s.key[tid - 1] >> shift))
+                ? s.count[tid] : 0ull;
         wave_reduce(CountStep{pop});
         if ((tid & 63) == WAVE_LAST) s.wave[tid >> 6] = pop;
     }
@@ -496,17 +499,24 @@ __device__ void rank_end(const RankArgs &a, RankShared &s, unsigned int *scratch
     for (int i = tid; i < words; i += blockDim.x) tab[i] = scratch[i];
     if (tid == 0) {
         if (NL == 0) {
-            // Copy the wanted buckets out in the second pass when that is
-            // less than reading the box again and the regions have room.
-            const unsigned long long pop = s.wave[0] + s.wave[1];
-            st->collect = wide && a.cand && pop <= s.nv / 6 &&
-                                  pop <= (unsigned long long)CAND_TOTAL / 4 * 3
-                              ? 1 : 0;
             st->overflow = 0u;
             st->m = m;
             st->wide = wide;
+            st->collect = 0;
+            st->nv = s.nv;
             st->done = 0;
             store_result<true>(&a.out->n_valid, s.nv);
+        }
+        // Copy those voxels out in the next pass when that is less than
+        // reading the box again and the regions have room: under the top 12
+        // bits when three passes are left but one, else under the top 20
+        // (64 levels of 2^28 noise voxels: about 0.4 % of them), so that the
+        // last pass reads the copies.
+        if (NL < 2 && (NL == 0) == (wide != 0)) {
+            const unsigned long long pop = s.wave[0] + s.wave[1];
+            const unsigned long long nv = NL == 0 ? s.nv : st->nv;
+            if (a.cand && pop <= nv / 6 && pop <= (unsigned long long)CAND_TOTAL / 4 * 3)
+                st->collect = NL + 1;
         }
         st->shift = shift - next_width;
         st->width = next_width;
@@ -538,8 +548,8 @@ __global__ void __launch_bounds__(Q_THREADS) k_quant(RankArgs a)
         t2_bytes = cs->t2_bytes;
         t3_bytes = cs->t3_bytes;
         wide = cs->wide;
-        if (NL == 1) collect = cs->collect != 0;
-        if (NL == 2) from_cand = cs->collect != 0 && cs->overflow == 0u;
+        collect = NL < 3 && cs->collect == NL;
+        from_cand = NL > 1 && cs->collect == NL - 1 && cs->overflow == 0u;
     }
     const int nbins = 1 << width;
     const int rows = NL == 0 ? 1 : slots + 1;   // after the first pass, row 0 is unused
@@ -578,8 +588,8 @@ __global__ void __launch_bounds__(Q_THREADS) k_quant(RankArgs a)
     st.cand = a.cand + (size_t)blockIdx.x * a.cand_cap;
     st.cand_cap = a.cand_cap;
     st.s_cnt = &s_cnt;
-    if (NL == 2 && from_cand) {
-        // The voxels the second pass copied to this block's region.
+    if (NL > 1 && from_cand) {
+        // The voxels that the pass before copied to this block's region.
         const unsigned int n = a.cand_n[blockIdx.x];
         for (unsigned int i0 = 0; i0 < n; i0 += 4u * (unsigned int)B) {
             float x[4];
@@ -607,7 +617,7 @@ __global__ void __launch_bounds__(Q_THREADS) k_quant(RankArgs a)
     }
     if (tid == 0) {
         if (NL == 0 && s_valid) atomicAdd(&a.acc[Q_ACC], (unsigned long long)s_valid);
-        if (NL == 1 && collect) {
+        if (NL > 0 && collect) {
             a.cand_n[blockIdx.x] = min(s_cnt, a.cand_cap);
             if (s_cnt > a.cand_cap) atomicOr(&a.st->overflow, 1u);
         }
