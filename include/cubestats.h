@@ -309,7 +309,8 @@ CUBE_API int cube_median(const float *ptr, const int64_t *dims, double *median,
  * be NULL).  Three passes over the box when the ranks wanted (two per level
  * at most) fall in at most eight distinct leading 12-bit key buckets and
  * number at most 96, four otherwise; the last reads only a copy of the voxels
- * still wanted, when it fits.  Synchronous on the null stream.  Shares the memory that
+ * still wanted, when it fits.  A single level of a box of 3 * 2^24 voxels or
+ * more is found in one read, as the median is.  Synchronous on the null stream.  Shares the memory that
  * cube_select keeps.  Errors: CUBE_EINVAL
  * for the box errors of the other calls, an empty box, no valid voxel (with
  * *n_valid = 0), NULL q or out, m outside its range or a level outside
@@ -321,9 +322,9 @@ CUBE_API int cube_quantiles(const float *ptr, const int64_t *dims, const double 
 
 /*
  * Number of passes (3 or 4, see cube_quantiles) of the CALLING THREAD's last
- * successful cube_quantiles call, each a read of the box unless the last
- * reads copied voxels; 0 before the thread's first successful call.  Never
- * fails.
+ * successful cube_quantiles call, each a read of the box unless it reads
+ * copied voxels or a sample gave a bracket (counted as 3); 0 before the
+ * thread's first successful call.  Never fails.
  */
 CUBE_API int cube_last_quantile_reads(void);
 

@@ -1,5 +1,5 @@
-// cube_bracket.h -- one rank, or the two middle ranks, of a large box in one
-// read (included by cube_quantile.hip).
+// cube_bracket.h -- one rank, the two middle ranks or those of one quantile
+// level of a large box in one read (included by cube_quantile.hip).
 //
 // A sample of the box (one voxel out of each of 2^18 or more equal strides)
 // gives a bracket of keys that holds the wanted ranks unless the sample is
@@ -15,7 +15,8 @@
 // ranks and lays out the next pass.
 //
 // Measured (median, microseconds; before: two reads, by cube_quantile.hip): of
-// 2^28 voxels 370 -> 257, of a 941 x 937 x 240 box 362 -> 237.  About 65 us
+// 2^28 voxels 370 -> 257, of a 941 x 937 x 240 box 362 -> 237; one quantile level
+// the same.  About 65 us
 // are the five passes' ends and the sample; the read reaches 5.6 TB/s, bound by
 // the issue of some 75 instructions for 4 voxels of each lane (loads a tile
 // ahead, or more wavefronts, change nothing).
@@ -69,8 +70,9 @@ struct BracketArgs {
     unsigned int n_pieces;
     unsigned int waves;            // of the read of the box
     unsigned int n_sample, stride;
-    int32_t median;
-    unsigned long long rank;       // not the median
+    int32_t mode;                  // RANK_*: a rank, the median or one level
+    unsigned long long rank;       // RANK_GIVEN
+    double level;                  // RANK_LEVELS: ranks floor(level (n - 1)) and the next
     RankOut *out;
     unsigned int gen;
 };
@@ -299,10 +301,11 @@ __device__ __forceinline__ void bracket_end(const BracketArgs &a, BracketShared 
             // The sample ranks 5 standard deviations (of a binomial count)
             // either side of the wanted ones; 16 more for small counts.
             const double v = (double)s.nv;
-            const double of = a.median ? v : (double)a.n_sample;
-            const double c = a.median ? 0.5 * (v - 1.0)
-                                      : (double)a.rank * ((double)a.n_sample /
-                                                          (double)a.g.n_total);
+            const double of = a.mode == RANK_GIVEN ? (double)a.n_sample : v;
+            const double c =
+                a.mode == RANK_GIVEN
+                    ? (double)a.rank * ((double)a.n_sample / (double)a.g.n_total)
+                    : (a.mode == RANK_MEDIAN ? 0.5 : a.level) * (v - 1.0);
             const double half = 5.0 * sqrt(fmax(c * (1.0 - c / of), 0.0)) + 16.0;
             const double lo = floor(c - half), hi = ceil(c + half);
             st->open = (lo < 0.0 ? 1 : 0) | (hi >= v ? 2 : 0);
@@ -313,8 +316,13 @@ __device__ __forceinline__ void bracket_end(const BracketArgs &a, BracketShared 
             if (s.nv < 1024ull) s.over = RANK_MISSED;
         }
         if (SRC == BR_BOX) {
-            const unsigned long long r = a.median ? (s.nv - 1ull) / 2ull : a.rank;
-            s.m = a.median && s.nv % 2 == 0 ? 2 : 1;
+            unsigned long long r = a.mode == RANK_GIVEN ? a.rank : (s.nv - 1ull) / 2ull;
+            s.m = a.mode == RANK_MEDIAN && s.nv % 2 == 0 ? 2 : 1;
+            if (a.mode == RANK_LEVELS) {
+                const double h = a.level * (double)(s.nv - 1ull), j = floor(h);
+                r = (unsigned long long)j;
+                s.m = h - j > 0.0 ? 2 : 1;
+            }
             s.rank[0] = r - s.below;  // huge if below the bracket
             s.rank[1] = r + 1ull - s.below;
             if (r < s.below || s.nv == 0ull ||

@@ -307,7 +307,7 @@ __device__ __forceinline__ void find_bins(const RankArgs &a, RankShared &s, int 
                                           unsigned long long *sums)
 {
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6, B = blockDim.x;
-    const int nw = B >> 6, nbins = 1 << width, m = s.m;
+    const int nw = B >> 6, nbins = 1 << width;
     if (nbins > 64 * 4) {
         // 4096 bins: the whole block on one slot, consecutive bins per thread;
         // the threads' inclusive sums go to LDS, where each rank searches.
@@ -748,9 +748,9 @@ unsigned int sample_of(const Box &b, const QuantWorkspace &w)
     return 0u;
 }
 
-// The median or one rank in a single read of the box; status RANK_MISSED if
-// the box has to be read again.
-int run_bracket(const Box &box, unsigned int n_sample, int median, uint64_t rank,
+// The median, one rank or one level in a single read of the box; status
+// RANK_MISSED if the box has to be read again.
+int run_bracket(const Box &box, unsigned int n_sample, int mode, uint64_t rank, double level,
                 QuantWorkspace *w, std::vector<unsigned int> *keys, uint64_t *n_valid, int *status)
 {
     BracketArgs a;
@@ -764,8 +764,9 @@ int run_bracket(const Box &box, unsigned int n_sample, int median, uint64_t rank
     a.n_pieces = BR_PIECES;
     a.n_sample = n_sample;
     a.stride = (unsigned int)(box.n / n_sample);
-    a.median = median;
+    a.mode = mode;
     a.rank = rank;
+    a.level = level;
     a.out = w->d_out;
     if (++w->calls == 0u) w->calls = 1u;
     a.gen = w->calls;
@@ -810,12 +811,10 @@ int run_bracket(const Box &box, unsigned int n_sample, int median, uint64_t rank
 
 // Queue the passes on the null stream and wait for the result.  `keys`: the
 // keys of the ranks, ascending.
-int run_ranks(const Box &box, int mode, uint64_t rank, const double *q, int nq,
-              std::vector<unsigned int> *keys, uint64_t *n_valid, int *status, int *wide)
+int run_passes(const Box &box, int mode, uint64_t rank, const double *q, int nq,
+               QuantWorkspace *w, std::vector<unsigned int> *keys, uint64_t *n_valid, int *status,
+               int *wide)
 {
-    QuantWorkspace *w = nullptr;
-    int rc = quant_ws(&w);
-    if (rc) return rc;
     RankArgs a;
     memset(&a, 0, sizeof a);
     a.st = w->st;
@@ -854,6 +853,7 @@ int run_ranks(const Box &box, int mode, uint64_t rank, const double *q, int nq,
     const bool packed = a.g.pack.cb > 0;
     const int passes = 2 * nq > Q_WIDE_BUCKETS ? 4 : 3;  // few ranks are always "wide"
     const size_t lds0 = (size_t)4096 * 4 << a.max_clog;
+    int rc;
     if ((rc = rank_launch(quant_kernel<0>(packed), a, (int)blocks, lds0)) ||
         (rc = rank_launch(quant_kernel<1>(packed), a, (int)blocks, Q_LDS)) ||
         (rc = rank_launch(quant_kernel<2>(packed), a, (int)blocks, Q_LDS)) ||
@@ -870,6 +870,22 @@ int run_ranks(const Box &box, int mode, uint64_t rank, const double *q, int nq,
     return CUBE_OK;
 }
 
+// The ranks' keys by the route that suits the box.
+int run_ranks(const Box &box, int mode, uint64_t rank, const double *q, int nq,
+              std::vector<unsigned int> *keys, uint64_t *n_valid, int *status, int *wide)
+{
+    QuantWorkspace *w = nullptr;
+    int rc = quant_ws(&w);
+    if (rc) return rc;
+    const unsigned int n_sample = nq > 1 ? 0u : sample_of(box, *w);
+    if (n_sample) {
+        *wide = 1;
+        rc = run_bracket(box, n_sample, mode, rank, nq ? q[0] : 0.0, w, keys, n_valid, status);
+        if (rc || *status != RANK_MISSED) return rc;
+    }
+    return run_passes(box, mode, rank, q, nq, w, keys, n_valid, status, wide);
+}
+
 }  // namespace
 
 int box_ranks(const Box &b, int median, uint64_t rank, float *v, int *n_v, uint64_t *n_valid)
@@ -878,18 +894,9 @@ int box_ranks(const Box &b, int median, uint64_t rank, float *v, int *n_v, uint6
     std::vector<unsigned int> keys;
     int status = 0, wide = 0;
     uint64_t n = 0;
-    QuantWorkspace *w = nullptr;
-    int rc = quant_ws(&w);
+    const int rc = run_ranks(b, median ? RANK_MEDIAN : RANK_GIVEN, rank, nullptr, 0, &keys, &n,
+                             &status, &wide);
     if (rc) return rc;
-    const unsigned int n_sample = sample_of(b, *w);
-    if (n_sample) {
-        if ((rc = run_bracket(b, n_sample, median, rank, w, &keys, &n, &status))) return rc;
-    }
-    if (!n_sample || status == RANK_MISSED) {
-        rc = run_ranks(b, median ? RANK_MEDIAN : RANK_GIVEN, rank, nullptr, 0, &keys, &n, &status,
-                       &wide);
-        if (rc) return rc;
-    }
     *n_valid = n;
     if (status == 1)
         return fail(CUBE_EINVAL, "rank %llu >= %llu valid voxels", (unsigned long long)rank,

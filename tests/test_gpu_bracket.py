@@ -72,6 +72,18 @@ def _check(x, ranks):
         assert got == ref and math.copysign(1.0, got) == math.copysign(1.0, ref), k
     with pytest.raises(Exception):
         cs.select(x, n)
+    for level in (0.0, 0.001, 0.37, 0.5, 1.0):
+        (got,), nv = cs.quantiles(x, [level])
+        h = level * (n - 1)
+        j = math.floor(h)
+        a, b = v[j].item(), v[min(j + 1, n - 1)].item()
+        if a == b or h == j:
+            want = a
+        elif math.isinf(a) or math.isinf(b):
+            want = math.nan if math.isinf(a) and math.isinf(b) else a if math.isinf(a) else b
+        else:
+            want = a + (h - j) * (b - a)
+        assert nv == n and (got == want or (math.isnan(got) and math.isnan(want))), level
 
 
 @pytest.mark.parametrize("name", ["noise", "offset", "constant", "levels", "fine levels", "zeros",
