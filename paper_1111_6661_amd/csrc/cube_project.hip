@@ -373,7 +373,9 @@ int cube_project(const float *ptr, const int64_t *dims, float *mip, double *mom0
     // 800 x 256 of 2048-wide rows: 2500 wavefronts 152 us, 3072 156).  Small
     // images: slices of the channel axis until enough wavefronts are busy,
     // each slice keeping at least 32 channels (256 x 256 x 256 with at least
-    // 64: 60 us, 32: 21).
+    // 64: 60 us, 32: 21), or 64 with two wavefronts per CU and more before
+    // slicing (the partials then cost more than the wavefronts give: 1819 x 80
+    // x 217 with 32: 30.3 us, 64: 28.0, 100: 31.8; 512 x 512 x 64 39 and 36).
     const int64_t cus = cu_count();
     int64_t waves = (a.units + 63) / 64;
     if (quad && waves > 12 * cus) {
@@ -387,7 +389,7 @@ int cube_project(const float *ptr, const int64_t *dims, float *mip, double *mom0
     const int Q = (int)((a.per + 63) / 64);
     const int64_t want = cus * (Q > 1 ? 4 : (quad ? 8 : 16));
     int64_t slices = waves * 8 >= want * 7 ? 1 : (want + waves - 1) / waves;
-    slices = std::min<int64_t>(slices, std::max<int64_t>(1, b.nz / 32));
+    slices = std::min<int64_t>(slices, std::max<int64_t>(1, b.nz / (waves >= 2 * cus ? 64 : 32)));
     slices = std::min<int64_t>(slices, 64);
     a.zps = (b.nz + slices - 1) / slices;
     a.slices = (int32_t)((b.nz + a.zps - 1) / a.zps);
