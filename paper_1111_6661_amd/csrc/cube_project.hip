@@ -366,11 +366,11 @@ int cube_project(const float *ptr, const int64_t *dims, float *mip, double *mom0
     const bool quad = a.nx >= 4 && a.nx < ((int64_t)1 << 31) &&
                       (64 * 16 / a.quads_row + 2) < (((int64_t)1 << 30) / (a.sy < 1 ? 1 : a.sy));
     a.units = quad ? quads : npix;
-    // From 192 K quads on, equal shares for every CU: a multiple of one block
+    // From 144 K quads on, equal shares for every CU: a multiple of one block
     // of four wavefronts per CU, as few as up to 16 quads per lane allow (each
-    // holds 16 Q registers of state).  Below, 64 quads per wavefront: with
-    // many wavefronts per CU whole ones read better than equal shares (800 x
-    // 800 x 256 of 2048-wide rows: 2500 wavefronts 152 us, 3072 156).  Small
+    // holds 16 Q registers of state).  Below, 64 quads per wavefront.  (A line
+    // at 192 K: 800 x 800 x 256 of 2048-wide rows 172 us against 169, dense 125
+    // and 115, 1500 x 430 x 256 141 and 129.)  Small
     // images: slices of the channel axis until enough wavefronts are busy,
     // each slice keeping at least 32 channels (256 x 256 x 256 with at least
     // 64: 60 us, 32: 21), or 64 with two wavefronts per CU and more before
@@ -378,7 +378,7 @@ int cube_project(const float *ptr, const int64_t *dims, float *mip, double *mom0
     // x 217 with 32: 30.3 us, 64: 28.0, 100: 31.8; 512 x 512 x 64 39 and 36).
     const int64_t cus = cu_count();
     int64_t waves = (a.units + 63) / 64;
-    if (quad && waves > 12 * cus) {
+    if (quad && waves > 9 * cus) {
         const int64_t most = 4 * cus * 64 * 16;
         waves = 4 * cus * ((a.units + most - 1) / most);
         a.per = (a.units + waves - 1) / waves;
@@ -388,7 +388,10 @@ int cube_project(const float *ptr, const int64_t *dims, float *mip, double *mom0
     waves = (a.units + a.per - 1) / a.per;
     const int Q = (int)((a.per + 63) / 64);
     const int64_t want = cus * (Q > 1 ? 4 : (quad ? 8 : 16));
-    int64_t slices = waves * 8 >= want * 7 ? 1 : (want + waves - 1) / waves;
+    // Equal shares come out a little under the wavefronts they aim at; with
+    // one quad per lane every wavefront counts (700 x 700 x 256, 1914 of 2048
+    // wavefronts: 134 us, in two slices 116).
+    int64_t slices = waves * 8 >= want * (Q > 1 ? 7 : 8) ? 1 : (want + waves - 1) / waves;
     slices = std::min<int64_t>(slices, std::max<int64_t>(1, b.nz / (waves >= 2 * cus ? 64 : 32)));
     slices = std::min<int64_t>(slices, 64);
     a.zps = (b.nz + slices - 1) / slices;
