@@ -111,6 +111,10 @@ struct Workspace {
     unsigned int *dump = nullptr;         // blocks' rows of counts (many bins), DUMP_BYTES
     hipEvent_t used = nullptr;            // recorded after the last work queued with it
     std::mutex mu;                        // held by synchronous calls
+    // Held while the launches of one call are queued: a later launch reads what
+    // an earlier one left in the workspace (d_range, dump, hist_acc), so no
+    // other thread's call on the stream may come between.  Taken after mu.
+    std::mutex queue;
 };
 
 std::mutex g_mu;
@@ -742,6 +746,7 @@ int run_async(Op op, const float *ptr, const int64_t *dims, float lo, float hi, 
         hipError_t e = hipGetLastError();
         return e == hipSuccess ? CUBE_OK : hip_fail(e, "empty-box launch");
     }
+    std::lock_guard<std::mutex> lk(w->queue);
     Plan p;
     const bool dump = op != OP_STATS && wants_dump(nbins, b.n) && have_dump(w, s);
     if (op == OP_STATS || op == OP_MINMAX) {
@@ -781,6 +786,7 @@ int run_pass(const Box &b, bool stats, bool hist, int nbins, const HistRange &ra
     Workspace *w = nullptr;
     int rc = get_ws(s, &w);
     if (rc) return rc;
+    std::lock_guard<std::mutex> lk(w->queue);
     Plan p;
     const bool dump = hist && wants_dump(nbins, b.n) && have_dump(w, s);
     if ((rc = make_plan(b, stats, hist ? 1 : 0, nbins, &p, dump))) return rc;

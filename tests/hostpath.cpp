@@ -1,0 +1,259 @@
+// The host path of libcubestats.so on a machine without a GPU: this program
+// defines the HIP calls that the library makes (an executable's symbols come
+// before those of the libraries it loads).  Device memory is host memory that
+// nobody touches, kernels do not run, and every launch is noted in the order
+// in which it was made.  Each scenario below drives entry points and exits 0,
+// or prints what was wrong.
+#include <dlfcn.h>
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+#include <sys/mman.h>
+
+#include <atomic>
+#include <chrono>
+#include <functional>
+#include <map>
+#include <mutex>
+#include <string>
+#include <thread>
+#include <vector>
+
+#include "cube_internal.h"
+
+using cube::PassArgs;
+
+#define CHECK(c)                                                  \
+    do {                                                          \
+        if (!(c)) {                                               \
+            printf("%s:%d: %s\n", __FILE__, __LINE__, #c);        \
+            dump_launches();                                      \
+            exit(1);                                              \
+        }                                                         \
+    } while (0)
+
+// ------------------------------------------------------------- the fake runtime
+struct Launch {
+    std::string name;
+    dim3 grid;
+    hipStream_t stream;
+    std::thread::id thread;
+    bool is_pass;     // `pass` holds the kernel's arguments
+    PassArgs pass;
+};
+
+static std::mutex g_m;
+// The library registers its kernels before this program's own objects exist.
+static std::map<const void *, std::string> &names()
+{
+    static std::map<const void *, std::string> n;
+    return n;
+}
+static std::map<uintptr_t, size_t> g_mem;      // device and pinned allocations
+static std::vector<Launch> g_launches;
+static std::vector<size_t> g_mallocs;          // sizes of device allocations, in order
+static std::vector<uintptr_t> g_frees;
+static std::function<void(const Launch &)> g_hook;  // after a launch was noted
+static bool g_signal = true;                   // passes tell the host that they are done
+static std::atomic<bool> g_capturing{false};
+static thread_local struct { dim3 grid, block; size_t lds; hipStream_t s; } g_cfg;
+
+static void dump_launches()
+{
+    for (const Launch &l : g_launches)
+        printf("  stream %p thread %zx %s\n", (void *)l.stream,
+               std::hash<std::thread::id>()(l.thread) & 0xffff, l.name.c_str());
+    fflush(stdout);
+}
+
+static void *take(size_t n)
+{
+    n = (n + 4095) & ~(size_t)4095;
+    void *p = mmap(nullptr, n, PROT_READ | PROT_WRITE,
+                   MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+    if (p == MAP_FAILED) abort();
+    std::lock_guard<std::mutex> lk(g_m);
+    g_mem[(uintptr_t)p] = n;
+    return p;
+}
+static void give(void *p)
+{
+    if (!p) return;
+    std::lock_guard<std::mutex> lk(g_m);
+    auto it = g_mem.find((uintptr_t)p);
+    if (it == g_mem.end()) abort();
+    munmap(p, it->second);
+    g_mem.erase(it);
+}
+
+extern "C" {
+void **__hipRegisterFatBinary(const void *) { static void *x; return &x; }
+void __hipUnregisterFatBinary(void **) {}
+void __hipRegisterFunction(void **, const void *f, char *, const char *name, unsigned, void *,
+                           void *, dim3 *, dim3 *, int *)
+{
+    names()[f] = name;
+}
+void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
+hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t lds, hipStream_t s)
+{
+    g_cfg = {g, b, lds, s};
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *lds, hipStream_t *s)
+{
+    *g = g_cfg.grid;
+    *b = g_cfg.block;
+    *lds = g_cfg.lds;
+    *s = g_cfg.s;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void *f, dim3 g, dim3, void **args, size_t, hipStream_t s)
+{
+    Launch l = {names().at(f), g, s, std::this_thread::get_id(), false, {}};
+    l.is_pass = l.name.find("6k_passI") != std::string::npos ||
+                l.name.find("10k_pass_dynI") != std::string::npos;
+    if (l.is_pass) l.pass = *(const PassArgs *)args[0];
+    {
+        std::lock_guard<std::mutex> lk(g_m);
+        g_launches.push_back(l);
+    }
+    if (g_hook) g_hook(l);
+    if (l.is_pass && l.pass.done && g_signal)
+        __atomic_store_n(l.pass.done, l.pass.done_gen, __ATOMIC_RELEASE);
+    return hipSuccess;
+}
+
+hipError_t hipMalloc(void **p, size_t n)
+{
+    if (g_capturing) return hipErrorStreamCaptureUnsupported;
+    {
+        std::lock_guard<std::mutex> lk(g_m);
+        g_mallocs.push_back(n);
+    }
+    *p = take(n);
+    return hipSuccess;
+}
+hipError_t hipFree(void *p)
+{
+    if (p) {
+        std::lock_guard<std::mutex> lk(g_m);
+        g_frees.push_back((uintptr_t)p);
+    }
+    give(p);
+    return hipSuccess;
+}
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = take(n); return hipSuccess; }
+hipError_t hipHostFree(void *p) { give(p); return hipSuccess; }
+hipError_t hipHostGetDevicePointer(void **d, void *h, unsigned) { *d = h; return hipSuccess; }
+hipError_t hipMemset(void *p, int v, size_t n) { memset(p, v, n); return hipSuccess; }
+hipError_t hipMemGetAddressRange(hipDeviceptr_t *base, size_t *size, hipDeviceptr_t p)
+{
+    std::lock_guard<std::mutex> lk(g_m);
+    auto it = g_mem.upper_bound((uintptr_t)p);
+    if (it == g_mem.begin()) return hipErrorInvalidValue;
+    --it;
+    *base = (hipDeviceptr_t)it->first;
+    *size = it->second;
+    return hipSuccess;
+}
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *)
+{
+    memset(a, 0, sizeof *a);
+    a->type = hipMemoryTypeDevice;
+    return hipSuccess;
+}
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
+hipError_t hipDeviceSynchronize(void) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *st)
+{
+    *st = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+hipError_t hipGetLastError(void) { return hipSuccess; }
+const char *hipGetErrorString(hipError_t) { return "an error"; }
+hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, int, size_t)
+{
+    *n = 1;
+    return hipSuccess;
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { *e = (hipEvent_t)1; return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+}
+
+// ------------------------------------------------------------------ scenarios
+static hipStream_t const STREAM = (hipStream_t)0x1000;
+
+static float *device_floats(size_t n) { return (float *)take(n * 4); }
+
+// Thread B makes its call while thread A is between two launches of its own;
+// the launches of each call must still follow each other.
+static void interleave(std::function<void()> a, std::function<void()> b)
+{
+    std::atomic<bool> started{false}, b_done{false};
+    std::thread::id a_id = std::this_thread::get_id();
+    g_launches.clear();
+    g_hook = [&](const Launch &l) {
+        if (l.thread != a_id || started.exchange(true)) return;
+        const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(300);
+        std::thread(
+            [&] {
+                b();
+                b_done = true;
+            })
+            .detach();
+        while (!b_done && std::chrono::steady_clock::now() < until) std::this_thread::yield();
+    };
+    a();
+    while (!b_done) std::this_thread::yield();
+    g_hook = nullptr;
+    int changes = 0;
+    for (size_t i = 1; i < g_launches.size(); ++i)
+        changes += g_launches[i].thread != g_launches[i - 1].thread;
+    CHECK(started && g_launches.size() >= 4 && changes == 1);
+}
+
+static void shared_stream()
+{
+    const int64_t n = 1 << 21, dims[5] = {n, 1, 1, 0, 0};
+    float *x = device_floats(n), *y = device_floats(n);
+    cube_stats_t *out = (cube_stats_t *)take(sizeof *out);
+    uint64_t *c = (uint64_t *)take((65536 + 3) * 8);
+    auto ok = [](int rc) {
+        if (rc) printf("error: %s\n", cube_last_error());
+        if (rc) exit(1);
+    };
+    for (int bins : {8192, 16384, 65536}) {
+        auto fused = [&](float *p, hipStream_t s) {
+            return [=] { ok(cube_stats_hist_async(p, dims, -1.f, 1.f, bins, out, c, s)); };
+        };
+        ok(cube_stats_hist_async(x, dims, -1.f, 1.f, bins, out, c, STREAM));
+        interleave(fused(x, STREAM), fused(y, STREAM));
+        // A synchronous call and a stream-ordered one on the default stream.
+        std::vector<uint64_t> host((size_t)bins + 3);
+        auto sync = [&] { ok(cube_hist(x, dims, -1.f, 1.f, bins, host.data())); };
+        interleave(sync, fused(y, nullptr));
+        interleave(fused(y, nullptr), sync);
+    }
+    auto minmax = [&](float *p) {
+        return [=] { ok(cube_stats_hist_minmax_async(p, dims, 64, out, c, STREAM)); };
+    };
+    interleave(minmax(x), minmax(y));
+}
+
+int main(int argc, char **argv)
+{
+    static const std::map<std::string, void (*)()> all = {
+        {"shared_stream", shared_stream},
+    };
+    if (argc != 2 || !all.count(argv[1])) return 2;
+    all.at(argv[1])();
+    puts("ok");
+    return 0;
+}
