@@ -711,6 +711,9 @@ PassArgs base_args(const Workspace *w, const Plan &p, int nbins)
 
 // A synchronous call's last pass tells the CPU when its results are there
 // (*done_gen, 0 where it cannot: many bins are finished by a second kernel).
+// Every pass of such a call writes its results through (a.host): the first of
+// a min/max call leaves the statistics, and the second one's word alone would
+// not say that they have arrived.
 void ask_done(PassArgs &a, Workspace *w, unsigned int *done_gen)
 {
     if (!done_gen || (a.counts && a.nbins >= DEFER_MIN_BINS)) return;
@@ -746,6 +749,7 @@ int run_async(Op op, const float *ptr, const int64_t *dims, float lo, float hi, 
         hipError_t e = hipGetLastError();
         return e == hipSuccess ? CUBE_OK : hip_fail(e, "empty-box launch");
     }
+    const int32_t host = done_gen != nullptr;
     std::lock_guard<std::mutex> lk(w->queue);
     Plan p;
     const bool dump = op != OP_STATS && wants_dump(nbins, b.n) && have_dump(w, s);
@@ -753,6 +757,7 @@ int run_async(Op op, const float *ptr, const int64_t *dims, float lo, float hi, 
         if ((rc = make_plan(b, true, 0, nbins, &p, false))) return rc;
         PassArgs a = base_args(w, p, nbins);
         a.out = dev_out;
+        a.host = host;
         if (op == OP_MINMAX) {
             a.want_range = 1;
             a.out_range = w->d_range;
@@ -765,6 +770,7 @@ int run_async(Op op, const float *ptr, const int64_t *dims, float lo, float hi, 
         PassArgs a2 = base_args(w, p2, nbins);
         a2.dev_range = w->d_range;
         a2.counts = dev_counts;
+        a2.host = host;
         ask_done(a2, w, done_gen);
         return launch(a2, p2, false, w, s);
     }
@@ -774,6 +780,7 @@ int run_async(Op op, const float *ptr, const int64_t *dims, float lo, float hi, 
     a.range = range;
     a.out = dev_out;
     a.counts = dev_counts;
+    a.host = host;
     ask_done(a, w, done_gen);
     return launch(a, p, stats, w, s);
 }

@@ -1185,9 +1185,9 @@ __device__ __forceinline__ HistRange range_of_extrema(float fmn, float fmx, unsi
     return r;
 }
 
-// A result word to memory; with HOST to host memory that the CPU polls, as a
-// system-scope atomic store (written through; a plain store may stay in the L2
-// until the kernel ends).
+// A result word to memory; with HOST to host memory, as a system-scope atomic
+// store (written through; a plain store may stay in the L2 until the kernel
+// ends, or longer: a poll that sees a later kernel's word says nothing of it).
 template <bool HOST, class T>
 __device__ __forceinline__ void store_result(T *dst, T v)
 {
@@ -1278,6 +1278,8 @@ __device__ void finish_stats(const R *recs, int n_recs, int accum_mode,
         const unsigned long long *w = reinterpret_cast<const unsigned long long *>(&o);
         for (int i = 0; i < (int)(sizeof o / 8); ++i)
             store_result<true>(reinterpret_cast<unsigned long long *>(out) + i, w[i]);
+        // A min/max call's record is there before its second pass begins.
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     } else {
         *out = o;
     }
@@ -1286,7 +1288,7 @@ __device__ void finish_stats(const R *recs, int n_recs, int accum_mode,
 // Copy the global accumulators to the caller's counts (or, with `add`, add
 // them to the counts already there) and return them to zero; thread 0 writes
 // below / above / NaN.  `deferred`: the bins are left to launch_hist_sum.
-// `host`: the counts are host memory that the CPU polls (store_result).
+// `host`: the counts are host memory (store_result).
 __device__ __forceinline__ void finish_hist(unsigned long long *acc, unsigned long long *counts,
                                             int nbins, bool on, unsigned long long below,
                                             unsigned long long above, unsigned long long n_nan,
@@ -1294,7 +1296,7 @@ __device__ __forceinline__ void finish_hist(unsigned long long *acc, unsigned lo
                                             bool host = false)
 {
     if (host) {
-        for (int b = threadIdx.x; b < nbins; b += blockDim.x) {
+        for (int b = threadIdx.x; b < nbins && !deferred; b += blockDim.x) {
             store_result<true>(&counts[b], acc[b]);
             acc[b] = 0ull;
         }

@@ -92,8 +92,9 @@ struct PassArgs {
     int32_t n_chunks;            // 0: static partition; else chunks claimed at run time
     unsigned int *dump;          // a row of counts per block; null: atomics on hist_acc
     int32_t defer_bins;          // the bins are left to launch_hist_sum after the pass
-    unsigned int done_gen;       // written to *done (host memory) once the results,
-    unsigned int *done;          // then host memory too, are there; null: not wanted
+    int32_t host;                // `out` and `counts` are host memory: written through
+    unsigned int done_gen;       // written to *done (host memory too) once the results
+    unsigned int *done;          // are there (with `host`); null: not wanted
 };
 // Words in a block's row of PassArgs::dump.
 inline int dump_words(int hist, int nbins) { return hist == HIST_FINE ? FINE_WORDS : nbins; }

@@ -91,11 +91,11 @@ __global__ void __launch_bounds__(1024) k_pass(PassArgs a)
         HistRange *out_range = a.want_range ? a.out_range : nullptr;
         if (fp32_merge)
             finish_stats<ACC>(a.recs, (int)gridDim.x * nw, a.accum_mode, g.n_total, out, out_range,
-                              a.nbins, nv, below, above, a.done != nullptr);
+                              a.nbins, nv, below, above, a.host != 0);
         else
             finish_stats<ACC, ChunkRec>(brecs, (int)gridDim.x, CUBE_ACCUM_FP64MERGE, g.n_total,
                                         out, out_range, a.nbins, nv, below, above,
-                                        a.done != nullptr);
+                                        a.host != 0);
     } else {
         const BlockSums S = merge_counts<ChunkRec>(brecs, (int)gridDim.x);
         nv = S.nv;
@@ -104,7 +104,7 @@ __global__ void __launch_bounds__(1024) k_pass(PassArgs a)
     }
     if (HIST != HIST_NONE)
         finish_hist(a.hist_acc, a.counts, a.nbins, hist_on, below, above, g.n_total - nv,
-                    a.accumulate != 0, a.defer_bins != 0, a.done != nullptr);
+                    a.accumulate != 0, a.defer_bins != 0, a.host != 0);
     if (tid == 0) *a.ticket = 0u;
     if (a.done) tell_host(a.done, a.done_gen);
 }
@@ -218,7 +218,7 @@ __global__ void __launch_bounds__(1024) k_pass_dyn(PassArgs a)
     if (STATS) {
         finish_stats<CUBE_ACCUM_FP64MERGE, ChunkRec>(recs, nc, CUBE_ACCUM_FP64MERGE, g.n_total, a.out,
                                     a.want_range ? a.out_range : nullptr, a.nbins, nv, below,
-                                    above, a.done != nullptr);
+                                    above, a.host != 0);
     } else {
         const BlockSums S = merge_counts<ChunkRec>(recs, nc);
         nv = S.nv;
@@ -227,7 +227,7 @@ __global__ void __launch_bounds__(1024) k_pass_dyn(PassArgs a)
     }
     if (HIST != HIST_NONE)
         finish_hist(a.hist_acc, a.counts, a.nbins, hist_on, below, above, g.n_total - nv,
-                    a.accumulate != 0, a.defer_bins != 0, a.done != nullptr);
+                    a.accumulate != 0, a.defer_bins != 0, a.host != 0);
     if (tid == 0) {
         *a.ticket = 0u;
         *ctr = 0u;

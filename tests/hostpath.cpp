@@ -51,6 +51,7 @@ static std::map<const void *, std::string> &names()
 }
 static std::map<uintptr_t, size_t> g_mem;      // device and pinned allocations
 static std::vector<Launch> g_launches;
+static std::map<uintptr_t, size_t> g_pinned;   // those in host memory
 static std::vector<size_t> g_mallocs;          // sizes of device allocations, in order
 static std::vector<uintptr_t> g_frees;
 static std::function<void(const Launch &)> g_hook;  // after a launch was noted
@@ -143,7 +144,13 @@ hipError_t hipFree(void *p)
     give(p);
     return hipSuccess;
 }
-hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = take(n); return hipSuccess; }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned)
+{
+    *p = take(n);
+    std::lock_guard<std::mutex> lk(g_m);
+    g_pinned[(uintptr_t)*p] = n;
+    return hipSuccess;
+}
 hipError_t hipHostFree(void *p) { give(p); return hipSuccess; }
 hipError_t hipHostGetDevicePointer(void **d, void *h, unsigned) { *d = h; return hipSuccess; }
 hipError_t hipMemset(void *p, int v, size_t n) { memset(p, v, n); return hipSuccess; }
@@ -247,10 +254,48 @@ static void shared_stream()
     interleave(minmax(x), minmax(y));
 }
 
+static bool pinned(const void *p)
+{
+    auto it = g_pinned.upper_bound((uintptr_t)p);
+    return it != g_pinned.begin() && (uintptr_t)p < (--it)->first + it->second;
+}
+
+// Whatever a synchronous call's passes leave in host memory is written through.
+static void host_results()
+{
+    const int64_t n = 1 << 21, dims[5] = {n, 1, 1, 0, 0};
+    float *x = device_floats(n);
+    cube_stats_t st;
+    std::vector<uint64_t> c(65536 + 3);
+    int results = 0;
+    for (int bins : {64, 8191, 8192, 65536}) {
+        g_launches.clear();
+        CHECK(cube_stats(x, n, 1, 1, nullptr, &st) == CUBE_OK);
+        CHECK(cube_hist(x, dims, -1.f, 1.f, bins, c.data()) == CUBE_OK);
+        CHECK(cube_stats_hist(x, dims, -1.f, 1.f, bins, &st, c.data()) == CUBE_OK);
+        CHECK(cube_stats_hist_minmax(x, dims, bins, &st, c.data()) == CUBE_OK);
+        for (const Launch &l : g_launches) {
+            if (!l.is_pass) continue;
+            const bool host = pinned(l.pass.out) || pinned(l.pass.counts);
+            CHECK(host && l.pass.host);
+            CHECK(!l.pass.done || pinned(l.pass.done));
+            ++results;
+        }
+        // Only results, never the device's own words.
+        g_launches.clear();
+        cube_stats_t *d_out = (cube_stats_t *)take(sizeof st);
+        uint64_t *d_c = (uint64_t *)take((bins + 3) * 8);
+        CHECK(cube_stats_hist_minmax_async(x, dims, bins, d_out, d_c, nullptr) == CUBE_OK);
+        for (const Launch &l : g_launches) CHECK(!l.is_pass || (!l.pass.host && !l.pass.done));
+    }
+    CHECK(results == 4 * 5);
+}
+
 int main(int argc, char **argv)
 {
     static const std::map<std::string, void (*)()> all = {
         {"shared_stream", shared_stream},
+        {"host_results", host_results},
     };
     if (argc != 2 || !all.count(argv[1])) return 2;
     all.at(argv[1])();

@@ -35,3 +35,9 @@ def test_calls_that_share_a_stream_keep_their_launches_together(scenario):
     workspace (the rows of many bins, the range of a two-pass call) have no
     other call's launches between them."""
     scenario("shared_stream")
+
+
+def test_results_in_host_memory_are_written_through(scenario):
+    """Also those of a min/max call's first pass, which the CPU reads when the
+    second pass says that it is done."""
+    scenario("host_results")
