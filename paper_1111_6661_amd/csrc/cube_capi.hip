@@ -213,7 +213,9 @@ bool have_dump(Workspace *w, hipStream_t s)
 }
 
 // Polling sees the results about 4 us before the stream's own completion does;
-// after 100 us without them the stream is waited for instead.
+// after 100 us without them the stream is waited for instead.  A stream that
+// completes without the word has left no results (those before are still in
+// the buffers): an error.
 hipError_t poll_host(const unsigned int *done, unsigned int gen)
 {
     const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(100);
@@ -223,7 +225,9 @@ hipError_t poll_host(const unsigned int *done, unsigned int gen)
             __builtin_ia32_pause();
         }
     } while (std::chrono::steady_clock::now() < until);
-    return hipStreamSynchronize(nullptr);
+    const hipError_t e = hipStreamSynchronize(nullptr);
+    if (e != hipSuccess) return e;
+    return __atomic_load_n(done, __ATOMIC_ACQUIRE) == gen ? hipSuccess : hipErrorUnknown;
 }
 
 // Record that work using `w` was queued on `s` (after a successful enqueue).

@@ -291,11 +291,32 @@ static void host_results()
     CHECK(results == 4 * 5);
 }
 
+// A stream that completes without the pass's word: an error, not the results
+// of the call before.
+static void lost_results()
+{
+    const int64_t n = 1 << 20, dims[5] = {n, 1, 1, 0, 0};
+    float *x = device_floats(n);
+    cube_stats_t st;
+    std::vector<uint64_t> c(64 + 3);
+    double median;
+    CHECK(cube_stats_hist(x, dims, -1.f, 1.f, 64, &st, c.data()) == CUBE_OK);
+    g_signal = false;
+    CHECK(cube_stats(x, n, 1, 1, nullptr, &st) == CUBE_EDEVICE);
+    CHECK(cube_hist(x, dims, -1.f, 1.f, 64, c.data()) == CUBE_EDEVICE);
+    CHECK(cube_stats_hist(x, dims, -1.f, 1.f, 64, &st, c.data()) == CUBE_EDEVICE);
+    CHECK(cube_stats_hist_minmax(x, dims, 64, &st, c.data()) == CUBE_EDEVICE);
+    CHECK(cube_median(x, dims, &median, nullptr) == CUBE_EDEVICE);
+    g_signal = true;
+    CHECK(cube_stats_hist(x, dims, -1.f, 1.f, 64, &st, c.data()) == CUBE_OK);
+}
+
 int main(int argc, char **argv)
 {
     static const std::map<std::string, void (*)()> all = {
         {"shared_stream", shared_stream},
         {"host_results", host_results},
+        {"lost_results", lost_results},
     };
     if (argc != 2 || !all.count(argv[1])) return 2;
     all.at(argv[1])();

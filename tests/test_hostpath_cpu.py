@@ -41,3 +41,7 @@ def test_results_in_host_memory_are_written_through(scenario):
     """Also those of a min/max call's first pass, which the CPU reads when the
     second pass says that it is done."""
     scenario("host_results")
+
+
+def test_a_stream_that_ends_without_results_is_an_error(scenario):
+    scenario("lost_results")
