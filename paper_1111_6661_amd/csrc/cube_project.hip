@@ -254,29 +254,34 @@ __global__ void k_project_empty(ProjArgs a)
 struct ProjScratch {
     void *ptr = nullptr;
     size_t bytes = 0;
+    // Held from the buffer's choice until the merge is queued: another thread's
+    // projection on the stream would overwrite the partials, or free them.
+    std::mutex queue;
 };
 std::mutex g_pmu;
 std::map<std::pair<int, hipStream_t>, ProjScratch> g_pscratch;
 
-int scratch_for(hipStream_t s, size_t bytes, void **out)
+ProjScratch &scratch_of(hipStream_t s)
 {
     int dev = 0;
     hipGetDevice(&dev);
     std::lock_guard<std::mutex> lk(g_pmu);
-    ProjScratch &ps = g_pscratch[std::make_pair(dev, s)];
-    if (ps.bytes < bytes) {
-        hipError_t e;
-        // Earlier work on this stream may still read the old buffer.
-        if (ps.ptr && (e = hipStreamSynchronize(s)) != hipSuccess)
-            return hip_fail(e, "projection scratch");
-        hipFree(ps.ptr);
-        ps.ptr = nullptr;
-        ps.bytes = 0;
-        if ((e = hipMalloc(&ps.ptr, bytes)) != hipSuccess)
-            return hip_fail(e, "projection scratch");
-        ps.bytes = bytes;
-    }
-    *out = ps.ptr;
+    return g_pscratch[std::make_pair(dev, s)];
+}
+
+// `ps` (of stream s, its lock held) with room for `bytes`.
+int grow_scratch(ProjScratch &ps, hipStream_t s, size_t bytes)
+{
+    if (ps.bytes >= bytes) return CUBE_OK;
+    hipError_t e;
+    // Earlier work on this stream may still read the old buffer.
+    if (ps.ptr && (e = hipStreamSynchronize(s)) != hipSuccess)
+        return hip_fail(e, "projection scratch");
+    hipFree(ps.ptr);
+    ps.ptr = nullptr;
+    ps.bytes = 0;
+    if ((e = hipMalloc(&ps.ptr, bytes)) != hipSuccess) return hip_fail(e, "projection scratch");
+    ps.bytes = bytes;
     return CUBE_OK;
 }
 
@@ -396,13 +401,15 @@ int cube_project(const float *ptr, const int64_t *dims, float *mip, double *mom0
     slices = std::min<int64_t>(slices, 64);
     a.zps = (b.nz + slices - 1) / slices;
     a.slices = (int32_t)((b.nz + a.zps - 1) / a.zps);
+    std::unique_lock<std::mutex> queue;
     if (a.slices > 1) {
-        void *scr = nullptr;
+        ProjScratch &ps = scratch_of(s);
+        queue = std::unique_lock<std::mutex>(ps.queue);
         const size_t per = (size_t)npix * (size_t)a.slices;
-        if ((rc = scratch_for(s, per * 16, &scr))) return rc;
-        a.p_sum = (double *)scr;
-        a.p_max = (float *)((char *)scr + per * 8);
-        a.p_cnt = (uint32_t *)((char *)scr + per * 12);
+        if ((rc = grow_scratch(ps, s, per * 16))) return rc;
+        a.p_sum = (double *)ps.ptr;
+        a.p_max = (float *)((char *)ps.ptr + per * 8);
+        a.p_cnt = (uint32_t *)((char *)ps.ptr + per * 12);
     }
     if (!quad) {
         hipLaunchKernelGGL(k_project,

@@ -311,12 +311,29 @@ static void lost_results()
     CHECK(cube_stats_hist(x, dims, -1.f, 1.f, 64, &st, c.data()) == CUBE_OK);
 }
 
+// Two threads project on one stream: each call's slices and the launch that
+// merges them share the stream's partials, which the larger call also grows.
+static void shared_projection()
+{
+    const int64_t small[5] = {64, 64, 256, 0, 0}, large[5] = {256, 256, 256, 0, 0};
+    float *x = device_floats((size_t)256 * 256 * 256);
+    float *mip = device_floats(256 * 256);
+    auto project = [&](const int64_t *dims) {
+        return [=] { CHECK(cube_project(x, dims, mip, nullptr, nullptr, STREAM) == CUBE_OK); };
+    };
+    interleave(project(large), project(large));
+    interleave(project(small), project(large));
+    cube_shutdown();
+    interleave(project(small), project(large));  // the buffer grows in between
+}
+
 int main(int argc, char **argv)
 {
     static const std::map<std::string, void (*)()> all = {
         {"shared_stream", shared_stream},
         {"host_results", host_results},
         {"lost_results", lost_results},
+        {"shared_projection", shared_projection},
     };
     if (argc != 2 || !all.count(argv[1])) return 2;
     all.at(argv[1])();

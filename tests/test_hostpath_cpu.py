@@ -45,3 +45,7 @@ def test_results_in_host_memory_are_written_through(scenario):
 
 def test_a_stream_that_ends_without_results_is_an_error(scenario):
     scenario("lost_results")
+
+
+def test_projections_that_share_a_stream_keep_their_launches_together(scenario):
+    scenario("shared_projection")
