@@ -341,7 +341,11 @@ CUBE_API int cube_last_quantile_reads(void);
  * The outputs are dense DEVICE arrays of nx*ny elements; any may be NULL but
  * not all three.  Stream-ordered on `stream` (NULL = the default stream).
  * Sums are FP64 in channel order within each of at most 64 channel slices,
- * the slices merged in order; results depend only on the shape.  nz == 0
+ * the slices merged in order; results depend only on the shape (and, in the
+ * rounding of mom0, on whether there was memory for the slices' partials, at
+ * most 16 bytes per pixel and slice, which the library keeps per stream until
+ * cube_shutdown: without it, and in a capture of a stream on which no
+ * projection of that size has run, there is one slice).  nz == 0
  * gives NaN / NaN / 0 maps.  Errors: CUBE_EINVAL for the box errors of the
  * other calls, outputs that are not device memory of the needed size or are
  * misaligned (mom0 8-byte), or nz >= 2^32; CUBE_EDEVICE for a HIP error.

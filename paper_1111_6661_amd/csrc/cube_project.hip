@@ -269,20 +269,28 @@ ProjScratch &scratch_of(hipStream_t s)
     return g_pscratch[std::make_pair(dev, s)];
 }
 
-// `ps` (of stream s, its lock held) with room for `bytes`.
-int grow_scratch(ProjScratch &ps, hipStream_t s, size_t bytes)
+// Whether `ps` (of stream s, its lock held) has room for `bytes`, made if need
+// be.  Not while the stream captures: nothing can be allocated or waited for.
+bool have_scratch(ProjScratch &ps, hipStream_t s, size_t bytes)
 {
-    if (ps.bytes >= bytes) return CUBE_OK;
-    hipError_t e;
+    if (ps.bytes >= bytes) return true;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (s && (hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone)) {
+        (void)hipGetLastError();
+        return false;
+    }
+    void *p = nullptr;
     // Earlier work on this stream may still read the old buffer.
-    if (ps.ptr && (e = hipStreamSynchronize(s)) != hipSuccess)
-        return hip_fail(e, "projection scratch");
+    if (hipMalloc(&p, bytes) != hipSuccess ||
+        (ps.ptr && hipStreamSynchronize(s) != hipSuccess)) {
+        (void)hipGetLastError();
+        hipFree(p);
+        return false;
+    }
     hipFree(ps.ptr);
-    ps.ptr = nullptr;
-    ps.bytes = 0;
-    if ((e = hipMalloc(&ps.ptr, bytes)) != hipSuccess) return hip_fail(e, "projection scratch");
+    ps.ptr = p;
     ps.bytes = bytes;
-    return CUBE_OK;
+    return true;
 }
 
 // An output map must be device memory holding `bytes`, aligned to `align`.
@@ -401,15 +409,20 @@ int cube_project(const float *ptr, const int64_t *dims, float *mip, double *mom0
     slices = std::min<int64_t>(slices, 64);
     a.zps = (b.nz + slices - 1) / slices;
     a.slices = (int32_t)((b.nz + a.zps - 1) / a.zps);
+    // Without memory for their partials there is one slice.
     std::unique_lock<std::mutex> queue;
     if (a.slices > 1) {
         ProjScratch &ps = scratch_of(s);
         queue = std::unique_lock<std::mutex>(ps.queue);
         const size_t per = (size_t)npix * (size_t)a.slices;
-        if ((rc = grow_scratch(ps, s, per * 16))) return rc;
-        a.p_sum = (double *)ps.ptr;
-        a.p_max = (float *)((char *)ps.ptr + per * 8);
-        a.p_cnt = (uint32_t *)((char *)ps.ptr + per * 12);
+        if (have_scratch(ps, s, per * 16)) {
+            a.p_sum = (double *)ps.ptr;
+            a.p_max = (float *)((char *)ps.ptr + per * 8);
+            a.p_cnt = (uint32_t *)((char *)ps.ptr + per * 12);
+        } else {
+            a.zps = b.nz;
+            a.slices = 1;
+        }
     }
     if (!quad) {
         hipLaunchKernelGGL(k_project,

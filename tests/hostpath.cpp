@@ -56,7 +56,7 @@ static std::vector<size_t> g_mallocs;          // sizes of device allocations, i
 static std::vector<uintptr_t> g_frees;
 static std::function<void(const Launch &)> g_hook;  // after a launch was noted
 static bool g_signal = true;                   // passes tell the host that they are done
-static std::atomic<bool> g_capturing{false};
+static std::atomic<bool> g_capturing{false}, g_no_memory{false};
 static thread_local struct { dim3 grid, block; size_t lds; hipStream_t s; } g_cfg;
 
 static void dump_launches()
@@ -128,6 +128,7 @@ hipError_t hipLaunchKernel(const void *f, dim3 g, dim3, void **args, size_t, hip
 hipError_t hipMalloc(void **p, size_t n)
 {
     if (g_capturing) return hipErrorStreamCaptureUnsupported;
+    if (g_no_memory) return hipErrorOutOfMemory;
     {
         std::lock_guard<std::mutex> lk(g_m);
         g_mallocs.push_back(n);
@@ -174,7 +175,10 @@ hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
 hipError_t hipDeviceSynchronize(void) { return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t)
+{
+    return g_capturing ? hipErrorStreamCaptureUnsupported : hipSuccess;
+}
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *st)
 {
     *st = g_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
@@ -254,6 +258,13 @@ static void shared_stream()
     interleave(minmax(x), minmax(y));
 }
 
+static bool launched(const char *what)
+{
+    for (const Launch &l : g_launches)
+        if (l.name.find(what) != std::string::npos) return true;
+    return false;
+}
+
 static bool pinned(const void *p)
 {
     auto it = g_pinned.upper_bound((uintptr_t)p);
@@ -327,6 +338,35 @@ static void shared_projection()
     interleave(project(small), project(large));  // the buffer grows in between
 }
 
+// A projection that would take slices makes do with one where their partials
+// cannot be had: under capture, where nothing may be allocated or waited for,
+// and without memory.
+static void projection_without_partials()
+{
+    const int64_t dims[5] = {256, 256, 256, 0, 0}, more[5] = {517, 500, 256, 0, 0};
+    float *x = device_floats((size_t)512 * 512 * 256);
+    float *mip = device_floats(512 * 512);
+    auto project = [&](const int64_t *d) {
+        g_launches.clear();
+        return cube_project(x, d, mip, nullptr, nullptr, STREAM);
+    };
+    for (int k = 0; k < 2; ++k) {
+        std::atomic<bool> &no = k ? g_no_memory : g_capturing;
+        no = true;
+        CHECK(project(dims) == CUBE_OK && g_launches.size() == 1 && g_launches[0].grid.y == 1);
+        no = false;
+        CHECK(project(dims) == CUBE_OK && g_launches.size() == 2 && g_launches[0].grid.y > 1 &&
+              launched("k_project_merge"));
+        // The partials of an earlier call serve, too few of them do not.
+        no = true;
+        CHECK(project(dims) == CUBE_OK && g_launches.size() == 2);
+        CHECK(project(more) == CUBE_OK && g_launches.size() == 1 && g_launches[0].grid.y == 1);
+        no = false;
+        CHECK(project(more) == CUBE_OK && g_launches.size() == 2);
+        cube_shutdown();
+    }
+}
+
 int main(int argc, char **argv)
 {
     static const std::map<std::string, void (*)()> all = {
@@ -334,6 +374,7 @@ int main(int argc, char **argv)
         {"host_results", host_results},
         {"lost_results", lost_results},
         {"shared_projection", shared_projection},
+        {"projection_without_partials", projection_without_partials},
     };
     if (argc != 2 || !all.count(argv[1])) return 2;
     all.at(argv[1])();

@@ -49,3 +49,7 @@ def test_a_stream_that_ends_without_results_is_an_error(scenario):
 
 def test_projections_that_share_a_stream_keep_their_launches_together(scenario):
     scenario("shared_projection")
+
+
+def test_a_projection_without_room_for_slices_takes_one(scenario):
+    scenario("projection_without_partials")
