@@ -23,6 +23,7 @@
 // per lane (k_project).
 #include <string.h>
 
+#include <algorithm>
 #include <map>
 #include <mutex>
 #include <utility>
@@ -254,6 +255,8 @@ __global__ void k_project_empty(ProjArgs a)
 struct ProjScratch {
     void *ptr = nullptr;
     size_t bytes = 0;
+    bool captured = false;      // a graph holds its address
+    std::vector<void *> kept;   // outgrown buffers that graphs hold (each under half the next)
     // Held from the buffer's choice until the merge is queued: another thread's
     // projection on the stream would overwrite the partials, or free them.
     std::mutex queue;
@@ -273,23 +276,33 @@ ProjScratch &scratch_of(hipStream_t s)
 // be.  Not while the stream captures: nothing can be allocated or waited for.
 bool have_scratch(ProjScratch &ps, hipStream_t s, size_t bytes)
 {
-    if (ps.bytes >= bytes) return true;
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    bool capturing = false;
     if (s && (hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone)) {
         (void)hipGetLastError();
-        return false;
+        capturing = true;
     }
+    if (ps.bytes >= bytes) {
+        ps.captured |= capturing;
+        return true;
+    }
+    if (capturing) return false;
+    if (ps.captured) bytes = std::max(bytes, 2 * ps.bytes);
     void *p = nullptr;
     // Earlier work on this stream may still read the old buffer.
     if (hipMalloc(&p, bytes) != hipSuccess ||
-        (ps.ptr && hipStreamSynchronize(s) != hipSuccess)) {
+        (ps.ptr && !ps.captured && hipStreamSynchronize(s) != hipSuccess)) {
         (void)hipGetLastError();
         hipFree(p);
         return false;
     }
-    hipFree(ps.ptr);
+    if (ps.captured)
+        ps.kept.push_back(ps.ptr);
+    else
+        hipFree(ps.ptr);
     ps.ptr = p;
     ps.bytes = bytes;
+    ps.captured = false;
     return true;
 }
 
@@ -323,6 +336,7 @@ void project_release()
         hipSetDevice(kv.first.first);
         hipDeviceSynchronize();
         hipFree(kv.second.ptr);
+        for (void *p : kv.second.kept) hipFree(p);
     }
     hipSetDevice(cur);
     g_pscratch.clear();

@@ -367,6 +367,32 @@ static void projection_without_partials()
     }
 }
 
+// A captured graph keeps the address of the partials: making room for more
+// must not free them before cube_shutdown does.
+static void captured_partials()
+{
+    const int64_t dims[5] = {256, 256, 256, 0, 0}, more[5] = {517, 500, 256, 0, 0};
+    float *x = device_floats((size_t)517 * 500 * 256);
+    float *mip = device_floats(517 * 500);
+    auto project = [&](const int64_t *d) {
+        CHECK(cube_project(x, d, mip, nullptr, nullptr, STREAM) == CUBE_OK);
+    };
+    project(dims);
+    project(more);
+    CHECK(g_frees.size() == 1);   // nothing was captured
+    cube_shutdown();
+    g_frees.clear();
+    project(dims);
+    g_capturing = true;
+    project(dims);
+    g_capturing = false;
+    project(more);
+    CHECK(g_frees.empty());
+    cube_shutdown();
+    CHECK(g_frees.size() == 2);
+    project(dims);
+}
+
 int main(int argc, char **argv)
 {
     static const std::map<std::string, void (*)()> all = {
@@ -375,6 +401,7 @@ int main(int argc, char **argv)
         {"lost_results", lost_results},
         {"shared_projection", shared_projection},
         {"projection_without_partials", projection_without_partials},
+        {"captured_partials", captured_partials},
     };
     if (argc != 2 || !all.count(argv[1])) return 2;
     all.at(argv[1])();

@@ -62,3 +62,24 @@ def test_captured_projection(cs, cut, warm):
         queue(cs, v, out, s)
     replays(cs, g, v, out, host, v)
     del g
+
+
+def test_a_captured_projection_outlives_a_larger_one(cs):
+    """The graph's partials stay where they are when a later projection on the
+    stream needs more of them."""
+    big = cube_of((256, 500, 517), 5)
+    v = big[:, :256, :256].contiguous()
+    host, host_big = v.cpu().numpy(), big.cpu().numpy()
+    out, out_big = maps(256, 256), maps(500, 517)
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    queue(cs, v, out, s)
+    s.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        queue(cs, v, out, s)
+    queue(cs, big, out_big, s)
+    s.synchronize()
+    compare(out_big, host_big, "larger")
+    replays(cs, g, v, out, host, big)
+    del g

@@ -53,3 +53,7 @@ def test_projections_that_share_a_stream_keep_their_launches_together(scenario):
 
 def test_a_projection_without_room_for_slices_takes_one(scenario):
     scenario("projection_without_partials")
+
+
+def test_partials_of_a_captured_projection_are_kept(scenario):
+    scenario("captured_partials")
