@@ -19,8 +19,8 @@
 // too few pixels to fill the device the channels are split into slices, each
 // slice writes per-pixel partials, and a second kernel merges them in slice
 // order, so the result never depends on timing.  Images that quads do not fit
-// (rows under four pixels, or pitches beyond 32-bit offsets) take one pixel
-// per lane (k_project).
+// (rows under four pixels, or apart by more than 32-bit offsets reach) take one
+// pixel per lane (k_project).
 #include <string.h>
 
 #include <algorithm>
@@ -389,9 +389,11 @@ int cube_project(const float *ptr, const int64_t *dims, float *mip, double *mom0
     }
     a.quads_row = (a.nx + 3) / 4;
     const int64_t quads = a.quads_row * a.ny;
-    // Quads while a wavefront's offsets from its first row fit 32 bits.
-    const bool quad = a.nx >= 4 && a.nx < ((int64_t)1 << 31) &&
-                      (64 * 16 / a.quads_row + 2) < (((int64_t)1 << 30) / (a.sy < 1 ? 1 : a.sy));
+    // Quads while a wavefront's offsets from its first row fit 32 bits; in one
+    // row they are from its own first quad, 16 KB at most.
+    const bool quad =
+        a.nx >= 4 && (a.ny == 1 || (a.nx < ((int64_t)1 << 31) &&
+                                    64 * 16 / a.quads_row + 2 < ((int64_t)1 << 30) / a.sy));
     a.units = quad ? quads : npix;
     // From 144 K quads on, equal shares for every CU: a multiple of one block
     // of four wavefronts per CU, as few as up to 16 quads per lane allow (each

@@ -27,6 +27,7 @@ using cube::PassArgs;
     do {                                                          \
         if (!(c)) {                                               \
             printf("%s:%d: %s\n", __FILE__, __LINE__, #c);        \
+            printf("%s\n", cube_last_error());                    \
             dump_launches();                                      \
             exit(1);                                              \
         }                                                         \
@@ -393,6 +394,34 @@ static void captured_partials()
     project(dims);
 }
 
+// Which images take quads of pixels: whole ones of any size (their wavefronts
+// count from their own first quad), others while a wavefront's offsets from
+// its first row fit 32 bits.
+static void projection_kernels()
+{
+    const int64_t K = 1024;
+    struct { int64_t dims[5]; bool quads; } cases[] = {
+        {{64 * K, 8 * K, 2, 0, 0}, true},                     // 2^29 pixels, dense
+        {{64 * K, 32 * K + 1, 2, 0, 0}, true},                // over 2^31
+        {{(int64_t)1 << 31, 1, 1, 0, 0}, true},
+        {{4 * K, 4 * K, 2, (int64_t)1 << 28, (int64_t)1 << 40}, true},
+        {{4 * K, 4 * K, 2, (int64_t)1 << 29, (int64_t)1 << 41}, false},
+        {{3, 4 * K, 2, 4, 0}, false},
+        {{3, 4 * K, 2, 3, 0}, true}};
+    for (auto &c : cases) {
+        const size_t npix = (size_t)(c.dims[0] * c.dims[1]);
+        const int64_t *d = c.dims;
+        const int64_t sy = d[3] ? d[3] : d[0], sz = d[4] ? d[4] : sy * d[1];
+        const size_t end = (size_t)((d[2] - 1) * sz + (d[1] - 1) * sy + d[0]);
+        float *x = device_floats(end), *mip = device_floats(npix);
+        g_launches.clear();
+        CHECK(cube_project(x, d, mip, nullptr, nullptr, STREAM) == CUBE_OK);
+        CHECK(launched("k_project_quads") == c.quads && launched("9k_projectE") != c.quads);
+        give(x);
+        give(mip);
+    }
+}
+
 int main(int argc, char **argv)
 {
     static const std::map<std::string, void (*)()> all = {
@@ -402,6 +431,7 @@ int main(int argc, char **argv)
         {"shared_projection", shared_projection},
         {"projection_without_partials", projection_without_partials},
         {"captured_partials", captured_partials},
+        {"projection_kernels", projection_kernels},
     };
     if (argc != 2 || !all.count(argv[1])) return 2;
     all.at(argv[1])();

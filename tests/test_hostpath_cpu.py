@@ -57,3 +57,7 @@ def test_a_projection_without_room_for_slices_takes_one(scenario):
 
 def test_partials_of_a_captured_projection_are_kept(scenario):
     scenario("captured_partials")
+
+
+def test_images_of_any_size_are_projected_by_quads(scenario):
+    scenario("projection_kernels")
