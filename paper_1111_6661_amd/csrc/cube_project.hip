@@ -18,9 +18,9 @@
 // than compensated FP32 and is exact to about n * 2^-53.  When the image has
 // too few pixels to fill the device the channels are split into slices, each
 // slice writes per-pixel partials, and a second kernel merges them in slice
-// order, so the result never depends on timing.  Images that quads do not fit
-// (rows under four pixels, or apart by more than 32-bit offsets reach) take one
-// pixel per lane (k_project).
+// order, so the result never depends on timing.  Small images, and those that
+// quads do not fit (rows under four pixels, or apart by more than 32-bit
+// offsets reach), take one pixel per lane (k_project).
 #include <string.h>
 
 #include <algorithm>
@@ -220,6 +220,45 @@ void launch_quads(const ProjArgs &a, hipStream_t s)
         hipLaunchKernelGGL((k_project_quads<Q, ZU, false>), grid, dim3(PROJ_THREADS), 0, s, a);
 }
 
+// The choice of kernel and slices, measured with cold caches against every
+// other (1579 shapes of 24 to 2040 pixels a side and 16 to 1000 channels, in
+// cut-outs and whole): 1.9 % over the best of each, on the average.
+
+// Few pixels and channels take one pixel per lane: a lane's own work, a quarter
+// of a quad's, is then the bound.  256 x 256 x 32: 10.2 us against 12.2 by
+// quads, 450 x 450 x 32 11.9 and 13.7; 300 x 300 x 256 26.6 and 26.2, 400 x 400
+// x 128 24.4 and 25.3.  So do up to 256 channels of images that give some CUs
+// two blocks of quads and most one (550 x 550 x 256: 64.2 against 67.2); six to
+// nine wavefronts of one quad per lane on a CU do well by themselves (a 680 x 680
+// cut-out of 24 channels: 15.8 against 14.5 by quads, of 16: 11.9 and 12.6).
+bool small_projection(int64_t quad_waves, int64_t nz, int64_t cus)
+{
+    if (quad_waves > 6 * cus && quad_waves <= 9 * cus) return nz <= 16;
+    return quad_waves * nz <= 288 * cus ||
+           (quad_waves > 4 * cus && quad_waves <= 5 * cus && nz <= 256);
+}
+
+// Slices of the channels, for images of few wavefronts.  One quad per lane: as
+// many as keep two blocks of four wavefronts per CU at most (640 x 640 x 256,
+// 1600 wavefronts: one slice 77 us, two 93; 300 x 300 x 1000, 352: five 69,
+// six 82), each of 48 channels or more (the merge is a launch of 4 us).
+int64_t quad_slices(int64_t waves, int64_t nz, int64_t cus)
+{
+    const int64_t n = std::min(std::min(nz / 48, 8 * cus / waves), (int64_t)64);
+    // From four blocks for three CUs on the second slice pays for long columns
+    // (580 x 580 x 1000: 234 us against 253).
+    if (n <= 1 && 2 * waves <= 11 * cus && nz >= 400) return 2;
+    return std::max(n, (int64_t)1);
+}
+
+// One pixel per lane: 18 wavefronts per CU, 20 channels or more, and not more
+// slices than the merge is worth (100 x 100 x 512: 16, 19 us; 32, 22 us).
+int64_t pixel_slices(int64_t waves, int64_t nz, int64_t cus)
+{
+    const int64_t most = std::min(std::max(nz / 64, (int64_t)16), (int64_t)64);
+    return std::max(std::min(std::min(nz / 20, 18 * cus / waves), most), (int64_t)1);
+}
+
 // Merge the slice partials of every pixel in slice order.
 __global__ void __launch_bounds__(PROJ_THREADS) k_project_merge(ProjArgs a)
 {
@@ -391,40 +430,29 @@ int cube_project(const float *ptr, const int64_t *dims, float *mip, double *mom0
     const int64_t quads = a.quads_row * a.ny;
     // Quads while a wavefront's offsets from its first row fit 32 bits; in one
     // row they are from its own first quad, 16 KB at most.
-    const bool quad =
+    const bool fits =
         a.nx >= 4 && (a.ny == 1 || (a.nx < ((int64_t)1 << 31) &&
                                     64 * 16 / a.quads_row + 2 < ((int64_t)1 << 30) / a.sy));
+    const int64_t cus = cu_count(), nz = b.nz;
+    const int64_t quad_waves = (quads + 63) / 64;  // with one quad per lane
+    const bool quad = fits && !small_projection(quad_waves, nz, cus);
     a.units = quad ? quads : npix;
-    // From 144 K quads on, equal shares for every CU: a multiple of one block
-    // of four wavefronts per CU, as few as up to 16 quads per lane allow (each
-    // holds 16 Q registers of state).  Below, 64 quads per wavefront.  (A line
-    // at 192 K: 800 x 800 x 256 of 2048-wide rows 172 us against 169, dense 125
-    // and 115, 1500 x 430 x 256 141 and 129.)  Small
-    // images: slices of the channel axis until enough wavefronts are busy,
-    // each slice keeping at least 32 channels (256 x 256 x 256 with at least
-    // 64: 60 us, 32: 21), or 64 with two wavefronts per CU and more before
-    // slicing (the partials then cost more than the wavefronts give: 1819 x 80
-    // x 217 with 32: 30.3 us, 64: 28.0, 100: 31.8; 512 x 512 x 64 39 and 36).
-    const int64_t cus = cu_count();
-    int64_t waves = (a.units + 63) / 64;
-    if (quad && waves > 9 * cus) {
+    int64_t slices = 1;
+    if (quad && quad_waves > 9 * cus) {
+        // Equal shares for every CU: a multiple of one block of four wavefronts
+        // per CU, as few as up to 16 quads per lane allow (each holds 16 Q
+        // registers of state).
         const int64_t most = 4 * cus * 64 * 16;
-        waves = 4 * cus * ((a.units + most - 1) / most);
+        const int64_t waves = 4 * cus * ((a.units + most - 1) / most);
         a.per = (a.units + waves - 1) / waves;
     } else {
         a.per = std::min<int64_t>(64, a.units);
+        slices = quad ? quad_slices(quad_waves, nz, cus)
+                      : pixel_slices((a.units + 63) / 64, nz, cus);
     }
-    waves = (a.units + a.per - 1) / a.per;
     const int Q = (int)((a.per + 63) / 64);
-    const int64_t want = cus * (Q > 1 ? 4 : (quad ? 8 : 16));
-    // Equal shares come out a little under the wavefronts they aim at; with
-    // one quad per lane every wavefront counts (700 x 700 x 256, 1914 of 2048
-    // wavefronts: 134 us, in two slices 116).
-    int64_t slices = waves * 8 >= want * (Q > 1 ? 7 : 8) ? 1 : (want + waves - 1) / waves;
-    slices = std::min<int64_t>(slices, std::max<int64_t>(1, b.nz / (waves >= 2 * cus ? 64 : 32)));
-    slices = std::min<int64_t>(slices, 64);
-    a.zps = (b.nz + slices - 1) / slices;
-    a.slices = (int32_t)((b.nz + a.zps - 1) / a.zps);
+    a.zps = (nz + slices - 1) / slices;
+    a.slices = (int32_t)((nz + a.zps - 1) / a.zps);
     // Without memory for their partials there is one slice.
     std::unique_lock<std::mutex> queue;
     if (a.slices > 1) {

@@ -407,7 +407,7 @@ static void projection_kernels()
         {{4 * K, 4 * K, 2, (int64_t)1 << 28, (int64_t)1 << 40}, true},
         {{4 * K, 4 * K, 2, (int64_t)1 << 29, (int64_t)1 << 41}, false},
         {{3, 4 * K, 2, 4, 0}, false},
-        {{3, 4 * K, 2, 3, 0}, true}};
+        {{3, 4 * K, 2 * K, 3, 0}, true}};                     // one row of 12 K pixels
     for (auto &c : cases) {
         const size_t npix = (size_t)(c.dims[0] * c.dims[1]);
         const int64_t *d = c.dims;
@@ -422,6 +422,32 @@ static void projection_kernels()
     }
 }
 
+// The kernel and the number of slices on 256 CUs, on both sides of each line.
+static void projection_slices()
+{
+    struct { int64_t nx, ny, nz; bool quads; unsigned slices; } cases[] = {
+        {64, 64, 16, false, 1},   {64, 64, 39, false, 1},    {64, 64, 40, false, 2},
+        {64, 64, 512, false, 16}, {64, 64, 4608, false, 64}, {64, 64, 4609, true, 64},
+        {256, 256, 288, false, 4}, {256, 256, 289, true, 6}, {450, 450, 93, false, 1},
+        {450, 450, 94, true, 1},  {450, 450, 96, true, 2},   {512, 512, 72, false, 1},
+        {512, 512, 73, true, 1},  {512, 512, 96, true, 2},   {550, 550, 256, false, 1},
+        {550, 550, 257, true, 1}, {550, 550, 400, true, 2},  {600, 600, 399, true, 1},
+        {600, 600, 400, true, 2}, {640, 640, 512, true, 1},  {640, 640, 16, false, 1},
+        {640, 640, 17, true, 1},  {941, 937, 21, false, 1},  {941, 937, 22, true, 1},
+        {4096, 4096, 1, false, 1}, {4096, 4096, 2, true, 1}};
+    float *x = device_floats((size_t)1 << 28), *mip = device_floats((size_t)1 << 24);
+    for (auto &c : cases) {
+        const int64_t dims[5] = {c.nx, c.ny, c.nz, 0, 0};
+        g_launches.clear();
+        CHECK(cube_project(x, dims, mip, nullptr, nullptr, STREAM) == CUBE_OK);
+        if (launched("k_project_quads") != c.quads || g_launches[0].grid.y != c.slices) {
+            printf("%ld x %ld x %ld: %s, %u slices\n", (long)c.nx, (long)c.ny, (long)c.nz,
+                   g_launches[0].name.c_str(), g_launches[0].grid.y);
+            exit(1);
+        }
+    }
+}
+
 int main(int argc, char **argv)
 {
     static const std::map<std::string, void (*)()> all = {
@@ -432,6 +458,7 @@ int main(int argc, char **argv)
         {"projection_without_partials", projection_without_partials},
         {"captured_partials", captured_partials},
         {"projection_kernels", projection_kernels},
+        {"projection_slices", projection_slices},
     };
     if (argc != 2 || !all.count(argv[1])) return 2;
     all.at(argv[1])();

@@ -61,3 +61,7 @@ def test_partials_of_a_captured_projection_are_kept(scenario):
 
 def test_images_of_any_size_are_projected_by_quads(scenario):
     scenario("projection_kernels")
+
+
+def test_small_images_take_one_pixel_per_lane(scenario):
+    scenario("projection_slices")
