@@ -7,6 +7,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <atomic>
 #include <chrono>
 #include <map>
@@ -611,6 +612,11 @@ int make_plan(const Box &b, bool stats, int hist_kind_req, int nbins, Plan *p, b
             if (root > mid) root = mid;
             if (blocks > root) blocks = root < 1 ? 1 : root;
         }
+        // Rows too short for a float4 are visited one after the other, each at
+        // the latency of its loads: two blocks per CU.
+        if (p->g.row_len < 4)
+            blocks = std::max(blocks, std::min(2ll * cu_count(),
+                                               (long long)(p->g.ny * p->g.nz)));
         if (blocks > cap) blocks = cap;
     }
     if (p->hist == HIST_FINE && blocks > 256) blocks = 256;  // rows of the dump

@@ -776,7 +776,8 @@ int run_bracket(const Box &box, unsigned int n_sample, int mode, uint64_t rank, 
     // the read of 2^23 voxels took 29 us against 19.  Static unless the caller
     // asked for chunks: a region of 941 x 937 x 240 took 237 us, with 2^18-voxel
     // chunks 270.
-    long long blocks = cu_count();
+    // Two for rows under four voxels, which are visited one after the other.
+    long long blocks = cu_count() * (thin_rows(box) ? 2 : 1);
     long long units = blocks;
     if (cl) {
         units = chunks_of(box.n, cl);
@@ -834,9 +835,14 @@ int run_passes(const Box &box, int mode, uint64_t rank, const double *q, int nq,
     // nearly all of a CU's LDS), fewer for small boxes, where clearing and
     // adding up a block's histograms costs more than its share of the scan;
     // for the same reason fewer LDS copies of each.
+    // Rows under four voxels are visited one after the other, each at the
+    // latency of its loads: two blocks per CU (median of a spectrum of 1000
+    // channels of one pixel, by one block 1207 us, by 512 70 us).
     const int cl = scan_chunk_log2(box);
     long long blocks = cu_count();
-    if (cl == 0) {
+    if (cl == 0 && thin_rows(box)) {
+        blocks = std::min(2 * blocks, thin_rows(box));
+    } else if (cl == 0) {
         const long long root = (long long)sqrt((double)box.n) / 16;
         blocks = root < 1 ? 1 : (root < blocks ? root : blocks);
     }

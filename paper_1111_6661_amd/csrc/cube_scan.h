@@ -170,6 +170,15 @@ inline void scan_geom(const Box &b, long long blocks, int threads, Geom *g)
     pack_rows(*g, threads, SEL_U);
 }
 
+// The rows of a box whose rows are too short for a float4 even where they
+// follow each other (pack_rows leaves those as they are); 0 for other boxes.
+inline long long thin_rows(const Box &b)
+{
+    Geom g;
+    collapse(b, &g);
+    return g.row_len < 4 ? g.ny * g.nz : 0;
+}
+
 // The chunk size (log2 voxels; 0: static) of a selection pass over box b:
 // the calling thread's cube_set_partition setting, where automatic means
 // chunks of 2^18 voxels from 2^27 voxels on (as for the histogram passes).

@@ -10,6 +10,7 @@
 #include <string.h>
 #include <sys/mman.h>
 
+#include <algorithm>
 #include <atomic>
 #include <chrono>
 #include <functional>
@@ -448,6 +449,41 @@ static void projection_slices()
     }
 }
 
+// A box of rows under four voxels (a pixel's spectrum) is visited row by row:
+// every pass spreads its rows over the chip.
+static void thin_rows()
+{
+    struct { int64_t nx, ny, nz; } cases[] = {{1, 1, 1000}, {1, 5, 1024}, {2, 200, 200},
+                                              {3, 64, 1000}, {1, 1, 7},    {3, 1, 20000000}};
+    float *x = device_floats((size_t)1 << 32);
+    g_signal = false;    // no kernel runs: the calls end in an error
+    for (auto &c : cases) {
+        const int64_t dims[5] = {c.nx, c.ny, c.nz, 8, 8 * (c.ny + 1)};
+        const double q[3] = {0.1, 0.5, 0.9};
+        double v[3];
+        float f;
+        const unsigned want = (unsigned)std::min<int64_t>(512, c.ny * c.nz);
+        cube_stats_t st;
+        std::vector<uint64_t> counts(1024 + 3);
+        for (int op = 0; op < 5; ++op) {
+            g_launches.clear();
+            if (op == 3) cube_stats_hist(x, dims, -1.f, 1.f, 1024, &st, counts.data());
+            if (op == 4) cube_stats_hist_minmax(x, dims, 64, &st, counts.data());
+            if (op == 0) cube_median(x, dims, v, nullptr);
+            if (op == 1) cube_select(x, dims, 3, &f);
+            if (op == 2) cube_quantiles(x, dims, q, 3, v, nullptr);
+            bool seen = false;
+            for (const Launch &l : g_launches) {
+                const bool pass = l.is_pass || l.name.find("7k_quantI") != std::string::npos ||
+                                  l.name.find("9k_bracketILi2E") != std::string::npos;
+                if (pass) CHECK(l.grid.x >= want);
+                seen |= pass;
+            }
+            CHECK(seen);
+        }
+    }
+}
+
 int main(int argc, char **argv)
 {
     static const std::map<std::string, void (*)()> all = {
@@ -459,6 +495,7 @@ int main(int argc, char **argv)
         {"captured_partials", captured_partials},
         {"projection_kernels", projection_kernels},
         {"projection_slices", projection_slices},
+        {"thin_rows", thin_rows},
     };
     if (argc != 2 || !all.count(argv[1])) return 2;
     all.at(argv[1])();

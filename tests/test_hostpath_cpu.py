@@ -65,3 +65,7 @@ def test_images_of_any_size_are_projected_by_quads(scenario):
 
 def test_small_images_take_one_pixel_per_lane(scenario):
     scenario("projection_slices")
+
+
+def test_rows_under_four_voxels_are_spread_over_the_chip(scenario):
+    scenario("thin_rows")
