@@ -536,13 +536,20 @@ int make_plan(const Box &b, bool stats, int hist_kind_req, int nbins, Plan *p, b
                 // block clears and adds up all of them: 1024 bins of 2^20
                 // noise voxels take 18.3 us with 32 copies, 15.4 with 4 and
                 // 15.2 with 2; 2^26 voxels 56.2 with 32, 54.9 with 8, 55.5
-                // with 2.  Two at least, as skewed data want some (nearly all
-                // voxels in ten bins, 2^23: 8 copies 20.2, 2 copies 21.6).
+                // with 2.  Skewed data want some, the more the larger the
+                // box (one value, 8192 bins, 1 / 2 / 4 copies: 2^23 voxels 61
+                // / 49 / 44 us, 2^26 250 / 141 / 91, 2^28 920 / 485 / 277;
+                // noise 38 / 39 / 42, 72 / 73 / 74, 191 / 189 / 191), so two
+                // at least wherever they fit.  17408 words leave room for the
+                // second block of a shape that has two per CU.
+                const size_t most = automatic && per_cu > 1 ? 17408 : 33792;
                 const size_t words = b.n < ((uint64_t)1 << 22)   ? 4608
-                                     : b.n < ((uint64_t)1 << 26) ? 8704
-                                                                 : 17408;
+                                     : b.n < ((uint64_t)1 << 24) ? 8704
+                                     : b.n < ((uint64_t)1 << 26) ? 17408
+                                                                 : most;
+                const size_t two = b.n < ((uint64_t)1 << 24) ? 8704 : most;
                 while (clog < 3 && (size_t)(nbins + 2) << (clog + 1) <= words) ++clog;
-                if (clog == 0 && (size_t)(nbins + 2) * 2 <= 8704) clog = 1;
+                if (clog == 0 && (size_t)(nbins + 2) * 2 <= two) clog = 1;
             }
             while (clog > 0 && ((size_t)(nbins + 2) << clog) * 4 > LDS_MAX) --clog;
             p->copies_log2 = clog;

@@ -484,6 +484,29 @@ static void thin_rows()
     }
 }
 
+// The copies of an LDS histogram: nearly all voxels in one bin are as slow as
+// that bin's words are few, so large boxes have the copies that fit.
+static void histogram_copies()
+{
+    struct { int lg, bins, copies; } cases[] = {
+        {20, 1024, 4},  {23, 4096, 2},  {23, 8192, 1},  {24, 4096, 4},  {24, 8192, 2},
+        {24, 16384, 2}, {25, 16384, 2}, {26, 1024, 8},  {26, 4096, 8},  {26, 5000, 4},
+        {26, 8192, 4},  {26, 8446, 4},  {26, 8447, 2},  {26, 16384, 2}, {26, 16894, 2},
+        {28, 4096, 8},  {28, 8192, 4},  {28, 16384, 2}, {28, 32768, 1}, {32, 8192, 4}};
+    float *x = device_floats((size_t)1 << 32);
+    for (auto &c : cases)
+        for (int kind : {CUBE_Q_HIST, CUBE_Q_FUSED}) {
+            const int64_t dims[5] = {(int64_t)1 << c.lg, 1, 1, 0, 0};
+            char plan[512], want[32];
+            CHECK(cube_describe_plan(x, dims, kind, c.bins, plan, sizeof plan) == CUBE_OK);
+            snprintf(want, sizeof want, "\"copies\": %d,", c.copies);
+            if (!strstr(plan, want)) {
+                printf("2^%d voxels, %d bins: %s, not %s\n", c.lg, c.bins, plan, want);
+                exit(1);
+            }
+        }
+}
+
 int main(int argc, char **argv)
 {
     static const std::map<std::string, void (*)()> all = {
@@ -496,6 +519,7 @@ int main(int argc, char **argv)
         {"projection_kernels", projection_kernels},
         {"projection_slices", projection_slices},
         {"thin_rows", thin_rows},
+        {"histogram_copies", histogram_copies},
     };
     if (argc != 2 || !all.count(argv[1])) return 2;
     all.at(argv[1])();

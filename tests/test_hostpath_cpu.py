@@ -69,3 +69,7 @@ def test_small_images_take_one_pixel_per_lane(scenario):
 
 def test_rows_under_four_voxels_are_spread_over_the_chip(scenario):
     scenario("thin_rows")
+
+
+def test_histograms_of_large_boxes_have_the_copies_that_fit(scenario):
+    scenario("histogram_copies")
