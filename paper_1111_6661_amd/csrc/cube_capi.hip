@@ -103,6 +103,7 @@ struct Workspace {
     cube_stats_t *d_out = nullptr;
     unsigned long long *d_counts = nullptr;
     HistRange *d_range = nullptr;
+    cube_stats_t *d_stats = nullptr;      // of a min/max call's first pass (after d_range)
     // Results of the synchronous calls: pinned host memory that the kernels
     // write directly (d_*: the same memory as the device sees it).
     cube_stats_t *h_out = nullptr;
@@ -186,6 +187,7 @@ int get_ws(hipStream_t s, Workspace **out)
         return hip_fail(e, "workspace initialisation");
     }
     *w->h_done = 0u;
+    w->d_stats = (cube_stats_t *)((char *)w->d_range + 128);
     g_ws[key] = w;
     *out = w;
     return CUBE_OK;
@@ -728,9 +730,10 @@ PassArgs base_args(const Workspace *w, const Plan &p, int nbins)
 
 // A synchronous call's last pass tells the CPU when its results are there
 // (*done_gen, 0 where it cannot: many bins are finished by a second kernel).
-// Every pass of such a call writes its results through (a.host): the first of
-// a min/max call leaves the statistics, and the second one's word alone would
-// not say that they have arrived.
+// That pass writes all results through (a.host), also the statistics that the
+// first of a min/max call leaves on the device: written by the first, the word
+// of the second would not say that they have arrived, and waiting for them
+// costs that pass 1 us.
 void ask_done(PassArgs &a, Workspace *w, unsigned int *done_gen)
 {
     if (!done_gen || (a.counts && a.nbins >= DEFER_MIN_BINS)) return;
@@ -766,15 +769,15 @@ int run_async(Op op, const float *ptr, const int64_t *dims, float lo, float hi, 
         hipError_t e = hipGetLastError();
         return e == hipSuccess ? CUBE_OK : hip_fail(e, "empty-box launch");
     }
-    const int32_t host = done_gen != nullptr;
+    const bool host = done_gen != nullptr;
     std::lock_guard<std::mutex> lk(w->queue);
     Plan p;
     const bool dump = op != OP_STATS && wants_dump(nbins, b.n) && have_dump(w, s);
     if (op == OP_STATS || op == OP_MINMAX) {
         if ((rc = make_plan(b, true, 0, nbins, &p, false))) return rc;
         PassArgs a = base_args(w, p, nbins);
-        a.out = dev_out;
-        a.host = host;
+        a.out = host && op == OP_MINMAX ? w->d_stats : dev_out;
+        a.host = host && op == OP_STATS;
         if (op == OP_MINMAX) {
             a.want_range = 1;
             a.out_range = w->d_range;
@@ -788,6 +791,10 @@ int run_async(Op op, const float *ptr, const int64_t *dims, float lo, float hi, 
         a2.dev_range = w->d_range;
         a2.counts = dev_counts;
         a2.host = host;
+        if (host) {
+            a2.out = dev_out;
+            a2.stats_in = w->d_stats;
+        }
         ask_done(a2, w, done_gen);
         return launch(a2, p2, false, w, s);
     }

@@ -1197,6 +1197,16 @@ __device__ __forceinline__ void store_result(T *dst, T v)
         *dst = v;
 }
 
+// The statistics that an earlier pass left in device memory, to the host with
+// this pass's own results (called by every thread of the block).
+__device__ __forceinline__ void forward_stats(const cube_stats_t *from, cube_stats_t *to)
+{
+    constexpr int words = (int)(sizeof(cube_stats_t) / 8);
+    if ((int)threadIdx.x < words)
+        store_result<true>(reinterpret_cast<unsigned long long *>(to) + threadIdx.x,
+                           reinterpret_cast<const unsigned long long *>(from)[threadIdx.x]);
+}
+
 // Tell the polling CPU that the block's results are in host memory: every
 // thread has waited for its own write-through stores before the barrier.
 __device__ __forceinline__ void tell_host(unsigned int *done, unsigned int gen)
@@ -1278,8 +1288,6 @@ __device__ void finish_stats(const R *recs, int n_recs, int accum_mode,
         const unsigned long long *w = reinterpret_cast<const unsigned long long *>(&o);
         for (int i = 0; i < (int)(sizeof o / 8); ++i)
             store_result<true>(reinterpret_cast<unsigned long long *>(out) + i, w[i]);
-        // A min/max call's record is there before its second pass begins.
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     } else {
         *out = o;
     }

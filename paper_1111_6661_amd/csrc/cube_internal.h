@@ -92,6 +92,7 @@ struct PassArgs {
     int32_t n_chunks;            // 0: static partition; else chunks claimed at run time
     unsigned int *dump;          // a row of counts per block; null: atomics on hist_acc
     int32_t defer_bins;          // the bins are left to launch_hist_sum after the pass
+    const cube_stats_t *stats_in;  // a histogram pass's: an earlier one's, for `out` (host)
     int32_t host;                // `out` and `counts` are host memory: written through
     unsigned int done_gen;       // written to *done (host memory too) once the results
     unsigned int *done;          // are there (with `host`); null: not wanted

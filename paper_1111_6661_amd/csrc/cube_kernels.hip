@@ -97,6 +97,7 @@ __global__ void __launch_bounds__(1024) k_pass(PassArgs a)
                                         out, out_range, a.nbins, nv, below, above,
                                         a.host != 0);
     } else {
+        if (a.stats_in) forward_stats(a.stats_in, a.out);
         const BlockSums S = merge_counts<ChunkRec>(brecs, (int)gridDim.x);
         nv = S.nv;
         below = S.below;
@@ -220,6 +221,7 @@ __global__ void __launch_bounds__(1024) k_pass_dyn(PassArgs a)
                                     a.want_range ? a.out_range : nullptr, a.nbins, nv, below,
                                     above, a.host != 0);
     } else {
+        if (a.stats_in) forward_stats(a.stats_in, a.out);
         const BlockSums S = merge_counts<ChunkRec>(recs, nc);
         nv = S.nv;
         below = S.below;

@@ -273,35 +273,47 @@ static bool pinned(const void *p)
     return it != g_pinned.begin() && (uintptr_t)p < (--it)->first + it->second;
 }
 
-// Whatever a synchronous call's passes leave in host memory is written through.
+// Whatever a synchronous call's passes leave in host memory is written through,
+// by the pass that says that it is done; a min/max call's first pass leaves its
+// statistics on the device for the second.
 static void host_results()
 {
     const int64_t n = 1 << 21, dims[5] = {n, 1, 1, 0, 0};
     float *x = device_floats(n);
     cube_stats_t st;
     std::vector<uint64_t> c(65536 + 3);
-    int results = 0;
+    int results = 0, forwarded = 0;
     for (int bins : {64, 8191, 8192, 65536}) {
         g_launches.clear();
         CHECK(cube_stats(x, n, 1, 1, nullptr, &st) == CUBE_OK);
         CHECK(cube_hist(x, dims, -1.f, 1.f, bins, c.data()) == CUBE_OK);
         CHECK(cube_stats_hist(x, dims, -1.f, 1.f, bins, &st, c.data()) == CUBE_OK);
         CHECK(cube_stats_hist_minmax(x, dims, bins, &st, c.data()) == CUBE_OK);
+        const PassArgs *first = nullptr;
         for (const Launch &l : g_launches) {
             if (!l.is_pass) continue;
             const bool host = pinned(l.pass.out) || pinned(l.pass.counts);
-            CHECK(host && l.pass.host);
+            CHECK(host == (l.pass.host != 0) && (host || !l.pass.done));
             CHECK(!l.pass.done || pinned(l.pass.done));
-            ++results;
+            if (first) {
+                CHECK(l.pass.stats_in == first->out && pinned(l.pass.out));
+                ++forwarded;
+            } else {
+                CHECK(!l.pass.stats_in);
+            }
+            first = host ? nullptr : &l.pass;
+            results += host;
         }
-        // Only results, never the device's own words.
+        CHECK(!first);
+        // Stream-ordered: device memory, nothing forwarded.
         g_launches.clear();
         cube_stats_t *d_out = (cube_stats_t *)take(sizeof st);
         uint64_t *d_c = (uint64_t *)take((bins + 3) * 8);
         CHECK(cube_stats_hist_minmax_async(x, dims, bins, d_out, d_c, nullptr) == CUBE_OK);
-        for (const Launch &l : g_launches) CHECK(!l.is_pass || (!l.pass.host && !l.pass.done));
+        for (const Launch &l : g_launches)
+            CHECK(!l.is_pass || (!l.pass.host && !l.pass.done && !l.pass.stats_in));
     }
-    CHECK(results == 4 * 5);
+    CHECK(results == 4 * 4 && forwarded == 4);
 }
 
 // A stream that completes without the pass's word: an error, not the results

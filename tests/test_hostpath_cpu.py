@@ -38,8 +38,8 @@ def test_calls_that_share_a_stream_keep_their_launches_together(scenario):
 
 
 def test_results_in_host_memory_are_written_through(scenario):
-    """Also those of a min/max call's first pass, which the CPU reads when the
-    second pass says that it is done."""
+    """Also those of a min/max call's first pass, by the second, which says that
+    it is done."""
     scenario("host_results")
 
 
