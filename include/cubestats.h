@@ -323,10 +323,29 @@ CUBE_API int cube_quantiles(const float *ptr, const int64_t *dims, const double 
 /*
  * Number of passes (3 or 4, see cube_quantiles) of the CALLING THREAD's last
  * successful cube_quantiles call, each a read of the box unless it reads
- * copied voxels or a sample gave a bracket (counted as 3); 0 before the
- * thread's first successful call.  Never fails.
+ * copied voxels or a sample gave a bracket (counted as 3; a single read that
+ * missed is not counted, cube_last_rank_route tells); 0 before the thread's
+ * first successful call.  Never fails.
  */
 CUBE_API int cube_last_quantile_reads(void);
+
+/*
+ * How the CALLING THREAD's last successful cube_select, cube_median or
+ * cube_quantiles call found its ranks, for measurements: a sum of
+ *   CUBE_RANK_BRACKET   a sample gave a bracket, and one read found the ranks;
+ *   CUBE_RANK_MISSED    the sample was no help (too few valid voxels in it, too
+ *                       many in its bracket, or ranks outside), and the passes
+ *                       followed;
+ *   CUBE_RANK_COPIES    the last pass read copied voxels instead of the box;
+ *   CUBE_RANK_OVERFLOW  a block's copies did not fit, so the last pass read the
+ *                       box.
+ * 0: every pass read the box, or no call yet.  Never fails.
+ */
+#define CUBE_RANK_BRACKET 1
+#define CUBE_RANK_MISSED 2
+#define CUBE_RANK_COPIES 4
+#define CUBE_RANK_OVERFLOW 8
+CUBE_API int cube_last_rank_route(void);
 
 /*
  * Projections along the channel axis z: the maps a viewer of spectral cubes

@@ -49,6 +49,7 @@ class cube_stats_t(C.Structure):
 assert C.sizeof(cube_stats_t) == 64
 
 CUBE_Q_STATS, CUBE_Q_HIST, CUBE_Q_FUSED, CUBE_Q_MINMAX = 0, 1, 2, 3
+CUBE_RANK_BRACKET, CUBE_RANK_MISSED, CUBE_RANK_COPIES, CUBE_RANK_OVERFLOW = 1, 2, 4, 8
 CUBE_ORDER_LARGEST_FIRST, CUBE_ORDER_SMALLEST_FIRST = 0, 1
 
 
@@ -142,6 +143,8 @@ def load() -> C.CDLL:
     lib.cube_quantiles.restype = C.c_int
     lib.cube_last_quantile_reads.argtypes = []
     lib.cube_last_quantile_reads.restype = C.c_int
+    lib.cube_last_rank_route.argtypes = []
+    lib.cube_last_rank_route.restype = C.c_int
     lib.cube_autotune.argtypes = [P, I64P, i32, f32, f32, i32, i32, C.c_char_p, C.c_size_t]
     lib.cube_autotune.restype = C.c_int
     lib.cube_autotune_batch.argtypes = [C.POINTER(cube_query_t), i32, i32, C.c_char_p, C.c_size_t]
@@ -318,6 +321,12 @@ def cube_last_quantile_reads() -> int:
     """Passes of this thread's last successful quantiles call (each a read of the
     box unless the last reads copied voxels)."""
     return int(load().cube_last_quantile_reads())
+
+
+def cube_last_rank_route() -> int:
+    """How this thread's last successful select, median or quantiles call found
+    its ranks: a sum of CUBE_RANK_* (0: every pass read the box)."""
+    return int(load().cube_last_rank_route())
 
 
 def select(t, rank: int) -> float:

@@ -49,6 +49,8 @@ namespace cube {
 
 // Passes of the calling thread's last successful cube_quantiles call.
 thread_local int g_quant_reads = 0;
+// CUBE_RANK_* of its last successful selection, median or quantiles call.
+thread_local int g_rank_route = 0;
 
 namespace {
 
@@ -82,6 +84,7 @@ struct RankOut {
     unsigned int done;           // the call's number, written last
     int status;                  // 0, or 1: rank >= n_valid, 2: no valid voxel
     int m, wide;
+    int route;                   // CUBE_RANK_COPIES or CUBE_RANK_OVERFLOW
     unsigned long long n_valid;
     unsigned int key[Q_MAX_RANKS];
 };
@@ -449,6 +452,9 @@ __device__ void rank_end(const RankArgs &a, RankShared &s, unsigned int *scratch
             st->done = 1;
             store_result<true>(&a.out->m, m);
             store_result<true>(&a.out->wide, wide);
+            store_result<true>(&a.out->route, !st->collect     ? 0
+                                              : st->overflow ? CUBE_RANK_OVERFLOW
+                                                             : CUBE_RANK_COPIES);
             store_result<true>(&a.out->status, 0);
         }
         tell_host(&a.out->done, a.gen);
@@ -806,15 +812,18 @@ int run_bracket(const Box &box, unsigned int n_sample, int mode, uint64_t rank, 
     const RankOut &o = *w->h_out;
     *n_valid = o.n_valid;
     *status = o.status;
-    if (!o.status) keys->assign(o.key, o.key + o.m);
+    if (!o.status) {
+        g_rank_route = CUBE_RANK_BRACKET;
+        keys->assign(o.key, o.key + o.m);
+    }
     return CUBE_OK;
 }
 
 // Queue the passes on the null stream and wait for the result.  `keys`: the
-// keys of the ranks, ascending.
+// keys of the ranks, ascending; `missed`: CUBE_RANK_MISSED after a single read.
 int run_passes(const Box &box, int mode, uint64_t rank, const double *q, int nq,
-               QuantWorkspace *w, std::vector<unsigned int> *keys, uint64_t *n_valid, int *status,
-               int *wide)
+               int missed, QuantWorkspace *w, std::vector<unsigned int> *keys, uint64_t *n_valid,
+               int *status, int *wide)
 {
     RankArgs a;
     memset(&a, 0, sizeof a);
@@ -872,6 +881,7 @@ int run_passes(const Box &box, int mode, uint64_t rank, const double *q, int nq,
     *status = o.status;
     if (o.status) return CUBE_OK;
     *wide = o.wide;
+    g_rank_route = missed | o.route;
     keys->assign(o.key, o.key + o.m);
     return CUBE_OK;
 }
@@ -889,7 +899,7 @@ int run_ranks(const Box &box, int mode, uint64_t rank, const double *q, int nq,
         rc = run_bracket(box, n_sample, mode, rank, nq ? q[0] : 0.0, w, keys, n_valid, status);
         if (rc || *status != RANK_MISSED) return rc;
     }
-    return run_passes(box, mode, rank, q, nq, w, keys, n_valid, status, wide);
+    return run_passes(box, mode, rank, q, nq, n_sample ? CUBE_RANK_MISSED : 0, w, keys, n_valid, status, wide);
 }
 
 }  // namespace
@@ -976,5 +986,7 @@ int cube_quantiles(const float *ptr, const int64_t *dims, const double *q, int32
 }
 
 int cube_last_quantile_reads(void) { return g_quant_reads; }
+
+int cube_last_rank_route(void) { return g_rank_route; }
 
 }  // extern "C"
