@@ -9,7 +9,7 @@
 // copies.  All of it is exact: the counts of the full read say whether the
 // ranks do lie in the bracket, and if they don't, or the copies don't fit, the
 // caller goes on with the passes over the box (status RANK_MISSED).  A bracket
-// of at most 256 keys (a value held by many voxels) needs no copies.
+// of at most 512 keys (a value held by many voxels) needs no copies.
 //
 // Five launches, queued at once; each pass's last block finds the bins of the
 // ranks and lays out the next pass.
@@ -33,6 +33,7 @@ constexpr int BR_BINS_LOG2 = 12;   // bits of a pass, but for the read of the bo
 // (at about 23 G atomics/s), so few; the copies' passes have 12 bits each for
 // the other 24.
 constexpr int BR_BOX_LOG2 = 8;
+constexpr int BR_BOX_ALL = 9;      // a bracket of at most 2^9 keys is binned whole: both zeros' groups
 // The copied voxels' room is handed out in pieces, to a wavefront as it fills
 // the one before: a box whose wanted voxels lie together fits as any other
 // does (a region for each block would not hold them).  Every wavefront has
@@ -242,7 +243,7 @@ __device__ __forceinline__ void bracket_next(const BracketArgs &a, BracketShared
             st->lo = __uint_as_float(klo & 0x80000000u ? klo ^ 0x80000000u : ~klo);
             st->hi = __uint_as_float(khi & 0x80000000u ? khi ^ 0x80000000u : ~khi);
             st->base = klo;
-            bits = w < BR_BOX_LOG2 ? w : BR_BOX_LOG2;
+            bits = w <= BR_BOX_ALL ? w : BR_BOX_LOG2;
             next = w - bits;
             st->collect = next > 0 ? 1 : 0;
             st->pieces = 0u;

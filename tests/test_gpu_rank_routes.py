@@ -11,7 +11,7 @@ from tests.test_gpu_bracket import N, _fill
 
 pytestmark = pytest.mark.gpu
 
-HIT = ["noise", "offset", "constant", "levels", "blanks", "ramp", "period", "tiny"]
+HIT = ["noise", "offset", "constant", "levels", "zeros", "blanks", "ramp", "period", "tiny"]
 # Half of the box in one value at one end of the bracket, or in both infinities
 # around it: more than there is room to copy.
 MISS = ["sampled", "few", "edge", "infinite"]
@@ -32,6 +32,19 @@ def test_single_read(name):
     assert cs.cube_last_quantile_reads() == 3
     cs.quantiles(x, [0.25, 0.5])          # more than one level: the passes
     assert cs.cube_last_rank_route() & known == 0
+
+
+def test_one_zero_held_by_most_voxels():
+    """The bracket takes both zeros, also where there is one only."""
+    x = _fill("noise", torch.Generator(device="cuda").manual_seed(5))
+    for zero in (0.0, -0.0):
+        y = torch.where(x.abs() < 1.0, torch.full_like(x, zero), x)
+        m, n = cs.median(y)
+        assert m == 0.0 and n == N
+        assert cs.cube_last_rank_route() == cs.CUBE_RANK_BRACKET
+        got = cs.select(y, N // 2)
+        assert got == 0.0 and str(got) == str(zero)
+        assert cs.cube_last_rank_route() == cs.CUBE_RANK_BRACKET
 
 
 def test_small_boxes_take_the_passes():
