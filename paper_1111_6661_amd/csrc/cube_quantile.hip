@@ -18,8 +18,10 @@
 // wanted prefixes falls through to 0 with no test: the table of the top 12
 // key bits gives its index among the wanted 12-bit prefixes, each further
 // table, indexed by that entry and the level's next key bits, its index
-// among the longer prefixes.  Only voxels that end at a wanted prefix count
-// (histogram row 0 is laid out but never written).  No search.
+// among the longer prefixes.  Only voxels that end at a wanted prefix count, in
+// the row of its index.  No search.  (Without a row for entry 0 one prefix has
+// room for twice the LDS copies of its 4096 bins: one value in 2^28 voxels,
+// three levels, 650 -> 563 us.)
 //
 // The host queues all the passes at once.  The last block of each adds up that
 // pass's histograms, finds the bin of every rank, and lays out the next pass:
@@ -558,14 +560,13 @@ __global__ void __launch_bounds__(Q_THREADS) k_quant(RankArgs a)
         from_cand = NL > 1 && cs->collect == NL - 1 && cs->overflow == 0u;
     }
     const int nbins = 1 << width;
-    const int rows = NL == 0 ? 1 : slots + 1;   // after the first pass, row 0 is unused
     const int tab_words = NL == 0 ? 0 : (4096 + (NL >= 2 ? t2_bytes : 0) +
                                          (NL >= 3 ? t3_bytes : 0)) / 4;
     int clog = 0;
     while (clog < a.max_clog &&
-           (unsigned int)((((rows * nbins) << (clog + 1)) + tab_words) * 4) <= a.lds_bytes)
+           (unsigned int)((((slots * nbins) << (clog + 1)) + tab_words) * 4) <= a.lds_bytes)
         ++clog;
-    const int words = (rows * nbins) << clog;
+    const int words = (slots * nbins) << clog;
     for (int i = tid; i < words; i += B) lds[i] = 0u;
     // The tables follow the histograms in LDS (all sizes are multiples of 4).
     unsigned int *tw = lds + words;
@@ -588,7 +589,8 @@ __global__ void __launch_bounds__(Q_THREADS) k_quant(RankArgs a)
     st.wb = width;
     st.bmask = (unsigned int)nbins - 1u;
     st.clog = clog;
-    st.cbase = tid & 63 & ((1 << clog) - 1);
+    // A prefix's row is its table entry less one.
+    st.cbase = (tid & 63 & ((1 << clog) - 1)) - (NL == 0 ? 0 : nbins << clog);
     st.valid = 0u;
     st.collect = collect;
     st.cand = a.cand + (size_t)blockIdx.x * a.cand_cap;
@@ -612,13 +614,11 @@ __global__ void __launch_bounds__(Q_THREADS) k_quant(RankArgs a)
     // Every lane of a wavefront holds the same count (sums of ballots).
     if (NL == 0 && (tid & 63) == 0 && st.valid) atomicAdd(&s_valid, st.valid);
     __syncthreads();
-    // Flush the histograms (after the first pass, rows 1..: row 0 is
-    // never written).
+    // Flush the histograms.
     const int C = 1 << clog;
-    const int first = NL == 0 ? 0 : nbins;
     for (int b = tid; b < slots * nbins; b += B) {
         unsigned int sum = 0;
-        for (int c = 0; c < C; ++c) sum += lds[((b + first) << clog) + ((c + tid) & (C - 1))];
+        for (int c = 0; c < C; ++c) sum += lds[(b << clog) + ((c + tid) & (C - 1))];
         if (sum) atomicAdd(&a.acc[b], (unsigned long long)sum);
     }
     if (tid == 0) {
