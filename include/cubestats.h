@@ -215,7 +215,8 @@ CUBE_API int cube_set_launch(int32_t threads, int32_t blocks, int32_t hist_copie
  *                   atomics on a skewed histogram, a few more scalar
  *                   instructions per voxel otherwise.
  * Counts are identical in every form.  Histograms of more than 32768 bins
- * use global atomics whatever the form.  Returns the previous form of the
+ * take 16-bit LDS counters, or global atomics (fewer than 2^20 voxels, an
+ * explicit grid, cube_stats_hist_noalloc), whatever the form.  Returns the previous form of the
  * thread, or CUBE_EINVAL for an unknown one.
  */
 #define CUBE_HIST_AUTO 0
@@ -413,8 +414,15 @@ CUBE_API void cube_tune_clear(void);
  * with each).  The library stays usable; workspaces are made again on demand. */
 CUBE_API void cube_shutdown(void);
 
-/* The single-box calls keep one workspace (about 2 MiB of device and pinned
- * memory) per (device, stream) they were given, until cube_shutdown.  Call
+/* The single-box calls keep one workspace (about 5 MiB of device and pinned
+ * memory) per (device, stream) they were given, until cube_shutdown.  The
+ * first histogram of many bins adds 32 MiB of device memory for the blocks'
+ * counts: more than 32768 bins of 2^20 voxels or more, 16384 to 32768 bins, or
+ * from 8192 on of 2^24 voxels or fewer, where the launch shape suits it.  It
+ * is not made while the stream captures: a captured pass of that kind takes
+ * global atomics instead (above 32768 bins one per voxel, some 40 times
+ * slower) unless a call of that kind was made on the stream before; so queue
+ * one first.  Call
  * this before destroying a stream that was passed to them: it waits for the
  * stream's last call and frees its workspaces (a later call on the same
  * stream makes a new one).  Not concurrently with calls on that stream.  A

@@ -486,7 +486,7 @@ static Shape default_shape(bool hist, uint64_t n, bool short_rows)
     return {512, 2, 1, 19};
 }
 
-int make_plan(const Box &b, bool stats, int hist_kind_req, int nbins, Plan *p, bool dump)
+int make_plan(const Box &b, bool stats, int hist_kind_req, int nbins, Plan *p, bool fine)
 {
     collapse(b, &p->g);
     int threads = g_threads, unroll = g_unroll, copies_req = g_copies;
@@ -520,7 +520,7 @@ int make_plan(const Box &b, bool stats, int hist_kind_req, int nbins, Plan *p, b
     p->copies_log2 = 0;
     if (hist_kind_req) {
         if (nbins > 32768) {
-            p->hist = dump && g_blocks == 0 && b.n >= FINE_MIN_VOXELS ? HIST_FINE : HIST_GLOBAL;
+            p->hist = fine && g_blocks == 0 && b.n >= FINE_MIN_VOXELS ? HIST_FINE : HIST_GLOBAL;
             // One block fills a CU's LDS, so it takes all the CU's wavefronts;
             // four vectors per lane and tile spill beside the counters' words.
             if (p->hist == HIST_FINE && automatic) {
@@ -693,16 +693,23 @@ __global__ void k_write_empty(cube_stats_t *out, unsigned long long *counts, int
 // atomics / rows) 8192 bins: 2^20 voxels 36.8 / 30.2, 2^24 56.8 / 51.7, 2^26
 // 77.8 / 85.1; 16384 bins: 49.0 / 34.4, 75.7 / 56.7, 94.4 / 89.7; 2048 bins:
 // 23.2 / 24.2, 41.8 / 43.2, 72.4 / 80.7.
-bool wants_dump(int nbins, uint64_t n)
+bool wants_rows(int nbins, uint64_t n)
 {
     return nbins >= 16384 || (nbins >= DEFER_MIN_BINS && n <= ((uint64_t)1 << 24));
+}
+
+// Whether a pass may take 16-bit counters: its box and grid suit them, and the
+// rows that its blocks write are there (made now if need be).
+bool have_fine(int nbins, uint64_t n, Workspace *w, hipStream_t s)
+{
+    return nbins > 32768 && n >= FINE_MIN_VOXELS && g_blocks == 0 && have_dump(w, s);
 }
 
 int launch(PassArgs a, const Plan &p, bool stats, Workspace *w, hipStream_t s)
 {
     if (p.hist == HIST_FINE ||
-        (p.hist == HIST_LDS && wants_dump(a.nbins, a.g.n_total) && w->dump &&
-         (size_t)p.blocks * (size_t)a.nbins * 4 <= DUMP_BYTES))
+        (p.hist == HIST_LDS && wants_rows(a.nbins, a.g.n_total) &&
+         (size_t)p.blocks * (size_t)a.nbins * 4 <= DUMP_BYTES && have_dump(w, s)))
         a.dump = w->dump;
     a.defer_bins = a.dump || (p.hist != HIST_NONE && a.nbins >= DEFER_MIN_BINS) ? 1 : 0;
     hipError_t e =
@@ -772,7 +779,7 @@ int run_async(Op op, const float *ptr, const int64_t *dims, float lo, float hi, 
     const bool host = done_gen != nullptr;
     std::lock_guard<std::mutex> lk(w->queue);
     Plan p;
-    const bool dump = op != OP_STATS && wants_dump(nbins, b.n) && have_dump(w, s);
+    const bool fine = op != OP_STATS && have_fine(nbins, b.n, w, s);
     if (op == OP_STATS || op == OP_MINMAX) {
         if ((rc = make_plan(b, true, 0, nbins, &p, false))) return rc;
         PassArgs a = base_args(w, p, nbins);
@@ -786,7 +793,7 @@ int run_async(Op op, const float *ptr, const int64_t *dims, float lo, float hi, 
         if ((rc = launch(a, p, true, w, s))) return rc;
         if (op == OP_STATS) return CUBE_OK;
         Plan p2;
-        if ((rc = make_plan(b, false, 1, nbins, &p2, dump))) return rc;
+        if ((rc = make_plan(b, false, 1, nbins, &p2, fine))) return rc;
         PassArgs a2 = base_args(w, p2, nbins);
         a2.dev_range = w->d_range;
         a2.counts = dev_counts;
@@ -799,7 +806,7 @@ int run_async(Op op, const float *ptr, const int64_t *dims, float lo, float hi, 
         return launch(a2, p2, false, w, s);
     }
     const bool stats = op == OP_FUSED;
-    if ((rc = make_plan(b, stats, 1, nbins, &p, dump))) return rc;
+    if ((rc = make_plan(b, stats, 1, nbins, &p, fine))) return rc;
     PassArgs a = base_args(w, p, nbins);
     a.range = range;
     a.out = dev_out;
@@ -819,8 +826,8 @@ int run_pass(const Box &b, bool stats, bool hist, int nbins, const HistRange &ra
     if (rc) return rc;
     std::lock_guard<std::mutex> lk(w->queue);
     Plan p;
-    const bool dump = hist && wants_dump(nbins, b.n) && have_dump(w, s);
-    if ((rc = make_plan(b, stats, hist ? 1 : 0, nbins, &p, dump))) return rc;
+    const bool fine = hist && have_fine(nbins, b.n, w, s);
+    if ((rc = make_plan(b, stats, hist ? 1 : 0, nbins, &p, fine))) return rc;
     PassArgs a = base_args(w, p, nbins);
     a.range = range;
     a.dev_range = dev_range;

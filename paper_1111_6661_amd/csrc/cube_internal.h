@@ -191,9 +191,9 @@ void get_launch(int *threads, int *blocks, int *copies, int *unroll);
 // The launch shape of one pass over a validated box: statistics (`stats`)
 // and/or a histogram (hist_kind_req 1) of nbins bins; the explicit shape of
 // cube_set_launch, else the tuned one, else the default rules.
-// `dump`: the caller has a buffer for the blocks' rows of counts (without it
+// `fine`: the caller has a buffer for the blocks' rows of counts (without it
 // more than 32768 bins take global atomics).
-int make_plan(const Box &b, bool stats, int hist_kind_req, int nbins, Plan *p, bool dump);
+int make_plan(const Box &b, bool stats, int hist_kind_req, int nbins, Plan *p, bool fine);
 // Cut the rows of a collapsed box into segments so that there are at least
 // `blocks` work units (a row is never cut below 4 floats).
 void cut_rows(Geom &g, long long blocks);

@@ -519,6 +519,51 @@ static void histogram_copies()
         }
 }
 
+// The blocks' rows of counts (32 MiB) are allocated by the first pass that
+// writes them, and by no other.
+static void rows_memory()
+{
+    const size_t rows = (size_t)32 << 20;
+    const int64_t small[5] = {(1 << 20) - 1, 1, 1, 0, 0}, large[5] = {1 << 20, 1, 1, 0, 0},
+                  huge[5] = {(1 << 24) + 1, 1, 1, 0, 0};
+    float *x = device_floats((1 << 24) + 1);
+    cube_stats_t *out = (cube_stats_t *)take(sizeof *out);
+    uint64_t *c = (uint64_t *)take((65536 + 3) * 8);
+    auto has = [&] {
+        return std::count(g_mallocs.begin(), g_mallocs.end(), rows) != 0;
+    };
+    auto hist = [&](const int64_t *dims, int bins, bool fused) {
+        g_launches.clear();
+        CHECK((fused ? cube_stats_hist_async(x, dims, -1.f, 1.f, bins, out, c, STREAM)
+                     : cube_hist_async(x, dims, -1.f, 1.f, bins, c, STREAM)) == CUBE_OK);
+        CHECK(g_launches[0].is_pass);
+        return g_launches[0].pass.dump != nullptr;
+    };
+    for (bool fused : {false, true}) {
+        CHECK(!hist(large, 8191, fused) && !hist(huge, 8192, fused) && !hist(huge, 16383, fused));
+        CHECK(!hist(small, 32769, fused) && !hist(small, 65536, fused) && !has());
+        CHECK(cube_set_launch(0, 64, 0, 0) == CUBE_OK);       // an explicit grid
+        CHECK(!hist(large, 65536, fused) && !has());
+        CHECK(cube_set_launch(0, 4096, 0, 0) == CUBE_OK);     // more rows than there is room for
+        CHECK(!hist(large, 16384, fused) && !has());
+        CHECK(cube_set_launch(0, 0, 0, 0) == CUBE_OK);
+        cube_set_hist_mode(CUBE_HIST_HOT);
+        CHECK(!hist(large, 8192, fused) && !has());
+        cube_set_hist_mode(CUBE_HIST_AUTO);
+        g_capturing = true;
+        CHECK(!hist(large, 8192, fused) && !hist(large, 65536, fused) && !has());
+        g_capturing = false;
+        CHECK(hist(large, fused ? 65536 : 8192, fused) && has());
+        g_mallocs.clear();
+        CHECK(hist(large, 8192, fused) && hist(large, 65536, fused) && hist(huge, 16384, fused));
+        g_capturing = true;
+        CHECK(hist(large, 8192, fused) && hist(large, 65536, fused) && !has());
+        g_capturing = false;
+        cube_release_stream(STREAM);
+        g_mallocs.clear();
+    }
+}
+
 int main(int argc, char **argv)
 {
     static const std::map<std::string, void (*)()> all = {
@@ -532,6 +577,7 @@ int main(int argc, char **argv)
         {"projection_slices", projection_slices},
         {"thin_rows", thin_rows},
         {"histogram_copies", histogram_copies},
+        {"rows_memory", rows_memory},
     };
     if (argc != 2 || !all.count(argv[1])) return 2;
     all.at(argv[1])();

@@ -73,3 +73,7 @@ def test_rows_under_four_voxels_are_spread_over_the_chip(scenario):
 
 def test_histograms_of_large_boxes_have_the_copies_that_fit(scenario):
     scenario("histogram_copies")
+
+
+def test_rows_of_counts_are_allocated_where_they_are_written(scenario):
+    scenario("rows_memory")
