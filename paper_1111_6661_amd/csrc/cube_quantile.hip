@@ -25,9 +25,9 @@
 //
 // The host queues all the passes at once.  The last block of each adds up that
 // pass's histograms, finds the bin of every rank, and lays out the next pass:
-// its prefixes, tables and bits (cube_quantile_plan.h holds the same plan in
-// plain C++).  The last pass's last block writes the ranks' keys to host
-// memory.  When the voxels under the wanted prefixes are few enough, the last
+// its prefixes, tables and bits (by the functions of cube_quantile_plan.h, which
+// also holds the same plan for the host).  The last pass's last block writes
+// the ranks' keys to host memory.  When the voxels under the wanted prefixes are few enough, the last
 // pass but one also copies them out, and the last reads only the copies.
 //
 // Measured (call, microseconds; before: the host read every pass's counts
@@ -58,10 +58,10 @@ namespace {
 
 constexpr int Q_THREADS = 1024;
 constexpr int Q_MAX_RANKS = 2 * CUBE_MAX_QUANTILES;   // index + 1 fits a byte
-constexpr size_t Q_LDS = 152 * 1024;        // dynamic LDS of one block at most
-constexpr int Q_ACC = 32768;                // slots << bin width never exceeds this
+constexpr size_t Q_LDS = QP_LDS;            // dynamic LDS of one block at most
+constexpr int Q_ACC = QP_COUNTERS;          // slots << bin width never exceeds this
 constexpr size_t Q_TAB = QP_TAB_MAX;        // bytes: T1, T2, T3 at most
-constexpr int Q_WIDE_BUCKETS = 8, Q_WIDE_RANKS = 96;
+static_assert(Q_MAX_RANKS == QP_RANKS, "a table entry is a byte");
 // Copied voxels: 2^24 floats (64 MiB) shared out among the blocks.
 constexpr unsigned int CAND_TOTAL = 1u << 24;
 
@@ -158,18 +158,18 @@ struct QuantStep {
             if (NL >= 2) {
 #pragma unroll
                 for (int j = 0; j < NV; ++j)
-                    g[j] = t2[(g[j] << w2) | __builtin_amdgcn_ubfe(k[j], 20 - w2, w2)];
+                    g[j] = t2[qp_entry(g[j], k[j], 20 - w2, w2)];
             }
             if (NL >= 3) {
 #pragma unroll
                 for (int j = 0; j < NV; ++j)
-                    g[j] = t3[(g[j] << w3) | __builtin_amdgcn_ubfe(k[j], 20 - w2 - w3, w3)];
+                    g[j] = t3[qp_entry(g[j], k[j], 20 - w2 - w3, w3)];
             }
 #pragma unroll
             for (int j = 0; j < NV; ++j) {
                 const unsigned int idx =
-                    (g[j] << wb) | (NL >= 2 ? __builtin_amdgcn_ubfe(k[j], shift, wb)
-                                            : (k[j] >> shift) & bmask);
+                    NL >= 2 ? qp_entry(g[j], k[j], shift, wb)
+                            : (g[j] << wb) | ((k[j] >> shift) & bmask);
                 if (x[j] == x[j] && g[j] != 0u) atomicAdd(&lds[(idx << clog) + cbase], 1u);
             }
             if ((NL == 1 || NL == 2) && collect) copy_out<NV>(x, g);
@@ -466,18 +466,18 @@ __device__ void rank_end(const RankArgs &a, RankShared &s, unsigned int *scratch
     // The next pass: its prefix levels, its tables, its bits.
     int i1 = 0, i2 = 0, i3 = 0;
     const int n1 = prefix_index(s, m, 12, &i1);
-    if (NL == 0) wide = n1 <= Q_WIDE_BUCKETS && m <= Q_WIDE_RANKS ? 1 : 0;
-    const int next_width = wide ? (NL == 0 ? 12 : 8) : (NL == 0 ? 8 : 6);
+    if (NL == 0) wide = qp_wide(n1, m) ? 1 : 0;
+    const int next_width = qp_width(wide != 0, NL + 1);
     if (NL == 1) w2 = width;
     if (NL == 2) w3 = width;
     int n2 = 0, n3 = 0, t2_bytes = 0, t3_bytes = 0;
     if (NL >= 1) {
         n2 = prefix_index(s, m, 12 + w2, &i2);
-        t2_bytes = (n1 + 1) << w2;
+        t2_bytes = qp_table_bytes(n1, w2);
     }
     if (NL >= 2) {
         n3 = prefix_index(s, m, 12 + w2 + w3, &i3);
-        t3_bytes = (n2 + 1) << w3;
+        t3_bytes = qp_table_bytes(n2, w3);
     }
     const int words = (4096 + t2_bytes + t3_bytes) / 4;
     for (int i = tid; i < words; i += blockDim.x) scratch[i] = 0u;
@@ -487,11 +487,9 @@ __device__ void rank_end(const RankArgs &a, RankShared &s, unsigned int *scratch
         const unsigned int k = s.key[tid];
         t1[k >> 20] = (unsigned char)(i1 + 1);
         if (NL >= 1)
-            t1[4096 + (((i1 + 1) << w2) | (int)((k >> (20 - w2)) & ((1u << w2) - 1u)))] =
-                (unsigned char)(i2 + 1);
+            t1[4096 + qp_entry((unsigned int)i1 + 1u, k, 20 - w2, w2)] = (unsigned char)(i2 + 1);
         if (NL >= 2)
-            t1[4096 + t2_bytes +
-               (((i2 + 1) << w3) | (int)((k >> (20 - w2 - w3)) & ((1u << w3) - 1u)))] =
+            t1[4096 + t2_bytes + qp_entry((unsigned int)i2 + 1u, k, 20 - w2 - w3, w3)] =
                 (unsigned char)(i3 + 1);
     }
     __syncthreads();
@@ -562,10 +560,7 @@ __global__ void __launch_bounds__(Q_THREADS) k_quant(RankArgs a)
     const int nbins = 1 << width;
     const int tab_words = NL == 0 ? 0 : (4096 + (NL >= 2 ? t2_bytes : 0) +
                                          (NL >= 3 ? t3_bytes : 0)) / 4;
-    int clog = 0;
-    while (clog < a.max_clog &&
-           (unsigned int)((((slots * nbins) << (clog + 1)) + tab_words) * 4) <= a.lds_bytes)
-        ++clog;
+    const int clog = qp_copies_log2(slots, width, tab_words * 4, a.max_clog, a.lds_bytes);
     const int words = (slots * nbins) << clog;
     for (int i = tid; i < words; i += B) lds[i] = 0u;
     // The tables follow the histograms in LDS (all sizes are multiples of 4).
@@ -866,7 +861,7 @@ int run_passes(const Box &box, int mode, uint64_t rank, const double *q, int nq,
     a.max_clog = box.n < ((uint64_t)1 << 22) ? 1 : (box.n < ((uint64_t)1 << 25) ? 2 : 3);
     scan_geom(box, units, Q_THREADS, &a.g);
     const bool packed = a.g.pack.cb > 0;
-    const int passes = 2 * nq > Q_WIDE_BUCKETS ? 4 : 3;  // few ranks are always "wide"
+    const int passes = qp_wide(2 * nq, 2 * nq) ? 3 : 4;  // few ranks are always "wide"
     const size_t lds0 = (size_t)4096 * 4 << a.max_clog;
     int rc;
     if ((rc = rank_launch(quant_kernel<0>(packed), a, (int)blocks, lds0)) ||

@@ -1,8 +1,15 @@
-// cube_quantile_plan.h -- the host side of the quantile passes: which ranks
-// the levels need, the order of the key bits over the passes, the prefix
-// tables each pass reads, the choice of each rank's bin from the counts, and
-// the interpolation of the levels.  Plain C++ with no GPU calls: the caller
-// supplies the passes themselves (QuantPasses below).
+// cube_quantile_plan.h -- the plan of the quantile passes: which ranks the
+// levels need, the order of the key bits over the passes, the layout of the
+// prefix tables and histograms that a pass reads and counts in, the choice of
+// each rank's bin from the counts, and the interpolation of the levels.  Plain
+// C++ with no GPU call.
+//
+// The passes lay out one another on the device (rank_end in cube_quantile.hip).
+// What that layout and its lookups compute -- widths, entries, sizes, copies --
+// are the functions shared by both below (QP_HD).  quantiles_run and qp_tables
+// are the whole plan on the host with the same functions, over passes that the
+// caller supplies; the library does not run them, the CPU tests do, with every
+// index checked.
 //
 // The key of a float orders like its value (-0 before +0).  Pass 0 counts
 // the top 12 key bits of every valid voxel.  Then, when the ranks fall in at
@@ -23,10 +30,59 @@
 #include <algorithm>
 #include <vector>
 
+#if defined(__HIPCC__)
+#include <hip/hip_runtime.h>
+#define QP_HD __host__ __device__ __forceinline__
+#else
+#define QP_HD inline
+#endif
+
 namespace cube {
 
 constexpr int QP_TOP = 4096;                       // bins of the first pass
 constexpr size_t QP_TAB_MAX = 4096 + 9 * 4096 + 129 * 64;  // table bytes at most
+constexpr int QP_RANKS = 128;                      // ranks at most: index + 1 fits a byte
+constexpr int QP_COUNTERS = 32768;                 // slots << width at most
+constexpr size_t QP_LDS = 152 * 1024;              // a block's histograms and tables at most
+
+// Whether ranks in `buckets` distinct top buckets take 12 and 8 more bits.
+QP_HD bool qp_wide(int buckets, int ranks) { return buckets <= 8 && ranks <= 96; }
+
+// The bits that the pass with `levels` (1..3) prefix levels counts.
+QP_HD int qp_width(bool wide, int levels)
+{
+    return wide ? (levels == 1 ? 12 : 8) : (levels == 1 ? 8 : 6);
+}
+
+// Key bits [low, low + width).
+QP_HD unsigned int qp_field(unsigned int key, int low, int width)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_ubfe(key, (unsigned int)low, (unsigned int)width);
+#else
+    return (key >> low) & ((1u << width) - 1u);
+#endif
+}
+
+// The place of a key in a further table (g: the entry of the table before), or
+// in the counters (g: the prefix's row): row g, column the key's next bits.
+QP_HD unsigned int qp_entry(unsigned int g, unsigned int key, int low, int width)
+{
+    return (g << width) | qp_field(key, low, width);
+}
+
+// A further table's bytes: a row for every entry of the table before, and row 0.
+QP_HD int qp_table_bytes(int prefixes, int width) { return (prefixes + 1) << width; }
+
+// LDS copies (log2, at most `most`) of the histograms that fit beside the tables.
+QP_HD int qp_copies_log2(int slots, int width, int tab_bytes, int most, unsigned int lds_bytes)
+{
+    int clog = 0;
+    while (clog < most &&
+           (unsigned int)(((slots << width) << (clog + 1)) * 4 + tab_bytes) <= lds_bytes)
+        ++clog;
+    return clog;
+}
 
 // One refinement pass as the caller runs it.
 struct QuantPassSpec {
@@ -121,20 +177,21 @@ inline std::vector<unsigned int> qp_tables(const std::vector<QuantWant> &want, i
     if (nl < 2) return p1;
     const std::vector<unsigned int> p2 = qp_prefixes(want, 12 + lev[1]);
     unsigned char *t2 = t1 + QP_TOP;
-    *t2_bytes = (int)((p1.size() + 1) << lev[1]);
+    *t2_bytes = qp_table_bytes((int)p1.size(), lev[1]);
     memset(t2, 0, (size_t)*t2_bytes);
     for (size_t i = 0; i < p2.size(); ++i) {
         const unsigned int up = (unsigned int)qp_index(p1, p2[i] >> lev[1]) + 1;
-        t2[(up << lev[1]) | (p2[i] & ((1u << lev[1]) - 1u))] = (unsigned char)(i + 1);
+        t2[qp_entry(up, p2[i] << (20 - lev[1]), 20 - lev[1], lev[1])] = (unsigned char)(i + 1);
     }
     if (nl < 3) return p2;
     const std::vector<unsigned int> p3 = qp_prefixes(want, 12 + lev[1] + lev[2]);
     unsigned char *t3 = t2 + *t2_bytes;
-    *t3_bytes = (int)((p2.size() + 1) << lev[2]);
+    *t3_bytes = qp_table_bytes((int)p2.size(), lev[2]);
     memset(t3, 0, (size_t)*t3_bytes);
     for (size_t i = 0; i < p3.size(); ++i) {
         const unsigned int up = (unsigned int)qp_index(p2, p3[i] >> lev[2]) + 1;
-        t3[(up << lev[2]) | (p3[i] & ((1u << lev[2]) - 1u))] = (unsigned char)(i + 1);
+        const int low = 20 - lev[1] - lev[2];
+        t3[qp_entry(up, p3[i] << low, low, lev[2])] = (unsigned char)(i + 1);
     }
     return p3;
 }
@@ -167,16 +224,14 @@ int quantiles_run(Passes &passes, const double *q, int m, double *out, uint64_t 
         want[i].key = qp_pick_bin(h, QP_TOP, want[i].rank) << 20;
     }
 
-    const bool wide = qp_prefixes(want, 12).size() <= 8 && want.size() <= 96;
-    static const int wide_w[] = {12, 8}, narrow_w[] = {8, 6, 6};
-    const int *widths = wide ? wide_w : narrow_w;
+    const bool wide = qp_wide((int)qp_prefixes(want, 12).size(), (int)want.size());
     const int npass = wide ? 2 : 3;
     int lev[3] = {12, 0, 0};  // widths of the prefix levels
     int done = 12;            // key bits found so far
     for (int p = 0; p < npass; ++p) {
         QuantPassSpec s;
         s.nl = p + 1;
-        s.width = widths[p];
+        s.width = qp_width(wide, s.nl);
         s.shift = 32 - done - s.width;
         s.w2 = lev[1];
         s.w3 = lev[2];
