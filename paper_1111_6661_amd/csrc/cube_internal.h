@@ -87,16 +87,19 @@ struct PassArgs {
     unsigned long long *counts;  // device counts, nbins + 3 (histogram passes)
     HistRange *out_range;        // device [min, max] range (two-pass pass 1)
     int32_t accum_mode;          // CUBE_ACCUM_*
-    int32_t want_range;          // pass 1 of a two-pass call: write out_range
-    int32_t accumulate;          // add the counts to `counts` instead of writing them
+    // Flags.  Bytes, as 16 bytes more put the launch's own arguments (the block
+    // size), which follow these, on a cache line of their own: 0.3 us a call.
+    uint8_t want_range;          // pass 1 of a two-pass call: write out_range
+    uint8_t accumulate;          // add the counts to `counts` instead of writing them
+    uint8_t defer_bins;          // the bins are left to launch_hist_sum after the pass
+    uint8_t host;                // `out` and `counts` are host memory: written through
     int32_t n_chunks;            // 0: static partition; else chunks claimed at run time
-    unsigned int *dump;          // a row of counts per block; null: atomics on hist_acc
-    int32_t defer_bins;          // the bins are left to launch_hist_sum after the pass
-    const cube_stats_t *stats_in;  // a histogram pass's: an earlier one's, for `out` (host)
-    int32_t host;                // `out` and `counts` are host memory: written through
     unsigned int done_gen;       // written to *done (host memory too) once the results
     unsigned int *done;          // are there (with `host`); null: not wanted
+    unsigned int *dump;          // a row of counts per block; null: atomics on hist_acc
+    const cube_stats_t *stats_in;  // a histogram pass's: an earlier one's, for `out` (host)
 };
+static_assert(sizeof(PassArgs) <= 240, "the launch's own arguments share the last line");
 // Words in a block's row of PassArgs::dump.
 inline int dump_words(int hist, int nbins) { return hist == HIST_FINE ? FINE_WORDS : nbins; }
 
