@@ -35,8 +35,10 @@
  *   and NaN.  Counts are exact (integer atomics, order-free).
  * Valid range: lo, hi finite, hi >= lo, hi - lo finite in FP32, nbins/(hi-lo)
  *   finite in FP32 (when hi > lo), 1 <= nbins <= CUBE_MAX_BINS.
- * Precision: per-lane FP32 partial moments with compensated (TwoSum) chunk
- *   accumulation relative to a per-wavefront pivot, and one FP64 merge of the
+ * Precision: the squared deviations from a per-wavefront pivot are summed in
+ *   FP32 per lane with compensated (TwoSum) chunk accumulation; so are the
+ *   deviations themselves under a dynamic partition, while the other passes
+ *   and the batched queries sum x in FP64 per voxel.  One FP64 merge of the
  *   partials; mean and std agree with an FP64 evaluation of the definition to
  *   about 1e-7 relative.  Results are deterministic for a given input, shape
  *   and launch plan.
